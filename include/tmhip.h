@@ -403,7 +403,12 @@ int tm_grad_position(tm_ctx* ctx, int n_rhs, const tm_c128* mu, const tm_c128* s
 
 /* ---- matvec launch configuration (autotuner) ----------------------------- */
 
-/* Kernel variant and work split of the block matvec for one precision.
+/* The product with A runs by Fourier transform of the lattice by default,
+ * where a lattice fits it (a row or a column of at most 320 sites, and its
+ * column of coefficients in LDS: 320 sites to lmax 3, 150 at lmax 4, 100 (FP64)
+ * or 200 (complex64) above); else by the block kernels below, which this call
+ * also selects for its precision.
+ * Kernel variant and work split of the block matvec for one precision.
  * variant 0..7 (operands read from global memory): bit 0 = complex products
  * from three real matrix-core products (else four), bit 1 = operands of the
  * next displacement loaded during the current one's products, bit 2 =
@@ -421,8 +426,9 @@ int tm_get_matvec_config(tm_ctx* ctx, int precision, int* variant, int* items);
 
 /* Time the LDS-staged variants (8..10; FP64: 8, 9) with a few work-item
  * counts (4k..64k workgroups) on the current geometry for n_rhs right-hand
- * sides and keep the fastest for `precision`.  Synchronises; best_ms (host,
- * nullable) receives the best block-matvec time.  Without a call, FP64 uses
+ * sides, and the transformed product where the lattice fits it, and keep the
+ * fastest for `precision`.  Synchronises; best_ms (host, nullable) receives
+ * the best time of a product.  Without a call, FP64 uses
  * variant 9 and complex64 variant 8 with the default work split. */
 int tm_autotune(tm_ctx* ctx, int n_rhs, int precision, double* best_ms);
 

@@ -319,7 +319,7 @@ void tm_destroy(tm_ctx* c) {
   hipSetDevice(c->device);
   hipStreamSynchronize(c->stream);
   for (tmh::DevBuf* b : {&c->dtab[0], &c->dtab[1], &c->dtab[2], &c->dtab[3], &c->gpos, &c->jinc_buf,
-                        &c->gm_dev, &c->tmb, &c->tmflag})
+                        &c->gm_dev, &c->tmb, &c->tmflag, &c->spec_sym, &c->spec_w, &c->spec_const})
     tmh::release(*b);
   for (tmh::DevBuf* b : {&c->tab64, &c->tab32, &c->tabT64, &c->tabT32, &c->t64, &c->t32, &c->dt64,
                         &c->tden, &c->ttmp, &c->partial, &c->xlow, &c->work_a, &c->work_b, &c->work_c, &c->basis,
@@ -405,7 +405,9 @@ int tm_set_geometry(tm_ctx* c, int n, const double* pos, double k, int lmax) {
   tmh::host_slot_maps(lmax, g, c->maps);
   tmh::host_mblock_maps(lmax, c->mbmaps);
   c->have_geom = c->have_t = c->have_dt = c->have_tabT = c->have_dtab = c->t_dense = false;
-  c->t_mblock = false;
+  c->t_mblock = c->have_spec = false;
+  c->spec_fit[0] = tmh::spec_fits<double>(g, g.nx, g.ny, c->spec.X, c->spec.Y);
+  c->spec_fit[1] = tmh::spec_fits<float>(g, g.nx, g.ny, c->spec.X, c->spec.Y);
   c->plan_R[0] = c->plan_R[1] = -1;
   int rc;
   if (lattice) {
@@ -963,6 +965,7 @@ int tm_set_matvec_config(tm_ctx* c, int precision, int variant, int items) {
   const int w = precision == TM_PREC_MIXED ? 1 : 0;
   c->mv_variant[w] = variant;
   c->mv_items[w] = items;
+  c->mv_block[w] = true;
   return TM_OK;
 }
 

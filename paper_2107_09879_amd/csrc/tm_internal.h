@@ -89,6 +89,21 @@ struct SubParams {
 };
 
 
+// One axis of the transformed block matvec: n sites padded to P, the radices
+// of its stages (tm_spectral.hip).
+constexpr int SPEC_STAGES = 5, SPEC_P_MAX = 640;
+struct SpecDim {
+  int n, P, ns;
+  unsigned char r[SPEC_STAGES];
+};
+// A lattice's transformed blocks: symbol, twiddle factors, y frequency order.
+struct SpecPlan {
+  SpecDim X{}, Y{};
+  c128 *sym64 = nullptr, *twx64 = nullptr, *twy64 = nullptr;
+  c64 *sym32 = nullptr, *twx32 = nullptr, *twy32 = nullptr;
+  unsigned short* pos = nullptr;
+};
+
 // Workspace buffer that grows on demand.
 struct DevBuf {
   void* p = nullptr;
@@ -160,6 +175,14 @@ struct tm_ctx {
   // family (1 = direct, 2 = LDS-staged), R and work-item target
   int plan_kind[2] = {0, 0};
   int plan_R[2] = {-1, -1}, plan_target[2] = {0, 0}, plan_nitems[2] = {0, 0};
+  // transformed block matvec, the default where the lattice fits it: symbol and
+  // tables of the geometry (built on first use), grid workspace, constants of
+  // lmax; per precision slot whether it fits, and whether tm_set_matvec_config
+  // or tm_autotune asked for the block kernels instead
+  tmh::DevBuf spec_sym, spec_w, spec_const;
+  tmh::SpecPlan spec;
+  bool have_spec = false, spec_fit[2] = {false, false}, mv_block[2] = {false, false};
+  int spec_const_lmax = 0;
   int plan_nreg[2] = {0, 0};  // LDS plan: items of regular tiles (wide-tile items follow)
   int last_batch_graphed = 0;
   // batched solves: time the candidate launch configurations before solving
@@ -202,6 +225,15 @@ template <typename T>
 int offlattice_apply(tm_ctx* c, Op op, int R, const void* xin, const c128* x, c128* y);
 void detector_grad_constants(int lmax, std::vector<c128>& coef, std::vector<int>& dm);
 void host_slot_maps(int lmax, Geometry& g, SlotMaps& m);
+
+void table_constants(const Geometry& g, int Q, std::vector<double>& coef, std::vector<int>& dm,
+                     std::vector<int>& sig);
+
+// transformed block matvec (tm_spectral.hip)
+template <typename T>
+bool spec_fits(const Geometry& g, int nx, int ny, SpecDim& X, SpecDim& Y);
+template <typename T>
+int spec_apply(tm_ctx* c, Op op, int R, const c128* x, c128* y);
 
 // basis kernels (tm_basis.hip)
 int launch_mie(tm_ctx* c, const double* radii, double n_re, double n_im);

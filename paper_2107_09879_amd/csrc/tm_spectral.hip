@@ -1,0 +1,877 @@
+// Block matvec of a lattice by Fourier transform (App. I.D's matrix-free
+// product, for App. I.C's coupling A).
+//
+// On a lattice the blocks depend on the displacement alone, so A x is a 2-D
+// convolution.  On a zero-padded Px x Py grid (P >= 2 n - 1) it is
+//   y = F^-1 [ M^(k) F[x](k) ],   M^(k) = sum_d M(d) e^{-i k.d},
+// N log N work instead of N^2.  Every entry of a block is
+//   M_ij(d) = sum_q C_ijq h_q(k|d|) e^{i (m_j - m_i) phi(d)},
+// so M^ needs only the transforms of the (lmax + 1)(2 lmax + 1) scalar fields
+// h_q e^{i mu phi} (|mu| <= q, q + mu even: 28 at lmax 3, 91 at lmax 6), the
+// "symbol", and the blocks are formed from it where they are applied: 28 instead
+// of 450 numbers per grid point are read.  Three launches:
+//   spec_rows     rows of x: (T x,) to the grid's precision, transform along x
+//   spec_columns  columns: transform along y, block products, transform back
+//   spec_back     rows: transform back along x, y = x - T s etc.
+// A workgroup holds whole rows or columns of 16 (columns: S) slots in LDS; the
+// first and last stages of every transform read and write global memory from
+// registers.  Forward transforms are decimation in frequency, inverse ones
+// decimation in time, so that frequencies stay in digit-reversed order in
+// between and nothing is reordered.
+//
+// Two symmetries save work.  With x'_n = i^p x_n the constants C are real (the
+// N-M coupling is imaginary by itself).  Mirroring y maps phi to -phi, and with
+// U: a_(l,m,p) -> (-1)^p a_(l,-m,p) the blocks obey M^(kx, -ky) = U M^(kx, ky) U:
+// one formed block serves both ky and -ky.
+//
+// Bound: at 100x100, lmax 3 each launch moves 10-20 MB in a few microseconds and
+// the barriers and LDS round trips between stages set the time.  Operator with its
+// layout conversions, one right-hand side: 100x100 FP64 5.6 ms (block kernels) ->
+// 85 us, complex64 2.67 ms -> 78 us; 150x150 26.3 ms -> 220 us and 13.0 ms ->
+// 120 us; 33x31 at lmax 6 FP64 1.15 ms -> 128 us; 8x8 at lmax 2 100 -> 28 us, so no
+// lattice that fits is left to the block kernels.  Error against 64-bit sums of
+// the forward operator at 100x100: FP64 5.4e-16 (block kernels 1.3e-15), complex64
+// 9.7e-8 (6.1e-7).
+#include <algorithm>
+#include <cmath>
+#include <mutex>
+
+#include "tm_internal.h"
+#include "tm_spectral.h"
+
+namespace tmh {
+
+// ---------------------------------------------------------------- small DFTs
+template <typename T>
+__device__ __forceinline__ cplx<T> cadd(cplx<T> a, cplx<T> b) { return {a.re + b.re, a.im + b.im}; }
+template <typename T>
+__device__ __forceinline__ cplx<T> csub(cplx<T> a, cplx<T> b) { return {a.re - b.re, a.im - b.im}; }
+template <typename T>
+__device__ __forceinline__ cplx<T> cmulw(cplx<T> a, cplx<T> w, bool conj) {
+  const T wi = conj ? -w.im : w.im;
+  return {a.re * w.re - a.im * wi, a.re * wi + a.im * w.re};
+}
+// a * (-i) forward, a * (+i) inverse
+template <bool INV, typename T>
+__device__ __forceinline__ cplx<T> crot(cplx<T> a) {
+  return INV ? cplx<T>{-a.im, a.re} : cplx<T>{a.im, -a.re};
+}
+
+template <typename T, int R, bool INV>
+struct Dft;
+
+template <typename T, bool INV>
+struct Dft<T, 2, INV> {
+  static __device__ __forceinline__ void run(cplx<T>* a) {
+    const cplx<T> t = a[1];
+    a[1] = csub(a[0], t);
+    a[0] = cadd(a[0], t);
+  }
+};
+template <typename T, bool INV>
+struct Dft<T, 3, INV> {
+  static __device__ __forceinline__ void run(cplx<T>* a) {
+    constexpr T h = (T)0.86602540378443864676;
+    const cplx<T> s = cadd(a[1], a[2]), d = crot<INV>(csub(a[1], a[2]));
+    const cplx<T> m{a[0].re - (T)0.5 * s.re, a[0].im - (T)0.5 * s.im};
+    a[0] = cadd(a[0], s);
+    a[1] = {m.re + h * d.re, m.im + h * d.im};
+    a[2] = {m.re - h * d.re, m.im - h * d.im};
+  }
+};
+template <typename T, bool INV>
+struct Dft<T, 4, INV> {
+  static __device__ __forceinline__ void run(cplx<T>* a) {
+    const cplx<T> s0 = cadd(a[0], a[2]), d0 = csub(a[0], a[2]);
+    const cplx<T> s1 = cadd(a[1], a[3]), d1 = crot<INV>(csub(a[1], a[3]));
+    a[0] = cadd(s0, s1);
+    a[2] = csub(s0, s1);
+    a[1] = cadd(d0, d1);
+    a[3] = csub(d0, d1);
+  }
+};
+template <typename T, bool INV>
+struct Dft<T, 5, INV> {
+  static __device__ __forceinline__ void run(cplx<T>* a) {
+    // cos and sin of 2 pi / 5 and 4 pi / 5
+    constexpr T c1 = (T)0.30901699437494742410, c2 = (T)-0.80901699437494742410;
+    constexpr T s1 = (T)0.95105651629515357212, s2 = (T)0.58778525229247312917;
+    const cplx<T> p = cadd(a[1], a[4]), q = cadd(a[2], a[3]);
+    const cplx<T> u = crot<INV>(csub(a[1], a[4])), v = crot<INV>(csub(a[2], a[3]));
+    const cplx<T> m1{a[0].re + c1 * p.re + c2 * q.re, a[0].im + c1 * p.im + c2 * q.im};
+    const cplx<T> m2{a[0].re + c2 * p.re + c1 * q.re, a[0].im + c2 * p.im + c1 * q.im};
+    const cplx<T> n1{s1 * u.re + s2 * v.re, s1 * u.im + s2 * v.im};
+    const cplx<T> n2{s2 * u.re - s1 * v.re, s2 * u.im - s1 * v.im};
+    a[0] = cadd(a[0], cadd(p, q));
+    a[1] = cadd(m1, n1);
+    a[4] = csub(m1, n1);
+    a[2] = cadd(m2, n2);
+    a[3] = csub(m2, n2);
+  }
+};
+// coprime factors (Good's index maps: no twiddles)
+template <typename T, int A, int B, bool INV>
+__device__ __forceinline__ void dft_coprime(cplx<T>* a) {
+  constexpr int N = A * B;
+  cplx<T> t[B][A];
+#pragma unroll
+  for (int b = 0; b < B; ++b) {
+#pragma unroll
+    for (int i = 0; i < A; ++i) t[b][i] = a[(B * i + A * b) % N];
+    Dft<T, A, INV>::run(t[b]);
+  }
+#pragma unroll
+  for (int i = 0; i < A; ++i) {
+    cplx<T> u[B];
+#pragma unroll
+    for (int b = 0; b < B; ++b) u[b] = t[b][i];
+    Dft<T, B, INV>::run(u);
+    // the k with k = i (mod A), k = b (mod B)
+#pragma unroll
+    for (int k = 0; k < N; ++k)
+      if (k % A == i) a[k] = u[k % B];
+  }
+}
+template <typename T, bool INV>
+struct Dft<T, 6, INV> {
+  static __device__ __forceinline__ void run(cplx<T>* a) { dft_coprime<T, 3, 2, INV>(a); }
+};
+template <typename T, bool INV>
+struct Dft<T, 10, INV> {
+  static __device__ __forceinline__ void run(cplx<T>* a) { dft_coprime<T, 5, 2, INV>(a); }
+};
+template <typename T, bool INV>
+struct Dft<T, 12, INV> {
+  static __device__ __forceinline__ void run(cplx<T>* a) { dft_coprime<T, 3, 4, INV>(a); }
+};
+template <typename T, bool INV>
+struct Dft<T, 15, INV> {
+  static __device__ __forceinline__ void run(cplx<T>* a) { dft_coprime<T, 5, 3, INV>(a); }
+};
+template <typename T, bool INV>
+struct Dft<T, 8, INV> {
+  static __device__ __forceinline__ void run(cplx<T>* a) {
+    constexpr T h = (T)0.70710678118654752440;
+    cplx<T> e[4] = {a[0], a[2], a[4], a[6]}, o[4] = {a[1], a[3], a[5], a[7]};
+    Dft<T, 4, INV>::run(e);
+    Dft<T, 4, INV>::run(o);
+    // o[k] * w8^k: w8 = (1 -+ i) / sqrt 2
+    const cplx<T> r1 = crot<INV>(o[1]), r3 = crot<INV>(o[3]);
+    o[1] = {h * (o[1].re + r1.re), h * (o[1].im + r1.im)};
+    o[2] = crot<INV>(o[2]);
+    o[3] = {h * (r3.re - o[3].re), h * (r3.im - o[3].im)};
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      a[k] = cadd(e[k], o[k]);
+      a[k + 4] = csub(e[k], o[k]);
+    }
+  }
+};
+template <typename T, bool INV>
+struct Dft<T, 16, INV> {
+  static __device__ __forceinline__ void run(cplx<T>* a) {
+    constexpr T c1 = (T)0.92387953251128675613, s1 = (T)0.38268343236508977173;
+    constexpr T h = (T)0.70710678118654752440;
+    cplx<T> t[4][4];
+#pragma unroll
+    for (int b = 0; b < 4; ++b) {
+#pragma unroll
+      for (int i = 0; i < 4; ++i) t[b][i] = a[4 * i + b];
+      Dft<T, 4, INV>::run(t[b]);
+    }
+    // t[b][k] * w16^(b k)
+    const cplx<T> w1{c1, -s1}, w2{h, -h}, w3{s1, -c1}, w6{-h, -h}, w9{-c1, s1};
+    t[1][1] = cmulw(t[1][1], w1, INV);
+    t[1][2] = cmulw(t[1][2], w2, INV);
+    t[1][3] = cmulw(t[1][3], w3, INV);
+    t[2][1] = cmulw(t[2][1], w2, INV);
+    t[2][2] = crot<INV>(t[2][2]);
+    t[2][3] = cmulw(t[2][3], w6, INV);
+    t[3][1] = cmulw(t[3][1], w3, INV);
+    t[3][2] = cmulw(t[3][2], w6, INV);
+    t[3][3] = cmulw(t[3][3], w9, INV);
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      cplx<T> u[4] = {t[0][k], t[1][k], t[2][k], t[3][k]};
+      Dft<T, 4, INV>::run(u);
+#pragma unroll
+      for (int q = 0; q < 4; ++q) a[k + 4 * q] = u[q];
+    }
+  }
+};
+
+// ---------------------------------------------------------------- stages
+// One stage of a transform over positions of `P` = N blocks of the current
+// length N = R M, for W slots side by side.  ld(pos, slot), st(pos, slot, v).
+template <typename T, int R, int W, bool INV, class LD, class ST>
+__device__ __forceinline__ void fft_stage(int P, int N, const cplx<T>* __restrict__ tw, LD ld, ST st) {
+  const int M = N / R, stride = P / N;
+  const unsigned magic = (1u << 20) / (unsigned)M + 1u;  // b / M for b < 640
+  const int items = (P / R) * W;
+  for (int it = threadIdx.x; it < items; it += blockDim.x) {
+    const int slot = it % W, b = it / W;
+    const int blk = (int)(((unsigned)b * magic) >> 20), j = b - blk * M;
+    const int base = blk * N + j;
+    cplx<T> a[R];
+#pragma unroll
+    for (int k = 0; k < R; ++k) a[k] = ld(base + k * M, slot);
+    if (INV) {
+#pragma unroll
+      for (int k = 1; k < R; ++k) a[k] = cmulw(a[k], tw[j * k * stride], true);
+      Dft<T, R, true>::run(a);
+    } else {
+      Dft<T, R, false>::run(a);
+#pragma unroll
+      for (int k = 1; k < R; ++k) a[k] = cmulw(a[k], tw[j * k * stride], false);
+    }
+#pragma unroll
+    for (int k = 0; k < R; ++k) st(base + k * M, slot, a[k]);
+  }
+}
+template <typename T, int W, bool INV, class LD, class ST>
+__device__ __forceinline__ void fft_any(int R, int P, int N, const cplx<T>* __restrict__ tw, LD ld, ST st) {
+  switch (R) {
+    case 2: fft_stage<T, 2, W, INV>(P, N, tw, ld, st); break;
+    case 3: fft_stage<T, 3, W, INV>(P, N, tw, ld, st); break;
+    case 4: fft_stage<T, 4, W, INV>(P, N, tw, ld, st); break;
+    case 5: fft_stage<T, 5, W, INV>(P, N, tw, ld, st); break;
+    case 6: fft_stage<T, 6, W, INV>(P, N, tw, ld, st); break;
+    case 8: fft_stage<T, 8, W, INV>(P, N, tw, ld, st); break;
+    case 10: fft_stage<T, 10, W, INV>(P, N, tw, ld, st); break;
+    case 12: fft_stage<T, 12, W, INV>(P, N, tw, ld, st); break;
+    case 15: fft_stage<T, 15, W, INV>(P, N, tw, ld, st); break;
+    default: fft_stage<T, 16, W, INV>(P, N, tw, ld, st); break;
+  }
+}
+// Forward transform: the first stage reads through `ld`, the last writes
+// through `st` (at least two stages), LDS `sh` in between; inverse likewise
+// in the opposite stage order.
+template <typename T, int W, class LD, class ST>
+__device__ __forceinline__ void fft_forward(const SpecDim& d, const cplx<T>* __restrict__ tw, cplx<T>* sh,
+                                            LD ld, ST st) {
+  auto lds_ld = [&](int p, int s) { return sh[p * W + s]; };
+  auto lds_st = [&](int p, int s, cplx<T> v) { sh[p * W + s] = v; };
+  int N = d.P;
+  fft_any<T, W, false>(d.r[0], d.P, N, tw, ld, lds_st);
+  N /= d.r[0];
+  for (int s = 1; s + 1 < d.ns; ++s) {
+    __syncthreads();
+    fft_any<T, W, false>(d.r[s], d.P, N, tw, lds_ld, lds_st);
+    N /= d.r[s];
+  }
+  __syncthreads();
+  fft_any<T, W, false>(d.r[d.ns - 1], d.P, N, tw, lds_ld, st);
+}
+template <typename T, int W, class LD, class ST>
+__device__ __forceinline__ void fft_inverse(const SpecDim& d, const cplx<T>* __restrict__ tw, cplx<T>* sh,
+                                            LD ld, ST st) {
+  auto lds_ld = [&](int p, int s) { return sh[p * W + s]; };
+  auto lds_st = [&](int p, int s, cplx<T> v) { sh[p * W + s] = v; };
+  int N = d.r[d.ns - 1];
+  fft_any<T, W, true>(d.r[d.ns - 1], d.P, N, tw, ld, lds_st);
+  for (int s = d.ns - 2; s > 0; --s) {
+    __syncthreads();
+    N *= d.r[s];
+    fft_any<T, W, true>(d.r[s], d.P, N, tw, lds_ld, lds_st);
+  }
+  __syncthreads();
+  fft_any<T, W, true>(d.r[0], d.P, d.P, tw, lds_ld, st);
+}
+
+// ---------------------------------------------------------------- kernels
+extern __shared__ __align__(16) unsigned char spec_lds[];
+
+// multiply by i^p (p = 1 for N-type slots) or i^-p
+template <typename T>
+__device__ __forceinline__ cplx<T> quarter(cplx<T> v, bool p, bool back) {
+  return p ? (back ? cplx<T>{v.im, -v.re} : cplx<T>{-v.im, v.re}) : v;
+}
+
+template <typename T>
+__device__ __forceinline__ bool spec_skip(const SpecArgs<T>& a, int k, int r) {
+  return (a.stop && *a.stop) || (a.active && !a.active[k * a.R + r]);
+}
+
+// blockIdx.x: row (of a subregion), blockIdx.y: (rhs, class, slot group)
+template <typename T, bool MULT>
+__global__ __launch_bounds__(256) void spec_rows(SpecArgs<T> a) {
+  const int g = blockIdx.y % a.NG, c = (blockIdx.y / a.NG) & 1, r = blockIdx.y / (2 * a.NG);
+  const SpecJob job = a.row_jobs ? a.row_jobs[blockIdx.x] : SpecJob{0, (int)blockIdx.x};
+  if (spec_skip(a, job.sub, r)) return;
+  const SpecSub<T> s = a.subs ? a.subs[job.sub] : a.one;
+  cplx<T>* sh = reinterpret_cast<cplx<T>*>(spec_lds);
+  const int S = a.S, n = s.X.n, N = n * s.Y.n;
+  const size_t off = ((size_t)c * N + (size_t)job.index * n) * S + g * SLOTS;
+  const c128* x = a.x + s.vec_off + (size_t)r * 2 * N * S + off;
+  const c128* t = a.t + s.t_off + off;
+  cplx<T>* W = a.W + s.w_off + ((size_t)(r * 2 + c) * s.X.P * s.Y.n + job.index) * S + g * SLOTS;
+  const unsigned long long pm = a.pmask[c] >> (g * SLOTS);
+  const size_t wp = (size_t)s.Y.n * S;
+  fft_forward<T, SLOTS>(
+      s.X, s.twx, sh,
+      [&](int p, int slot) {
+        if (p >= n) return cplx<T>{(T)0, (T)0};
+        c128 v = x[(size_t)p * S + slot];
+        if (MULT) {
+          const c128 tv = t[(size_t)p * S + slot];
+          v = c128{tv.re * v.re - tv.im * v.im, tv.re * v.im + tv.im * v.re};
+        }
+        return quarter(cplx<T>{(T)v.re, (T)v.im}, (pm >> slot) & 1, false);
+      },
+      [&](int p, int slot, cplx<T> v) { W[(size_t)p * wp + slot] = v; });
+}
+
+// blockIdx.x: column (position of kx), blockIdx.y: (rhs, class).
+// Block products: S lanes per (ky, -ky) pair, lane i the target slot.
+template <typename T, int NG>
+__global__ __launch_bounds__(512) void spec_columns(SpecArgs<T> a) {
+  constexpr int S = NG * SLOTS, NQ = SpecCfg<NG>::NQ, NF = SpecCfg<NG>::NF;
+  constexpr int GROUPS = NG == 1 ? 4 : NG == 2 ? 2 : 1;  // pairs a wave works on
+  const int c = blockIdx.y & 1, r = blockIdx.y >> 1;
+  const SpecJob job = a.col_jobs ? a.col_jobs[blockIdx.x] : SpecJob{0, (int)blockIdx.x};
+  if (spec_skip(a, job.sub, r)) return;
+  const SpecSub<T> s = a.subs ? a.subs[job.sub] : a.one;
+  cplx<T>* sh = reinterpret_cast<cplx<T>*>(spec_lds);
+  cplx<T>* stage = sh + (size_t)s.Y.P * S;
+  const int ny = s.Y.n, P = s.Y.P;
+  cplx<T>* W = a.W + s.w_off + ((size_t)(r * 2 + c) * s.X.P + job.index) * ny * S;
+  auto lds_st = [&](int p, int slot, cplx<T> v) { sh[p * S + slot] = v; };
+  auto lds_ld = [&](int p, int slot) { return sh[p * S + slot]; };
+  fft_forward<T, S>(
+      s.Y, s.twy, sh,
+      [&](int p, int slot) { return p < ny ? W[p * S + slot] : cplx<T>{(T)0, (T)0}; }, lds_st);
+  __syncthreads();
+  {
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int grp = GROUPS == 1 ? 0 : lane / S, i = GROUPS == 1 ? lane : lane % S;
+    const int pairs = P / 2 + 1;
+    cplx<T>* f = stage + (size_t)(wave * GROUPS + grp) * NF;
+    const int* info = a.slots[c].info;
+    const T* cf = a.coef + (size_t)c * S * S * NQ + (size_t)i * NQ;
+    const unsigned char* f0 = a.first + (size_t)c * S * S + i;
+    const cplx<T>* sym = s.sym + (size_t)job.index * pairs * a.nf;
+    const int members = a.members;
+    for (int m = wave * GROUPS + grp; m - grp < pairs; m += GROUPS * (blockDim.x >> 6)) {
+      const bool ok = m < pairs && i < S;
+      if (ok)
+        for (int q = i; q < NF; q += S) f[q] = q < a.nf ? sym[(size_t)m * a.nf + q] : cplx<T>{(T)0, (T)0};
+      // one wave wrote what it reads: LDS operations of a wave stay in order
+      __builtin_amdgcn_wave_barrier();
+      if (ok && i < members) {
+        const int p1 = s.pos[m], p2 = m ? s.pos[P - m] : p1;
+        const cplx<T>* u = sh + p1 * S;
+        const cplx<T>* v = sh + p2 * S;
+        T yr = 0, yi = 0, zr = 0, zi = 0;
+        for (int j = 0; j < members; ++j) {
+          const T* cj = cf + (size_t)j * S * NQ;
+          const cplx<T>* fj = f + f0[j * S];
+          T mr = 0, mi = 0;
+#pragma unroll
+          for (int q = 0; q < NQ; ++q) {
+            const T cq = cj[q];
+            mr += cq * fj[q].re;
+            mi += cq * fj[q].im;
+          }
+          const cplx<T> b = u[j];
+          yr += mr * b.re - mi * b.im;
+          yi += mr * b.im + mi * b.re;
+          cplx<T> d = v[info[j] & 255];
+          if (info[j] >> 8) d = cplx<T>{-d.re, -d.im};
+          zr += mr * d.re - mi * d.im;
+          zi += mr * d.im + mi * d.re;
+        }
+        sh[p1 * S + i] = cplx<T>{yr, yi};
+        const int own = info[i];
+        if (p2 != p1) sh[p2 * S + (own & 255)] = (own >> 8) ? cplx<T>{-zr, -zi} : cplx<T>{zr, zi};
+      }
+      __builtin_amdgcn_wave_barrier();
+    }
+  }
+  __syncthreads();
+  fft_inverse<T, S>(
+      s.Y, s.twy, sh, lds_ld,
+      [&](int p, int slot, cplx<T> v) {
+        if (p < ny) W[p * S + slot] = v;
+      });
+}
+
+// blockIdx as spec_rows.  OP: y = x - T s, s, x - s
+template <typename T, int OP>
+__global__ __launch_bounds__(256) void spec_back(SpecArgs<T> a) {
+  const int g = blockIdx.y % a.NG, c = (blockIdx.y / a.NG) & 1, r = blockIdx.y / (2 * a.NG);
+  const SpecJob job = a.row_jobs ? a.row_jobs[blockIdx.x] : SpecJob{0, (int)blockIdx.x};
+  if (spec_skip(a, job.sub, r)) return;
+  const SpecSub<T> s = a.subs ? a.subs[job.sub] : a.one;
+  cplx<T>* sh = reinterpret_cast<cplx<T>*>(spec_lds);
+  const int S = a.S, n = s.X.n, N = n * s.Y.n;
+  const size_t off = ((size_t)c * N + (size_t)job.index * n) * S + g * SLOTS;
+  const size_t vo = s.vec_off + (size_t)r * 2 * N * S + off;
+  const c128* x = a.x + vo;
+  const c128* t = a.t + s.t_off + off;
+  c128* y = a.y + vo;
+  const cplx<T>* W = a.W + s.w_off + ((size_t)(r * 2 + c) * s.X.P * s.Y.n + job.index) * S + g * SLOTS;
+  const unsigned long long pm = a.pmask[c] >> (g * SLOTS);
+  const size_t wp = (size_t)s.Y.n * S;
+  fft_inverse<T, SLOTS>(
+      s.X, s.twx, sh, [&](int p, int slot) { return W[(size_t)p * wp + slot]; },
+      [&](int p, int slot, cplx<T> w) {
+        if (p >= n) return;
+        const cplx<T> q = quarter(w, (pm >> slot) & 1, true);
+        const size_t e = (size_t)p * S + slot;
+        c128 o{(double)q.re, (double)q.im};
+        if (OP == SPEC_FORWARD) {
+          const c128 tv = t[e], xv = x[e];
+          o = c128{xv.re - (tv.re * o.re - tv.im * o.im), xv.im - (tv.re * o.im + tv.im * o.re)};
+        } else if (OP == SPEC_MINUS) {
+          const c128 xv = x[e];
+          o = c128{xv.re - o.re, xv.im - o.im};
+        }
+        y[e] = o;
+      });
+}
+
+// ---------------------------------------------------------------- symbol
+// Rows of the scalar fields and their transform along x: blockIdx.x the
+// wrapped displacement row, blockIdx.y a group of 16 fields.
+__global__ __launch_bounds__(256) void spec_symbol_rows(SpecDim X, SpecDim Y, const c128* __restrict__ tw,
+                                                        const short2* __restrict__ fields, int nf,
+                                                        int qmax, double pitch, double k,
+                                                        c128* __restrict__ G, int ldf) {
+  c128* sh = reinterpret_cast<c128*>(spec_lds);
+  const int iy = blockIdx.x, f0 = blockIdx.y * SLOTS;
+  const int dy = iy < Y.n ? iy : iy - Y.P;
+  const bool row_in = dy > -Y.n;
+  for (int p = threadIdx.x; p < X.P; p += blockDim.x) {
+    const int dx = p < X.n ? p : p - X.P;
+    for (int s = 0; s < SLOTS; ++s) sh[p * SLOTS + s] = c128{0.0, 0.0};
+    if (!row_in || dx <= -X.n || (dx == 0 && dy == 0)) continue;
+    const double ax = pitch * dx, ay = pitch * dy;
+    const double phi = atan2(ay, ax), z = k * sqrt(ax * ax + ay * ay);
+    // h_q of the first kind by upward recurrence from h_-1 = e^{iz}/z, h_0 = -i e^{iz}/z
+    double sn, cs;
+    sincos(z, &sn, &cs);
+    const double iz = 1.0 / z;
+    c128 prev{cs * iz, sn * iz}, h{sn * iz, -cs * iz};
+    for (int q = 0; q <= qmax; ++q) {
+      for (int s = 0; s < SLOTS && f0 + s < nf; ++s) {
+        const short2 fd = fields[f0 + s];
+        if (fd.x != q) continue;
+        double es, ec;
+        sincos((double)fd.y * phi, &es, &ec);
+        sh[p * SLOTS + s] = c128{h.re * ec - h.im * es, h.re * es + h.im * ec};
+      }
+      const double f = (2 * q + 1) * iz;
+      const c128 next{f * h.re - prev.re, f * h.im - prev.im};
+      prev = h;
+      h = next;
+    }
+  }
+  __syncthreads();
+  auto lds_ld = [&](int p, int s) { return sh[p * SLOTS + s]; };
+  fft_forward<double, SLOTS>(X, tw, sh, lds_ld, [&](int p, int s, c128 v) {
+    G[((size_t)p * Y.P + iy) * ldf + f0 + s] = v;
+  });
+}
+// Columns: transform along y, the half 0 <= ky <= P/2 kept in frequency order,
+// scaled by 1/(Px Py), in both precisions.
+__global__ __launch_bounds__(256) void spec_symbol_columns(SpecDim X, SpecDim Y, const c128* __restrict__ tw,
+                                                           const unsigned short* __restrict__ pos, int nf,
+                                                           const c128* __restrict__ G, int ldf,
+                                                           c128* __restrict__ sym64,
+                                                           c64* __restrict__ sym32) {
+  c128* sh = reinterpret_cast<c128*>(spec_lds);
+  const int p = blockIdx.x, f0 = blockIdx.y * SLOTS, pairs = Y.P / 2 + 1;
+  const double scale = 1.0 / ((double)X.P * (double)Y.P);
+  fft_forward<double, SLOTS>(
+      Y, tw, sh, [&](int q, int s) { return G[((size_t)p * Y.P + q) * ldf + f0 + s]; },
+      [&](int q, int s, c128 v) { sh[q * SLOTS + s] = v; });
+  __syncthreads();
+  for (int e = threadIdx.x; e < pairs * SLOTS; e += blockDim.x) {
+    const int s = e % SLOTS, m = e / SLOTS;
+    if (f0 + s >= nf) continue;
+    const c128 v = sh[pos[m] * SLOTS + s];
+    const size_t o = ((size_t)p * pairs + m) * nf + f0 + s;
+    sym64[o] = c128{v.re * scale, v.im * scale};
+    sym32[o] = c64{(float)(v.re * scale), (float)(v.im * scale)};
+  }
+}
+
+// ---------------------------------------------------------------- host
+namespace {
+
+const int kRadices[] = {16, 15, 12, 10, 8, 6, 5, 4, 3, 2};
+
+// Fewest stages (at least two) with radices of the set; 0 if there are none.
+int factor(int P, int depth, unsigned char* r) {
+  if (depth == 1) {
+    for (int v : kRadices)
+      if (v == P) {
+        r[0] = (unsigned char)v;
+        return 1;
+      }
+    return 0;
+  }
+  for (int v : kRadices) {
+    if (P % v) continue;
+    r[0] = (unsigned char)v;
+    if (factor(P / v, depth - 1, r + 1)) return depth;
+  }
+  return 0;
+}
+
+}  // namespace
+
+// Padded length of n sites: at least 2n - 1, whole stages, and the least
+// P (1 + 0.15 stages): a stage costs a pass through LDS and a barrier.
+bool spec_dim(int n, SpecDim& d) {
+  double best = 1e300;
+  d = SpecDim{};
+  for (int P = std::max(4, 2 * n - 1); P <= SPEC_P_MAX && P < 3 * n + 8; ++P) {
+    unsigned char r[SPEC_STAGES] = {0};
+    int ns = 0;
+    for (int depth = 2; depth <= SPEC_STAGES && !ns; ++depth) ns = factor(P, depth, r);
+    if (!ns) continue;
+    const double cost = P * (1.0 + 0.15 * ns);
+    if (cost < best) {
+      best = cost;
+      d.n = n;
+      d.P = P;
+      d.ns = ns;
+      for (int s = 0; s < SPEC_STAGES; ++s) d.r[s] = r[s];
+    }
+  }
+  return d.P > 0;
+}
+
+// e^{-2 pi i k / P} and the position of every frequency after the forward stages
+void spec_tables(const SpecDim& d, std::vector<c128>& tw, std::vector<unsigned short>& pos) {
+  tw.resize(d.P);
+  pos.resize(d.P);
+  const long double w = 2.0L * acosl(-1.0L) / d.P;
+  for (int k = 0; k < d.P; ++k) {
+    tw[k] = c128{(double)cosl(w * k), (double)-sinl(w * k)};
+    int f = k, p = 0, len = d.P;
+    for (int s = 0; s < d.ns; ++s) {
+      len /= d.r[s];
+      p += (f % d.r[s]) * len;
+      f /= d.r[s];
+    }
+    pos[k] = (unsigned short)p;
+  }
+}
+
+namespace {
+
+// What depends on lmax alone: the scalar fields, and for A and A^T the real
+// constants [class][source j][target i][NQ] with the index of their first field.
+struct SpecConst {
+  int nf = 0, NQ = 0, S = 0, members = 0, qmax = 0;
+  std::vector<short2> fields;
+  std::vector<double> coef[2];
+  std::vector<unsigned char> first[2];
+  SpecSlots slots[2];
+  unsigned long long pmask[2] = {0, 0};
+};
+
+const SpecConst& spec_constants(const Geometry& g) {
+  static std::mutex mu;
+  static SpecConst cache[LMAX_SUPPORTED + 1];
+  std::lock_guard<std::mutex> lk(mu);
+  SpecConst& k = cache[g.lmax];
+  if (k.nf) return k;
+  const int S = g.S, Q = 2 * g.lmax + 1;
+  k.S = S;
+  k.qmax = 2 * g.lmax;
+  k.members = g.L / 2;
+  k.NQ = g.NG == 1 ? SpecCfg<1>::NQ : g.NG == 2 ? SpecCfg<2>::NQ : SpecCfg<3>::NQ;
+  // fields in order of mu, then of q (steps of two)
+  std::vector<int> start(2 * k.qmax + 1, 0);
+  int nf = 0;
+  for (int mu_ = -k.qmax; mu_ <= k.qmax; ++mu_) {
+    start[mu_ + k.qmax] = nf;
+    for (int q = std::abs(mu_); q <= k.qmax; q += 2, ++nf) {
+      short2 f;
+      f.x = (short)q;
+      f.y = (short)mu_;
+      k.fields.push_back(f);
+    }
+  }
+  std::vector<double> coef;
+  std::vector<int> dm, sig;
+  table_constants(g, Q, coef, dm, sig);
+  std::vector<int> pt(g.L), bar(g.L);
+  const int half = g.L / 2;
+  for (int n = 0; n < g.L; ++n) {
+    pt[n] = n / half;
+    const int rr = n % half;
+    int l = 1;
+    while ((l + 1) * (l + 1) - 1 <= rr) ++l;
+    const int m = rr - (l * (l + 1) - 1);
+    bar[n] = n - 2 * m;  // (l, -m, p)
+  }
+  for (int c = 0; c < NCLASS; ++c) {
+    for (int i = 0; i < S; ++i) {
+      const int n = g.n_of[c][i];
+      k.slots[c].info[i] = n < 0 ? i : g.slot_of[bar[n]] | (pt[n] << 8);
+      if (n >= 0 && pt[n]) k.pmask[c] |= 1ull << i;
+    }
+  }
+  for (int tr = 0; tr < 2; ++tr) {
+    k.coef[tr].assign((size_t)NCLASS * S * S * k.NQ, 0.0);
+    k.first[tr].assign((size_t)NCLASS * S * S, 0);
+    for (int c = 0; c < NCLASS; ++c)
+      for (int i = 0; i < S; ++i)
+        for (int j = 0; j < S; ++j) {
+          if (g.n_of[c][i] < 0 || g.n_of[c][j] < 0) continue;
+          // A: C_ij on field mu = m_j - m_i.  A^T at k is the transpose of M^(-k): C_ji on
+          // field m_i - m_j with the sign (-1)^mu
+          const int ti = tr ? j : i, sj = tr ? i : j;
+          const int mu_ = dm[(c * S + ti) * S + sj];
+          const double sgn = (tr && (mu_ & 1)) ? -1.0 : 1.0;
+          const int pi = pt[g.n_of[c][i]], pj = pt[g.n_of[c][j]];
+          const double* cq = coef.data() + (((size_t)(c * S + ti) * S + sj) * Q) * 2;
+          int q0 = -1, terms = 0;
+          double* out = k.coef[tr].data() + ((size_t)(c * S + j) * S + i) * k.NQ;
+          for (int q = std::abs(mu_); q <= k.qmax; q += 2) {
+            const double re = cq[2 * q], im = cq[2 * q + 1];
+            if (re == 0.0 && im == 0.0 && q0 < 0) continue;
+            if (q0 < 0) q0 = q;
+            const int t = (q - q0) / 2;
+            // i^(p_i - p_j) C is real
+            const double v = pi == pj ? re : (pi < pj ? im : -im);
+            if (v != 0.0) terms = t + 1;
+            if (t < k.NQ) out[t] = sgn * v;
+          }
+          if (q0 < 0) q0 = std::abs(mu_);
+          if (terms > k.NQ) k.nf = -1;  // not reached: at most lmax + 1 terms
+          k.first[tr][(size_t)(c * S + j) * S + i] =
+              (unsigned char)(start[mu_ + k.qmax] + (q0 - std::abs(mu_)) / 2);
+        }
+  }
+  k.nf = nf;
+  return k;
+}
+
+template <typename T>
+size_t columns_lds(const SpecDim& Y, int S, int NG, int threads) {
+  const int groups = (threads / 64) * (NG == 1 ? 4 : NG == 2 ? 2 : 1);
+  const int NF = NG == 1 ? SpecCfg<1>::NF : NG == 2 ? SpecCfg<2>::NF : SpecCfg<3>::NF;
+  return ((size_t)Y.P * S + (size_t)groups * NF) * sizeof(cplx<T>);
+}
+size_t align256(size_t b) { return (b + 255) & ~(size_t)255; }
+
+}  // namespace
+
+size_t spec_w_elems(const SpecDim& X, const SpecDim& Y, int S) {
+  return (size_t)NCLASS * X.P * Y.n * S;
+}
+
+// Whether a lattice's columns fit one workgroup's LDS at this precision.
+template <typename T>
+bool spec_fits(const Geometry& g, int nx, int ny, SpecDim& X, SpecDim& Y) {
+  if (!g.lattice || !spec_dim(nx, X) || !spec_dim(ny, Y)) return false;
+  return (size_t)X.P * SLOTS * sizeof(c128) <= SPEC_LDS_MAX &&
+         (size_t)Y.P * SLOTS * sizeof(c128) <= SPEC_LDS_MAX &&
+         columns_lds<T>(Y, g.S, g.NG, 256) <= SPEC_LDS_MAX;
+}
+template bool spec_fits<float>(const Geometry&, int, int, SpecDim&, SpecDim&);
+template bool spec_fits<double>(const Geometry&, int, int, SpecDim&, SpecDim&);
+
+static int allow_lds(tm_ctx* c, const void* f, size_t bytes) {
+  if (bytes <= 64 * 1024) return TM_OK;
+  TM_HIP(c, hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes));
+  return TM_OK;
+}
+
+// Constants of the geometry's lmax on the device (once per lmax of a context).
+static int spec_upload_constants(tm_ctx* c) {
+  if (c->spec_const_lmax == c->g.lmax) return TM_OK;
+  const SpecConst& k = spec_constants(c->g);
+  const size_t nc = k.coef[0].size(), nb = k.first[0].size();
+  SpecConstLayout L = spec_const_layout(k.S, k.NQ, (int)k.fields.size());
+  std::vector<unsigned char> h(L.bytes, 0);
+  for (int tr = 0; tr < 2; ++tr) {
+    double* d = reinterpret_cast<double*>(h.data() + L.coef64[tr]);
+    float* f = reinterpret_cast<float*>(h.data() + L.coef32[tr]);
+    for (size_t e = 0; e < nc; ++e) {
+      d[e] = k.coef[tr][e];
+      f[e] = (float)k.coef[tr][e];
+    }
+    std::copy(k.first[tr].begin(), k.first[tr].begin() + nb, h.begin() + L.first[tr]);
+  }
+  std::copy(k.fields.begin(), k.fields.end(), reinterpret_cast<short2*>(h.data() + L.fields));
+  int rc;
+  if ((rc = ensure(c, c->spec_const, L.bytes)) != TM_OK) return rc;
+  TM_HIP(c, hipStreamSynchronize(c->stream));  // earlier products may still read the old ones
+  TM_HIP(c, hipMemcpy(c->spec_const.p, h.data(), L.bytes, hipMemcpyHostToDevice));
+  c->spec_const_lmax = c->g.lmax;
+  return TM_OK;
+}
+
+// Device bytes of one lattice's symbol with its transform tables.
+size_t spec_plan_bytes(const Geometry& g, const SpecDim& X, const SpecDim& Y) {
+  const int nf = (g.lmax + 1) * (2 * g.lmax + 1);
+  const size_t ns = (size_t)X.P * (Y.P / 2 + 1) * nf;
+  return align256(ns * sizeof(c128)) + align256(ns * sizeof(c64)) +
+         2 * (align256(X.P * sizeof(c128)) + align256(Y.P * sizeof(c128))) + align256(Y.P * 2);
+}
+
+// Builds the symbol of an nx x ny lattice of the context's pitch into `buf`
+// (spec_plan_bytes) with the scratch `tmp` (spec_tmp_bytes), on the stream.
+size_t spec_tmp_bytes(const Geometry& g, const SpecDim& X, const SpecDim& Y) {
+  const int nf = (g.lmax + 1) * (2 * g.lmax + 1);
+  return (size_t)X.P * Y.P * (SLOTS * ((nf + SLOTS - 1) / SLOTS)) * sizeof(c128);
+}
+int spec_build(tm_ctx* c, int nx, int ny, void* buf, void* tmp, SpecPlan& pl) {
+  const Geometry& g = c->g;
+  int rc;
+  if ((rc = spec_upload_constants(c)) != TM_OK) return rc;
+  if (!spec_dim(nx, pl.X) || !spec_dim(ny, pl.Y)) return set_err(c, TM_ERR_INVALID_ARG, "lattice too long to transform");
+  const SpecConst& k = spec_constants(g);
+  const SpecDim &X = pl.X, &Y = pl.Y;
+  const int nf = k.nf, groups = (nf + SLOTS - 1) / SLOTS, ldf = groups * SLOTS;
+  const size_t ns = (size_t)X.P * (Y.P / 2 + 1) * nf;
+  char* b = static_cast<char*>(buf);
+  auto take = [&](size_t bytes) {
+    char* p = b;
+    b += align256(bytes);
+    return p;
+  };
+  pl.sym64 = (c128*)take(ns * sizeof(c128));
+  pl.sym32 = (c64*)take(ns * sizeof(c64));
+  char* tables = b;
+  pl.twx64 = (c128*)take(X.P * sizeof(c128));
+  pl.twy64 = (c128*)take(Y.P * sizeof(c128));
+  pl.twx32 = (c64*)take(X.P * sizeof(c128));
+  pl.twy32 = (c64*)take(Y.P * sizeof(c128));
+  pl.pos = (unsigned short*)take(Y.P * 2);
+  std::vector<unsigned char> h((size_t)(b - tables), 0);
+  std::vector<c128> tw;
+  std::vector<unsigned short> pos;
+  for (int axis = 0; axis < 2; ++axis) {
+    spec_tables(axis ? Y : X, tw, pos);
+    c128* d = reinterpret_cast<c128*>(h.data() + ((char*)(axis ? pl.twy64 : pl.twx64) - tables));
+    c64* f = reinterpret_cast<c64*>(h.data() + ((char*)(axis ? pl.twy32 : pl.twx32) - tables));
+    for (size_t e = 0; e < tw.size(); ++e) {
+      d[e] = tw[e];
+      f[e] = c64{(float)tw[e].re, (float)tw[e].im};
+    }
+  }
+  std::copy(pos.begin(), pos.end(), reinterpret_cast<unsigned short*>(h.data() + ((char*)pl.pos - tables)));
+  // the upload is not ordered with a non-blocking stream: what it replaces must be done with
+  TM_HIP(c, hipStreamSynchronize(c->stream));
+  TM_HIP(c, hipMemcpy(tables, h.data(), h.size(), hipMemcpyHostToDevice));
+  const SpecConstLayout L = spec_const_layout(k.S, k.NQ, nf);
+  const short2* fields = (const short2*)((char*)c->spec_const.p + L.fields);
+  const size_t lx = (size_t)X.P * SLOTS * sizeof(c128), ly = (size_t)Y.P * SLOTS * sizeof(c128);
+  if ((rc = allow_lds(c, (const void*)spec_symbol_rows, lx)) != TM_OK) return rc;
+  if ((rc = allow_lds(c, (const void*)spec_symbol_columns, ly)) != TM_OK) return rc;
+  hipLaunchKernelGGL(spec_symbol_rows, dim3(Y.P, groups), dim3(256), lx, c->stream, X, Y, pl.twx64, fields,
+                     nf, k.qmax, g.pitch, g.k, (c128*)tmp, ldf);
+  hipLaunchKernelGGL(spec_symbol_columns, dim3(X.P, groups), dim3(256), ly, c->stream, X, Y, pl.twy64, pl.pos,
+                     nf, (const c128*)tmp, ldf, pl.sym64, pl.sym32);
+  TM_HIP(c, hipGetLastError());
+  return TM_OK;
+}
+
+template <typename T>
+SpecSub<T> spec_sub(const SpecPlan& p) {
+  SpecSub<T> s{};
+  s.X = p.X;
+  s.Y = p.Y;
+  if constexpr (std::is_same<T, double>::value) {
+    s.twx = p.twx64;
+    s.twy = p.twy64;
+    s.sym = p.sym64;
+  } else {
+    s.twx = p.twx32;
+    s.twy = p.twy32;
+    s.sym = p.sym32;
+  }
+  s.pos = p.pos;
+  return s;
+}
+template SpecSub<float> spec_sub<float>(const SpecPlan&);
+template SpecSub<double> spec_sub<double>(const SpecPlan&);
+
+template <typename T>
+void spec_fill_args(tm_ctx* c, bool transposed, SpecArgs<T>& a) {
+  const SpecConst& k = spec_constants(c->g);
+  const SpecConstLayout L = spec_const_layout(k.S, k.NQ, k.nf);
+  char* b = (char*)c->spec_const.p;
+  a.coef = (const T*)(b + (std::is_same<T, double>::value ? L.coef64[transposed] : L.coef32[transposed]));
+  a.first = (const unsigned char*)(b + L.first[transposed]);
+  a.S = c->g.S;
+  a.NG = c->g.NG;
+  a.nf = k.nf;
+  a.members = k.members;
+  for (int q = 0; q < NCLASS; ++q) {
+    a.slots[q] = k.slots[q];
+    a.pmask[q] = k.pmask[q];
+  }
+}
+template void spec_fill_args<float>(tm_ctx*, bool, SpecArgs<float>&);
+template void spec_fill_args<double>(tm_ctx*, bool, SpecArgs<double>&);
+
+// The three launches; rows, columns: workgroups over all subregions, Pxmax and
+// Pymax the longest transforms among them.
+template <typename T>
+int spec_launch(tm_ctx* c, const SpecArgs<T>& a, Op op, int rows, int columns, int Pxmax, const SpecDim& Ymax) {
+  const size_t lx = (size_t)Pxmax * SLOTS * sizeof(cplx<T>);
+  // longer columns get more waves (one workgroup per CU then)
+  int threads = Ymax.P * a.S * (int)sizeof(cplx<T>) > 80 * 1024 ? 512 : 256;
+  if (columns_lds<T>(Ymax, a.S, a.NG, threads) > SPEC_LDS_MAX) threads = 256;
+  const size_t ly = columns_lds<T>(Ymax, a.S, a.NG, threads);
+  const dim3 gr(rows, 2 * a.NG * a.R), gc(columns, 2 * a.R);
+  int rc;
+  const void* kr = op == Op::Adjoint ? (const void*)spec_rows<T, true> : (const void*)spec_rows<T, false>;
+  const void* kc = a.NG == 1 ? (const void*)spec_columns<T, 1>
+                   : a.NG == 2 ? (const void*)spec_columns<T, 2> : (const void*)spec_columns<T, 3>;
+  const void* kb = op == Op::Forward   ? (const void*)spec_back<T, SPEC_FORWARD>
+                   : op == Op::Adjoint ? (const void*)spec_back<T, SPEC_MINUS> : (const void*)spec_back<T, SPEC_PLAIN>;
+  if ((rc = allow_lds(c, kr, lx)) != TM_OK || (rc = allow_lds(c, kc, ly)) != TM_OK ||
+      (rc = allow_lds(c, kb, lx)) != TM_OK)
+    return rc;
+  void* args[] = {const_cast<SpecArgs<T>*>(&a)};
+  TM_HIP(c, hipLaunchKernel(kr, gr, dim3(256), args, lx, c->stream));
+  TM_HIP(c, hipLaunchKernel(kc, gc, dim3(threads), args, ly, c->stream));
+  TM_HIP(c, hipLaunchKernel(kb, gr, dim3(256), args, lx, c->stream));
+  return TM_OK;
+}
+template int spec_launch<float>(tm_ctx*, const SpecArgs<float>&, Op, int, int, int, const SpecDim&);
+template int spec_launch<double>(tm_ctx*, const SpecArgs<double>&, Op, int, int, int, const SpecDim&);
+
+// The context's own lattice: symbol (built on first use) and grid workspace.
+int spec_ready(tm_ctx* c, size_t w_bytes) {
+  const Geometry& g = c->g;
+  const SpecDim X = c->spec.X, Y = c->spec.Y;
+  int rc;
+  if ((rc = ensure(c, c->spec_w, c->have_spec ? w_bytes : std::max(w_bytes, spec_tmp_bytes(g, X, Y)))) != TM_OK)
+    return rc;
+  if (c->have_spec) return TM_OK;
+  if ((rc = ensure(c, c->spec_sym, spec_plan_bytes(g, X, Y))) != TM_OK) return rc;
+  if ((rc = spec_build(c, g.nx, g.ny, c->spec_sym.p, c->spec_w.p, c->spec)) != TM_OK) return rc;
+  c->have_spec = true;
+  return TM_OK;
+}
+
+template <typename T>
+int spec_apply(tm_ctx* c, Op op, int R, const c128* x, c128* y) {
+  const Geometry& g = c->g;
+  int rc;
+  if ((rc = spec_ready(c, spec_w_elems(c->spec.X, c->spec.Y, g.S) * R * sizeof(cplx<T>))) != TM_OK) return rc;
+  SpecArgs<T> a{};
+  spec_fill_args<T>(c, op == Op::Adjoint || op == Op::CouplingT, a);
+  a.one = spec_sub<T>(c->spec);
+  a.x = x;
+  a.t = (const c128*)c->t64.p;
+  a.y = y;
+  a.W = (cplx<T>*)c->spec_w.p;
+  a.stop = c->mv_stop;
+  a.R = R;
+  return spec_launch<T>(c, a, op, g.ny, c->spec.X.P, c->spec.X.P, c->spec.Y);
+}
+template int spec_apply<float>(tm_ctx*, Op, int, const c128*, c128*);
+template int spec_apply<double>(tm_ctx*, Op, int, const c128*, c128*);
+
+}  // namespace tmh

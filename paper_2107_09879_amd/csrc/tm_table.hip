@@ -94,8 +94,8 @@ void host_slot_maps(int lmax, Geometry& g, SlotMaps& mp) {
 
 // Host constants: coef[c][i][j][q] (i target slot, j source slot) and
 // dm[c][i][j] = m_src - m_tgt, sig[c][i] = (-1)^(l+p).
-static void host_table_constants(const Geometry& g, int Q, std::vector<double>& coef,
-                                 std::vector<int>& dm, std::vector<int>& sig) {
+void table_constants(const Geometry& g, int Q, std::vector<double>& coef, std::vector<int>& dm,
+                     std::vector<int>& sig) {
   const int S = g.S;
   coef.assign((size_t)NCLASS * S * S * Q * 2, 0.0);
   dm.assign((size_t)NCLASS * S * S, 0);
@@ -361,7 +361,7 @@ int build_derivative_tables(tm_ctx* c) {
   std::vector<double> coef;
   std::vector<int> dm, sig;
   const int qmax = 2 * g.lmax;
-  host_table_constants(g, qmax + 1, coef, dm, sig);
+  table_constants(g, qmax + 1, coef, dm, sig);
   const long long D = g.n_disp();
   const size_t blk = (size_t)NCLASS * g.S * g.S;
   int rc;
@@ -410,7 +410,7 @@ static int build_impl(tm_ctx* c, DevBuf& t64, DevBuf& t32, int transpose) {
   std::vector<double> coef;
   std::vector<int> dm, sig;
   const int qmax = 2 * g.lmax;
-  host_table_constants(g, qmax + 1, coef, dm, sig);
+  table_constants(g, qmax + 1, coef, dm, sig);
   const long long D = g.n_disp();
   const size_t blk = (size_t)NCLASS * g.S * g.S;
   int rc;
@@ -471,7 +471,7 @@ int build_offlattice_constants(tm_ctx* c) {
   std::vector<double> coef;
   std::vector<int> dm, sig;
   const int Q = 2 * g.lmax + 1;
-  host_table_constants(g, Q, coef, dm, sig);
+  table_constants(g, Q, coef, dm, sig);
   // followed by an FP32 copy of coef for the complex64 kernel (no conversion per use)
   std::vector<float> coef32(coef.begin(), coef.end());
   const size_t cb = coef.size() * sizeof(double), db = dm.size() * sizeof(int);
