@@ -1,10 +1,5 @@
-// C ABI of libtmhip: context, set-up, restarted GMRES drivers, readout and
-// sensitivities.  The host enqueues whole GMRES cycles; every vector
-// operation, reduction, matvec, Givens rotation and the least-squares solve
-// is a HIP kernel on the context stream.  Per cycle the host reads back one
-// record (the true residual norm, the number of Arnoldi steps taken, a
-// non-finite flag): the steps of a cycle after its convergence test fired
-// on the device return at once.
+// C ABI of libtmhip: context, set-up, solve drivers, readout and
+// sensitivities.
 //
 // Solver (App. I.D: matrix-free matvecs inside GMRES; the preconditioned
 // system of App. I.C):
@@ -20,6 +15,7 @@
 #include <complex>
 #include <cstring>
 
+#include "tm_arnoldi.h"
 #include "tm_internal.h"
 
 using tmh::c128;
@@ -57,19 +53,6 @@ void release(DevBuf& b) {
   b.bytes = 0;
 }
 
-int ensure_pinned(tm_ctx* c, size_t bytes) {
-  if (c->host_pinned_bytes >= bytes) return TM_OK;
-  if (c->host_pinned) hipHostFree(c->host_pinned);
-  c->host_pinned = nullptr;
-  c->host_pinned_bytes = 0;
-  if (hipHostMalloc(&c->host_pinned, bytes, hipHostMallocDefault) != hipSuccess) {
-    (void)hipGetLastError();
-    return set_err(c, TM_ERR_OOM, "pinned host allocation failed");
-  }
-  c->host_pinned_bytes = bytes;
-  return TM_OK;
-}
-
 // Plane-wave incidences: khat unit vectors, pol finite and transverse.
 int validate_incidence(tm_ctx* c, int R, const double* khat, const tm_c128* pol) {
   for (int r = 0; r < R; ++r) {
@@ -87,169 +70,6 @@ int validate_incidence(tm_ctx* c, int R, const double* khat, const tm_c128* pol)
     if (std::hypot(dr, di) > 1e-9)
       return set_err(c, TM_ERR_INVALID_ARG, "polarisation must be transverse to khat");
   }
-  return TM_OK;
-}
-
-// ---------------------------------------------------------------- GMRES
-struct Gm {
-  tm_ctx* c;
-  Op op;
-  long long len;
-  int nblk;
-  c128 *V, *w, *r, *dots, *dots2, *dp;
-  double *np, *nout;
-};
-
-static double dev_norm(Gm& G, const c128* v) {
-  k_norm2_partial(G.c->stream, v, G.len, G.np, G.nblk);
-  k_reduce_norm(G.c->stream, G.np, G.nblk, G.nout);
-  double h = 0.0;
-  hipMemcpyAsync(G.c->host_pinned, G.nout, sizeof(double), hipMemcpyDeviceToHost, G.c->stream);
-  hipStreamSynchronize(G.c->stream);
-  std::memcpy(&h, G.c->host_pinned, sizeof(double));
-  return h;
-}
-
-// x (slot, one RHS) solves B x = b with B the operator `op`.
-static int gmres(tm_ctx* c, Op op, const c128* b, c128* x, const tm_solve_opts& o, bool use_x0,
-                 tm_solve_info& info) {
-  const Geometry& g = c->g;
-  const long long len = g.vec_len();
-  const int m = o.restart;
-  int rc;
-  // workspace: basis (m+1) vectors, w, r
-  if ((rc = ensure(c, c->basis, (size_t)(m + 1) * len * sizeof(c128))) != TM_OK) return rc;
-  if ((rc = ensure(c, c->work_c, (size_t)2 * len * sizeof(c128))) != TM_OK) return rc;
-  const int nblk = krylov_blocks(len);
-  if ((rc = ensure(c, c->dotpart, (size_t)nblk * (m + 2) * sizeof(c128))) != TM_OK) return rc;
-  if ((rc = ensure(c, c->dots, (size_t)(2 * (m + 2) + 4) * sizeof(c128))) != TM_OK) return rc;
-  if ((rc = ensure(c, c->scal, (size_t)(nblk + 8) * sizeof(double))) != TM_OK) return rc;
-  if ((rc = ensure_pinned(c, (size_t)(2 * m + 6) * sizeof(c128))) != TM_OK) return rc;
-  Gm G;
-  G.c = c;
-  G.op = op;
-  G.len = len;
-  G.nblk = nblk;
-  G.V = (c128*)c->basis.p;
-  G.w = (c128*)c->work_c.p;
-  G.r = G.w + len;
-  G.dp = (c128*)c->dotpart.p;
-  G.dots = (c128*)c->dots.p;
-  G.dots2 = G.dots + (m + 2);
-  G.np = (double*)c->scal.p;
-  G.nout = G.np + nblk;
-  hipStream_t st = c->stream;
-
-  info = tm_solve_info{};
-  const double bnorm = dev_norm(G, b);
-  if (!std::isfinite(bnorm)) return set_err(c, TM_ERR_NAN, "right-hand side is not finite");
-  if (bnorm == 0.0) {
-    TM_HIP(c, hipMemsetAsync(x, 0, len * sizeof(c128), st));
-    info.status = TM_OK;
-    return TM_OK;
-  }
-  if (use_x0) {
-    if ((rc = apply_op(c, op, TM_PREC_FP64, 1, x, G.r)) != TM_OK) return rc;
-    info.matvecs_fp64++;
-    k_sub(st, G.r, b, G.r, len);
-  } else {
-    TM_HIP(c, hipMemsetAsync(x, 0, len * sizeof(c128), st));
-    k_copy(st, G.r, b, len);
-  }
-  if ((rc = ensure(c, c->gm_dev, gm_state_bytes(m))) != TM_OK) return rc;
-  void* gs = c->gm_dev.p;
-  const int* stop = &static_cast<const GmFlags*>(gs)->stop;
-  // the matvecs of apply_op skip their work once the cycle has stopped;
-  // cleared on every way out of this function
-  struct StopGuard {
-    tm_ctx* c;
-    ~StopGuard() { c->mv_stop = nullptr; }
-  } guard{c};
-  const int which_prof = (o.precision == TM_PREC_MIXED) ? 1 : 0;
-  int it = 0;
-  double relres = 0.0;
-  const int prec = o.precision;
-  double beta = dev_norm(G, G.r);
-  for (;;) {
-    relres = beta / bnorm;
-    if (!std::isfinite(beta)) return set_err(c, TM_ERR_NAN, "residual became non-finite");
-    if (relres <= o.tol || it >= o.max_iter) break;
-    if (c->progress) c->progress(c->progress_user, info.cycles, it, 1, relres);
-    info.cycles++;
-    k_scale(st, G.V, G.r, 1.0 / beta, len);
-    k_gm_cycle_init(st, gs, m, G.nout);  // G.nout holds beta
-    const double target =
-        (prec == TM_PREC_MIXED) ? std::max(o.tol * bnorm, o.inner_tol * beta) : o.tol * bnorm;
-    const int jmax = std::min(m, o.max_iter - it);
-    c->mv_stop = stop;
-    int launched = 0;
-    for (int j = 0; j < jmax; ++j) {
-      ++launched;
-      c128* vj = G.V + (size_t)j * len;
-      if ((rc = apply_op(c, op, prec, 1, vj, G.w)) != TM_OK) return rc;
-      // CGS2: h1 = V^H w, w -= V h1, h2 = V^H w, w -= V h2, H(:,j) = h1 + h2
-      int nseg = k_multidot(st, G.V, len, j + 1, G.w, len, G.dp, nblk, stop);
-      k_reduce_dots(st, G.dp, nseg, j + 1, G.dots, nullptr, stop);
-      k_update(st, G.w, G.V, len, j + 1, G.dots, len, -1.0, stop);
-      nseg = k_multidot(st, G.V, len, j + 1, G.w, len, G.dp, nblk, stop);
-      k_reduce_dots(st, G.dp, nseg, j + 1, G.dots2, nullptr, stop);
-      k_update(st, G.w, G.V, len, j + 1, G.dots2, len, -1.0, stop);
-      k_norm2_partial(st, G.w, len, G.np, nblk, stop);
-      k_reduce_norm(st, G.np, nblk, G.nout, stop);
-      k_gm_givens(st, gs, m, j, G.dots, G.dots2, G.nout, target);
-      k_gm_scale_next(st, G.V + (size_t)(j + 1) * len, G.w, gs, len);
-      // with a progress callback, a long cycle also reports every 50 steps
-      // (one readback of the flags there; a cycle already stopped ends here)
-      if (c->progress && (j + 1) % 50 == 0 && j + 1 < jmax) {
-        TM_HIP(c, hipMemcpyAsync(c->host_pinned, gs, sizeof(GmFlags), hipMemcpyDeviceToHost, st));
-        TM_HIP(c, hipStreamSynchronize(st));
-        GmFlags fl;
-        std::memcpy(&fl, c->host_pinned, sizeof(GmFlags));
-        if (fl.stop) break;
-        c->progress(c->progress_user, info.cycles - 1, it + fl.jend, 1, fl.est / bnorm);
-      }
-    }
-    c->mv_stop = nullptr;
-    const size_t prof_mark = c->prof ? c->prof_pending[which_prof].size() : 0;
-    // y = H^-1 g on the device, x += V y (y is zero past the steps taken)
-    k_gm_backsub(st, gs, m);
-    k_gm_update_x(st, x, G.V, len, gs, m);
-    // true residual in FP64
-    if ((rc = apply_op(c, op, TM_PREC_FP64, 1, x, G.r)) != TM_OK) return rc;
-    info.matvecs_fp64++;
-    k_sub(st, G.r, b, G.r, len);
-    // the cycle's one readback: residual norm and the flags
-    k_norm2_partial(st, G.r, len, G.np, nblk);
-    k_reduce_norm(st, G.np, nblk, G.nout);
-    TM_HIP(c, hipMemcpyAsync(c->host_pinned, G.nout, sizeof(double), hipMemcpyDeviceToHost, st));
-    TM_HIP(c, hipMemcpyAsync((char*)c->host_pinned + 16, gs, sizeof(GmFlags), hipMemcpyDeviceToHost, st));
-    TM_HIP(c, hipStreamSynchronize(st));
-    GmFlags fl;
-    std::memcpy(&beta, c->host_pinned, sizeof(double));
-    std::memcpy(&fl, (const char*)c->host_pinned + 16, sizeof(GmFlags));
-    if (fl.nonfinite) return set_err(c, TM_ERR_NAN, "Arnoldi produced a non-finite value");
-    it += fl.jend;
-    if (prec == TM_PREC_MIXED) info.matvecs_lowp += fl.jend;
-    else info.matvecs_fp64 += fl.jend;
-    // matvecs launched after the convergence test fired did no work: their
-    // profile records (the last ones of the Arnoldi loop) are dropped
-    if (c->prof && fl.jend < launched) {
-      auto& pend = c->prof_pending[which_prof];
-      const size_t drop = (size_t)(launched - fl.jend);
-      const size_t mark = prof_mark;
-      if (mark >= drop && mark <= pend.size()) {
-        for (size_t k = mark - drop; k < mark; ++k) {
-          hipEventDestroy(pend[k].first);
-          hipEventDestroy(pend[k].second);
-        }
-        pend.erase(pend.begin() + (mark - drop), pend.begin() + mark);
-      }
-    }
-  }
-  info.iters = it;
-  info.rel_residual = relres;
-  info.status = (relres <= o.tol) ? TM_OK : TM_NOT_CONVERGED;
-  TM_HIP(c, hipGetLastError());
   return TM_OK;
 }
 
@@ -319,14 +139,14 @@ void tm_destroy(tm_ctx* c) {
   hipSetDevice(c->device);
   hipStreamSynchronize(c->stream);
   for (tmh::DevBuf* b : {&c->dtab[0], &c->dtab[1], &c->dtab[2], &c->dtab[3], &c->gpos, &c->jinc_buf,
-                        &c->gm_dev, &c->tmb, &c->tmflag, &c->spec_sym, &c->spec_w, &c->spec_const})
+                        &c->kry_dev, &c->tmb, &c->tmflag, &c->spec_sym, &c->spec_w, &c->spec_const})
     tmh::release(*b);
   for (tmh::DevBuf* b : {&c->tab64, &c->tab32, &c->tabT64, &c->tabT32, &c->t64, &c->t32, &c->dt64,
                         &c->tden, &c->ttmp, &c->partial, &c->xlow, &c->work_a, &c->work_b, &c->work_c, &c->basis,
-                        &c->dots, &c->dotpart, &c->scal, &c->plan_items[0], &c->plan_items[1],
+                        &c->plan_items[0], &c->plan_items[1],
                         &c->plan_ibeg[0], &c->plan_ibeg[1]})
     tmh::release(*b);
-  if (c->host_pinned) hipHostFree(c->host_pinned);
+  if (c->kry_host) hipHostFree(c->kry_host);
   if (c->side) {
     hipStreamSynchronize(c->side);
     hipStreamDestroy(c->side);
@@ -405,9 +225,7 @@ int tm_set_geometry(tm_ctx* c, int n, const double* pos, double k, int lmax) {
   tmh::host_slot_maps(lmax, g, c->maps);
   tmh::host_mblock_maps(lmax, c->mbmaps);
   c->have_geom = c->have_t = c->have_dt = c->have_tabT = c->have_dtab = c->t_dense = false;
-  c->t_mblock = c->have_spec = false;
-  c->spec_fit[0] = tmh::spec_fits<double>(g, g.nx, g.ny, c->spec.X, c->spec.Y);
-  c->spec_fit[1] = tmh::spec_fits<float>(g, g.nx, g.ny, c->spec.X, c->spec.Y);
+  c->t_mblock = c->have_spec = c->spec_known = false;
   c->plan_R[0] = c->plan_R[1] = -1;
   int rc;
   if (lattice) {
@@ -706,14 +524,48 @@ static int solve_common(tm_ctx* c, Op op, int R, const tm_c128* rhs, tm_c128* ou
     }
   }
   if (o->use_x0) tmh::pack_slots(c->stream, g, c->maps, R, out, xsl);
+  // right-hand sides share the launches of every step, as many as their bases
+  // leave three quarters of the free memory for; one at a time under a progress
+  // callback, which reports each by itself
+  int group = 1;
+  if (R > 1 && !c->progress) {
+    size_t free_b = 0, total_b = 0;
+    TM_HIP(c, hipMemGetInfo(&free_b, &total_b));
+    const size_t one = (size_t)(o->restart + 1) * len * sizeof(c128);
+    group = (int)std::max<size_t>(1, std::min<size_t>(R, std::max(free_b / 4, c->basis.bytes) / one));
+  }
   bool all_ok = true;
-  for (int r = 0; r < R; ++r) {
-    rc = tmh::gmres(c, op, bsl + (size_t)r * len, xsl + (size_t)r * len, *o, o->use_x0 != 0, info[r]);
+  for (int r = 0; r < R; r += group) {
+    const int n = std::min(group, R - r);
+    if ((rc = tmh::ensure(c, c->work_c, (size_t)2 * n * len * sizeof(c128))) != TM_OK) return rc;
+    tmh::KryProblem p;
+    p.nsys = n;
+    p.len = len;
+    p.total = n * len;
+    p.b = bsl + (size_t)r * len;
+    p.x = xsl + (size_t)r * len;
+    p.w = (c128*)c->work_c.p;
+    p.r = p.w + p.total;
+    p.opts = *o;
+    p.x0 = o->use_x0 != 0;
+    p.apply = [&](int prec, const c128* x, c128* y, const int* active) {
+      c->mv_active = active;
+      const int e = tmh::apply_op(c, op, prec, n, x, y);
+      c->mv_active = nullptr;
+      return e;
+    };
+    if (c->progress) {
+      p.progress = [&](int cyc, int it, int live, double res) { c->progress(c->progress_user, cyc, it, live, res); };
+      p.progress_inside = [&](int cyc, int it, double res) { c->progress(c->progress_user, cyc, it, 1, res); };
+    }
+    rc = tmh::kry_solve(c, p, info + r);
+    c->mv_stop = nullptr;
     if (rc != TM_OK) return rc;
-    if (info[r].status != TM_OK) all_ok = false;
+    for (int q = r; q < r + n; ++q) all_ok = all_ok && info[q].status == TM_OK;
   }
   tmh::unpack_slots(c->stream, g, c->maps, R, xsl, out);
   TM_HIP(c, hipStreamSynchronize(c->stream));
+  if (group > 1) tmh::kry_trim(c);
   return all_ok ? TM_OK : TM_NOT_CONVERGED;
 }
 

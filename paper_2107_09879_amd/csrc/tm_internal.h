@@ -151,15 +151,16 @@ struct tm_ctx {
   tmh::DevBuf tmb, tmflag;  // dense T as m-blocks [N][per_site]; structure flag
   tmh::MbMaps mbmaps{};
   // workspaces
-  tmh::DevBuf partial, xlow, work_a, work_b, work_c, basis, dots, dotpart, scal;
-  // single-system GMRES state on the device (flags, Hessenberg, rotations)
-  tmh::DevBuf gm_dev;
-  // while set, the block-matvec kernels of apply_op return at once when the
-  // pointed-to flag is nonzero (the GMRES cycle has stopped)
-  const int* mv_stop = nullptr;
-  // host staging (pinned)
-  void* host_pinned = nullptr;
-  size_t host_pinned_bytes = 0;
+  tmh::DevBuf partial, xlow, work_a, work_b, work_c, basis;
+  // GMRES: Krylov state on the device (partial sums, Hessenberg, rotations)
+  // and what its kernels and the host exchange (pinned)
+  tmh::DevBuf kry_dev;
+  void* kry_host = nullptr;
+  size_t kry_host_bytes = 0;
+  // while set, the matvec kernels of apply_op return at once when the
+  // pointed-to flag is nonzero (the GMRES cycle has stopped), and leave out
+  // right-hand sides whose flag is zero
+  const int *mv_stop = nullptr, *mv_active = nullptr;
   // profiling
   bool prof = false;
   hipEvent_t ev0 = nullptr, ev1 = nullptr;
@@ -181,7 +182,7 @@ struct tm_ctx {
   // or tm_autotune asked for the block kernels instead
   tmh::DevBuf spec_sym, spec_w, spec_const;
   tmh::SpecPlan spec;
-  bool have_spec = false, spec_fit[2] = {false, false}, mv_block[2] = {false, false};
+  bool have_spec = false, spec_known = false, spec_fit[2] = {false, false}, mv_block[2] = {false, false};
   int spec_const_lmax = 0;
   int plan_nreg[2] = {0, 0};  // LDS plan: items of regular tiles (wide-tile items follow)
   int last_batch_graphed = 0;
@@ -210,7 +211,6 @@ int set_err(tm_ctx* c, int code, const std::string& msg);
 
 int ensure(tm_ctx* c, DevBuf& b, size_t bytes);
 int validate_incidence(tm_ctx* c, int R, const double* khat, const tm_c128* pol);
-int ensure_pinned(tm_ctx* c, size_t bytes);
 void release(DevBuf& b);
 
 // ---- launchers implemented in the .hip files ------------------------------
@@ -232,6 +232,7 @@ void table_constants(const Geometry& g, int Q, std::vector<double>& coef, std::v
 // transformed block matvec (tm_spectral.hip)
 template <typename T>
 bool spec_fits(const Geometry& g, int nx, int ny, SpecDim& X, SpecDim& Y);
+bool spec_use(tm_ctx* c, int which);  // whether the geometry fits it at this precision slot
 template <typename T>
 int spec_apply(tm_ctx* c, Op op, int R, const c128* x, c128* y);
 
@@ -306,45 +307,11 @@ int lds_apply_fixed(tm_ctx* c, int R, const void* table, const void* xin, const 
 // looked up once per device by tm_create (tm_noalloc.hip)
 int noalloc_init(tm_ctx* c);
 
-// Krylov kernels (tm_krylov.hip).  `stop` (nullable, device): the kernel
-// returns at once when *stop is nonzero.  k_multidot returns the number of
-// partial-sum rows it wrote (at most nblk), to be passed to k_reduce_dots.
-int k_multidot(hipStream_t st, const c128* V, long long stride, int nvec, const c128* w,
-                long long len, c128* partial, int nblk, const int* stop = nullptr);
-void k_reduce_dots(hipStream_t st, const c128* partial, int nblk, int nvec, c128* out,
-                   const c128* add, const int* stop = nullptr);
-void k_update(hipStream_t st, c128* w, const c128* V, long long stride, int nvec,
-              const c128* h, long long len, double sign, const int* stop = nullptr);
-void k_norm2_partial(hipStream_t st, const c128* w, long long len, double* partial, int nblk,
-                     const int* stop = nullptr);
-void k_reduce_norm(hipStream_t st, const double* partial, int nblk, double* out,
-                   const int* stop = nullptr);
-// Device-side Givens of one restarted GMRES cycle.  Layout of the state
-// buffer: GmFlags, then H [(m+1) x m], cs [m], sn [m], g [m+1], y [m]
-// (complex).  One Arnoldi step: column j of H from the two CGS passes' dots
-// and the new vector's norm, the previous rotations applied, a new rotation,
-// the residual estimate |g[j+1]|; `stop` is raised when the estimate reaches
-// `target`, on a zero (lucky breakdown) or non-finite norm.
-struct GmFlags {
-  int stop, jend, nonfinite, pad;
-  double inv_hn, est;
-};
-size_t gm_state_bytes(int m);
-void k_gm_cycle_init(hipStream_t st, void* state, int m, const double* beta);
-void k_gm_givens(hipStream_t st, void* state, int m, int j, const c128* h1, const c128* h2,
-                 const double* hn, double target);
-void k_gm_scale_next(hipStream_t st, c128* v, const c128* w, const void* state, long long len);
-void k_gm_backsub(hipStream_t st, void* state, int m);
-void k_gm_update_x(hipStream_t st, c128* x, const c128* V, long long len, const void* state, int m);
-const c128* gm_y(const void* state, int m);
-void k_scale(hipStream_t st, c128* y, const c128* x, double a, long long len);
-void k_axpy_dev(hipStream_t st, c128* y, const c128* x, const c128* V, long long stride,
-                int nvec, const c128* coef, long long len);
+// vector kernels (tm_krylov.hip)
 void k_sub(hipStream_t st, c128* out, const c128* a, const c128* b, long long len);
 void k_add(hipStream_t st, c128* out, const c128* a, const c128* b, long long len);
 void k_copy(hipStream_t st, c128* out, const c128* in, long long len);
 void k_mul_t(hipStream_t st, c128* out, const c128* t, const c128* x, long long len_per_rhs,
              int R);
-int krylov_blocks(long long len);
 
 }  // namespace tmh

@@ -446,7 +446,7 @@ static int apply_impl(tm_ctx* c, Op op, int R, const c128* x, c128* y) {
     if ((rc = build_transposed_tables(c)) != TM_OK) return rc;
   }
   const int which = std::is_same<T, double>::value ? 0 : 1;
-  if (c->spec_fit[which] && !c->mv_block[which]) {
+  if (!c->mv_block[which] && spec_use(c, which)) {
     hipEvent_t e0 = nullptr, e1 = nullptr;
     if (c->prof) {
       TM_HIP(c, hipEventCreate(&e0));
@@ -584,7 +584,7 @@ static int autotune_impl(tm_ctx* c, int R, double* best_ms) {
   c->mv_items[which] = bi;
   // the transformed product stays unless the block kernels beat it
   c->mv_block[which] = true;
-  if (c->spec_fit[which]) {
+  if (spec_use(c, which)) {
     const size_t vb = (size_t)total * sizeof(c128);
     if ((rc = ensure(c, c->work_a, vb)) != TM_OK || (rc = ensure(c, c->work_b, vb)) != TM_OK) return rc;
     TM_HIP(c, hipMemsetAsync(c->work_a.p, 0, vb, c->stream));

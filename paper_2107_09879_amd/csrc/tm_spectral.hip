@@ -677,6 +677,16 @@ bool spec_fits(const Geometry& g, int nx, int ny, SpecDim& X, SpecDim& Y) {
 template bool spec_fits<float>(const Geometry&, int, int, SpecDim&, SpecDim&);
 template bool spec_fits<double>(const Geometry&, int, int, SpecDim&, SpecDim&);
 
+bool spec_use(tm_ctx* c, int which) {
+  if (!c->spec_known) {
+    const Geometry& g = c->g;
+    c->spec_fit[0] = spec_fits<double>(g, g.nx, g.ny, c->spec.X, c->spec.Y);
+    c->spec_fit[1] = spec_fits<float>(g, g.nx, g.ny, c->spec.X, c->spec.Y);
+    c->spec_known = true;
+  }
+  return c->spec_fit[which];
+}
+
 static int allow_lds(tm_ctx* c, const void* f, size_t bytes) {
   if (bytes <= 64 * 1024) return TM_OK;
   TM_HIP(c, hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes));
@@ -868,6 +878,7 @@ int spec_apply(tm_ctx* c, Op op, int R, const c128* x, c128* y) {
   a.y = y;
   a.W = (cplx<T>*)c->spec_w.p;
   a.stop = c->mv_stop;
+  a.active = c->mv_active;
   a.R = R;
   return spec_launch<T>(c, a, op, g.ny, c->spec.X.P, c->spec.X.P, c->spec.Y);
 }
