@@ -251,7 +251,6 @@ int tm_set_geometry(tm_ctx* c, int n, const double* pos, double k, int lmax) {
       if (sorted[i] == sorted[i - 1]) return tmh::set_err(c, TM_ERR_OVERLAP, "two scatterers share a centre");
     if ((rc = tmh::ensure(c, c->xy, (size_t)2 * n * sizeof(double))) != TM_OK) return rc;
     TM_HIP(c, hipMemcpy(c->xy.p, c->host_xy.data(), (size_t)2 * n * sizeof(double), hipMemcpyHostToDevice));
-    if ((rc = tmh::build_offlattice_constants(c)) != TM_OK) return rc;
   }
   const size_t vb = (size_t)g.vec_len();
   if ((rc = tmh::ensure(c, c->t64, vb * sizeof(c128))) != TM_OK) return rc;

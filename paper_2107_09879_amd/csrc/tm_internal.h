@@ -143,7 +143,6 @@ struct tm_ctx {
   tmh::DevBuf gpos;  // position-gradient workspace (slot-layout vectors)
   tmh::DevBuf jinc_buf;  // jinc sources, polar nodes and subregion tables
   tmh::DevBuf xy;        // scatterer centres [N][2] (off-lattice geometries)
-  tmh::DevBuf olc;       // off-lattice translation constants (coef, dm)
   std::vector<double> host_xy;  // the same on the host (off-lattice)
   // T and dT/dr in slot layout [2][N][S]
   tmh::DevBuf t64, t32, dt64;
@@ -218,7 +217,6 @@ void release(DevBuf& b);
 int build_tables(tm_ctx* c);            // forward tables, FP64 + c64
 int build_transposed_tables(tm_ctx* c); // A^T tables
 int build_derivative_tables(tm_ctx* c); // position-gradient tables (FP64)
-int build_offlattice_constants(tm_ctx* c);  // per-entry constants of the on-the-fly matvec
 // on-the-fly block matvec for off-lattice geometries (tm_offlattice.hip)
 enum class Op;
 template <typename T>
