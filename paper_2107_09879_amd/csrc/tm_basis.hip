@@ -457,15 +457,26 @@ struct NfPhase<double> {
 // Staged layout per (sphere, RHS), in reals: for l = 1..LMAX at offset
 // 4 (l^2 - 1): m = 0 as [M.re, M.im, N.re, N.im], then for |m| = 1..l
 // [M: A+, A-, B+, B-][N: A+, A-, B+, B-].
+//
+// blockIdx.y takes `per` spheres; with more than one such chunk the sums go to
+// `part` [chunk][R][P][3] and nf_combine adds them in FP64.  One point per thread
+// leaves most of the chip idle below about 5e5 points: 4e4 points over 1e4
+// spheres (lmax 3, two right-hand sides, FP32 basis) were 157 workgroups, 16.3 ms;
+// in chunks 5.7 ms
+// (62 % of the FP32 VALU issue peak).  25 points over 1600 spheres: 1.47 ms -> 47 us.
+template <int LMAX>
+struct NfChunk {
+  // spheres staged per LDS pass: at most 48 KB of coefficients
+  static constexpr int N = LMAX <= 3 ? 32 : 8;
+};
 template <typename T, int LMAX, int R>
 __global__ __launch_bounds__(256) void near_field_v2(
-    const tm_c128* __restrict__ s, int N, SitePos sp, double k,
-    const double* __restrict__ pts, int P, tm_c128* __restrict__ E) {
+    const tm_c128* __restrict__ s, int N, int per, SitePos sp, double k,
+    const double* __restrict__ pts, int P, tm_c128* __restrict__ E, cx<T>* __restrict__ part) {
   constexpr int L = 2 * LMAX * (LMAX + 2), H = LMAX * (LMAX + 2);
   constexpr int NF = 2 * L;                     // staged reals per (sphere, RHS)
   constexpr int NU = LMAX * (LMAX + 3) / 2;     // (l, |m|) units per (sphere, RHS)
-  // spheres staged per LDS chunk: at most 48 KB of coefficients
-  constexpr int CHN = (LMAX <= 3) ? 32 : 8;
+  constexpr int CHN = NfChunk<LMAX>::N;
   __shared__ __align__(16) T sh[CHN][R][NF];
   __shared__ __align__(16) double shp[CHN][2];  // centres of the staged spheres
   const int ip = blockIdx.x * blockDim.x + threadIdx.x;
@@ -474,8 +485,9 @@ __global__ __launch_bounds__(256) void near_field_v2(
                pz = live ? pts[3 * ip + 2] : 1.0;
   const T invk = (T)(1.0 / k);
   cx<T> acc[R][3];
-  for (int i0 = 0; i0 < N; i0 += CHN) {
-    const int nch = min(CHN, N - i0);
+  const int i1 = min(N, (int)(blockIdx.y + 1) * per);
+  for (int i0 = blockIdx.y * per; i0 < i1; i0 += CHN) {
+    const int nch = min(CHN, i1 - i0);
     __syncthreads();
     if (threadIdx.x < nch) sp.at(i0 + threadIdx.x, shp[threadIdx.x][0], shp[threadIdx.x][1]);
     for (int q = threadIdx.x; q < nch * R * NU; q += blockDim.x) {
@@ -612,73 +624,127 @@ __global__ __launch_bounds__(256) void near_field_v2(
     }
   }
   if (!live) return;
+  cx<T>* out = part + (size_t)blockIdx.y * R * P * 3;
 #pragma unroll
   for (int r = 0; r < R; ++r)
 #pragma unroll
-    for (int q = 0; q < 3; ++q)
-      E[((size_t)r * P + ip) * 3 + q] = tm_c128{(double)acc[r][q].re, (double)acc[r][q].im};
+    for (int q = 0; q < 3; ++q) {
+      const size_t o = ((size_t)r * P + ip) * 3 + q;
+      if (gridDim.y > 1) out[o] = acc[r][q];
+      else E[o] = tm_c128{(double)acc[r][q].re, (double)acc[r][q].im};
+    }
+}
+
+// sum of `n` partial results of `total` values each, in order, in FP64
+template <typename T>
+__global__ void nf_combine(const cx<T>* __restrict__ part, int n, long long total, tm_c128* __restrict__ out) {
+  const long long e = (long long)blockIdx.x * blockDim.x + threadIdx.x;
+  if (e >= total) return;
+  double re = 0.0, im = 0.0;
+#pragma unroll 4
+  for (int q = 0; q < n; ++q) {
+    const cx<T> v = part[(size_t)q * total + e];
+    re += (double)v.re;
+    im += (double)v.im;
+  }
+  out[e] = tm_c128{re, im};
+}
+
+static inline unsigned nblk(long long n, int t = 256) { return (unsigned)((n + t - 1) / t); }
+
+// Work split of `rows` threads over `terms` terms each: threads per workgroup
+// (no wider than the rows need) and chunks of at least `least` terms so that
+// about `want` waves run (eight per SIMD for the near field; two for its
+// transpose, whose registers allow no more and whose partial sums are long).
+struct RowSplit {
+  int threads, chunks, per;
+  unsigned blocks;
+};
+static RowSplit row_split(long long rows, int terms, int least, long long want) {
+  RowSplit w;
+  w.threads = rows <= 64 ? 64 : rows <= 128 ? 128 : 256;
+  w.blocks = nblk(rows, w.threads);
+  const long long waves = (long long)w.blocks * (w.threads / 64);
+  const int most = std::max(1, (terms + least - 1) / least);
+  w.chunks = (int)std::max(1ll, std::min<long long>(most, want / waves));
+  w.per = least * std::max(1, (terms + w.chunks * least - 1) / (w.chunks * least));
+  w.chunks = std::max(1, (terms + w.per - 1) / w.per);
+  return w;
 }
 
 template <typename T, int LMAX>
-static void nf_dispatch_r(int R, dim3 g, hipStream_t st, const tm_c128* s, int N, SitePos sp, double k,
-                          const double* pts, int P, tm_c128* E) {
+static int nf_launch(tm_ctx* c, int R, const tm_c128* s, const double* pts, int P, tm_c128* E) {
+  const Geometry& g = c->g;
+  const RowSplit w = row_split(P, g.n, NfChunk<LMAX>::N, 8192);
+  const long long total = (long long)R * P * 3;
+  int rc;
+  if (w.chunks > 1 && (rc = ensure(c, c->partial, (size_t)w.chunks * total * sizeof(cx<T>))) != TM_OK) return rc;
+  cx<T>* part = (cx<T>*)c->partial.p;
+  const dim3 grid(w.blocks, w.chunks), block(w.threads);
+  const SitePos sp = site_pos(c);
+#define NF_R(RR)                                                                                              \
+  hipLaunchKernelGGL((near_field_v2<T, LMAX, RR>), grid, block, 0, c->stream, s, g.n, w.per, sp, g.k, pts, P, E, part)
   switch (R) {
-    case 1: hipLaunchKernelGGL((near_field_v2<T, LMAX, 1>), g, dim3(256), 0, st, s, N, sp, k, pts, P, E); break;
-    case 2: hipLaunchKernelGGL((near_field_v2<T, LMAX, 2>), g, dim3(256), 0, st, s, N, sp, k, pts, P, E); break;
-    case 3: hipLaunchKernelGGL((near_field_v2<T, LMAX, 3>), g, dim3(256), 0, st, s, N, sp, k, pts, P, E); break;
-    default: hipLaunchKernelGGL((near_field_v2<T, LMAX, 4>), g, dim3(256), 0, st, s, N, sp, k, pts, P, E); break;
+    case 1: NF_R(1); break;
+    case 2: NF_R(2); break;
+    case 3: NF_R(3); break;
+    default: NF_R(4); break;
   }
+#undef NF_R
+  if (w.chunks > 1)
+    hipLaunchKernelGGL(nf_combine<T>, dim3(nblk(total)), dim3(256), 0, c->stream, part, w.chunks, total, E);
+  return TM_OK;
 }
-
 template <typename T>
-static void nf_dispatch(int lmax, int R, dim3 g, hipStream_t st, const tm_c128* s, int N, SitePos sp,
-                        double k, const double* pts, int P, tm_c128* E) {
-  switch (lmax) {
-    case 1: nf_dispatch_r<T, 1>(R, g, st, s, N, sp, k, pts, P, E); break;
-    case 2: nf_dispatch_r<T, 2>(R, g, st, s, N, sp, k, pts, P, E); break;
-    case 3: nf_dispatch_r<T, 3>(R, g, st, s, N, sp, k, pts, P, E); break;
-    case 4: nf_dispatch_r<T, 4>(R, g, st, s, N, sp, k, pts, P, E); break;
-    case 5: nf_dispatch_r<T, 5>(R, g, st, s, N, sp, k, pts, P, E); break;
-    default: nf_dispatch_r<T, 6>(R, g, st, s, N, sp, k, pts, P, E); break;
+static int nf_dispatch(tm_ctx* c, int R, const tm_c128* s, const double* pts, int P, tm_c128* E) {
+  switch (c->g.lmax) {
+    case 1: return nf_launch<T, 1>(c, R, s, pts, P, E);
+    case 2: return nf_launch<T, 2>(c, R, s, pts, P, E);
+    case 3: return nf_launch<T, 3>(c, R, s, pts, P, E);
+    case 4: return nf_launch<T, 4>(c, R, s, pts, P, E);
+    case 5: return nf_launch<T, 5>(c, R, s, pts, P, E);
+    default: return nf_launch<T, 6>(c, R, s, pts, P, E);
   }
 }
 
 // F(d) = (1/k) sum_i e^{-ik d.x_i} sum_n s_{i,n} F_n(d), with
 // F_n = (-i)^{l+1} [i pi th - tau ph] e^{im phi} (p = 0), (-i)^l [tau th + i pi ph] e^{im phi}
 // (p = 1), times 1/sqrt(2l(l+1)): the h_l(x) ~ (-i)^{l+1} e^{ix}/x limit.
-// One workgroup per (rhs, direction): threads stride over scatterers to form
-// c_n = sum_i e^{-ik d.x_i} s_{i,n}, then a fixed-order wave + LDS reduction.
+// Phase sums: one workgroup per (rhs, direction) and chunk of `per` scatterers
+// (blockIdx.y; four directions over 22500 scatterers were four workgroups, 760 us,
+// now 30 us), sums
+// c_n = sum_i e^{-ik d.x_i} s_{i,n} per thread, then a fixed-order wave + LDS
+// reduction into part [chunk][rhs, direction][L].
 constexpr int FF_THREADS = 256;
 template <int LMAXT>
-__global__ __launch_bounds__(FF_THREADS) void far_field_kernel(
-    const tm_c128* __restrict__ s, int R, int N, int L, int lmax, SitePos sp, double k,
-    const double* __restrict__ dirs, int D, tm_c128* __restrict__ F) {
-  constexpr int LM = 2 * LMAXT * (LMAXT + 2);
-  __shared__ double red[FF_THREADS / 64][2 * LM];
+__global__ __launch_bounds__(FF_THREADS) void far_sums_kernel(
+    const tm_c128* __restrict__ s, int N, int per, SitePos sp, double k,
+    const double* __restrict__ dirs, int D, c128* __restrict__ part) {
+  constexpr int L = 2 * LMAXT * (LMAXT + 2);
+  __shared__ double red[FF_THREADS / 64][2 * L];
   const int e = blockIdx.x;
   const int r = e / D, id = e % D;
-  const double ux = dirs[3 * id], uy = dirs[3 * id + 1], uz = dirs[3 * id + 2];
-  double cr[LM], ci[LM];
+  const double ux = dirs[3 * id], uy = dirs[3 * id + 1];
+  double cr[L], ci[L];
 #pragma unroll
-  for (int n = 0; n < LM; ++n) cr[n] = ci[n] = 0.0;
-  for (int i = threadIdx.x; i < N; i += FF_THREADS) {
+  for (int n = 0; n < L; ++n) cr[n] = ci[n] = 0.0;
+  const int i1 = min(N, (int)(blockIdx.y + 1) * per);
+  for (int i = blockIdx.y * per + threadIdx.x; i < i1; i += FF_THREADS) {
     double xi, yi;
     sp.at(i, xi, yi);
     double sph, cph;
     sincos(-k * (ux * xi + uy * yi), &sph, &cph);
     const tm_c128* si = s + ((size_t)r * N + i) * L;
 #pragma unroll
-    for (int n = 0; n < LM; ++n) {
-      if (n < L) {
-        const tm_c128 v = si[n];
-        cr[n] += cph * v.re - sph * v.im;
-        ci[n] += cph * v.im + sph * v.re;
-      }
+    for (int n = 0; n < L; ++n) {
+      const tm_c128 v = si[n];
+      cr[n] += cph * v.re - sph * v.im;
+      ci[n] += cph * v.im + sph * v.re;
     }
   }
   const int w = threadIdx.x >> 6, ln = threadIdx.x & 63;
 #pragma unroll
-  for (int n = 0; n < LM; ++n) {
+  for (int n = 0; n < L; ++n) {
     double a = cr[n], b = ci[n];
     for (int o = 32; o > 0; o >>= 1) {
       a += __shfl_xor(a, o, 64);
@@ -690,7 +756,21 @@ __global__ __launch_bounds__(FF_THREADS) void far_field_kernel(
     }
   }
   __syncthreads();
-  if (threadIdx.x != 0) return;
+  double* out = (double*)(part + ((size_t)blockIdx.y * gridDim.x + e) * L);
+  for (int q = threadIdx.x; q < 2 * L; q += FF_THREADS) {
+    double v = red[0][q];
+    for (int x = 1; x < FF_THREADS / 64; ++x) v += red[x][q];
+    out[q] = v;
+  }
+}
+// The far field of every (rhs, direction): one workgroup of 128, a coefficient
+// per thread.
+__global__ __launch_bounds__(128) void far_field_kernel(const c128* __restrict__ part, int chunks, int L, int lmax,
+                                                        double k, const double* __restrict__ dirs, int D,
+                                                        tm_c128* __restrict__ F) {
+  __shared__ cplx<double> ft[LM_MAX], fp[LM_MAX];
+  const int e = blockIdx.x, id = e % D, n = threadIdx.x;
+  const double ux = dirs[3 * id], uy = dirs[3 * id + 1], uz = dirs[3 * id + 2];
   const double rho = sqrt(ux * ux + uy * uy);
   const double ct = uz, st = rho;
   double cf = 1.0, sf = 0.0;
@@ -698,12 +778,12 @@ __global__ __launch_bounds__(FF_THREADS) void far_field_kernel(
     cf = ux / rho;
     sf = uy / rho;
   }
-  cx<double> Ft, Fp;
-  for (int n = 0; n < L; ++n) {
+  if (n < L) {
     double a = 0.0, b = 0.0;
-    for (int q = 0; q < FF_THREADS / 64; ++q) {
-      a += red[q][2 * n];
-      b += red[q][2 * n + 1];
+    for (int q = 0; q < chunks; ++q) {
+      const c128 v = part[((size_t)q * gridDim.x + e) * L + n];
+      a += v.re;
+      b += v.im;
     }
     int p, l, m;
     plm_of_n(n, lmax, p, l, m);
@@ -717,13 +797,22 @@ __global__ __launch_bounds__(FF_THREADS) void far_field_kernel(
     const cx<double> c = nrm * (cx<double>(a, b) * em);
     if (p == 0) {
       const cx<double> f = ipow<double>(-(l + 1)) * c;  // (-i)^{l+1} = i^{-(l+1)}
-      Ft = Ft + mul_i(pi * f);
-      Fp = Fp - tau * f;
+      const cx<double> u = mul_i(pi * f), q = (-tau) * f;
+      ft[n] = cplx<double>{u.re, u.im};
+      fp[n] = cplx<double>{q.re, q.im};
     } else {
       const cx<double> f = ipow<double>(-l) * c;
-      Ft = Ft + tau * f;
-      Fp = Fp + mul_i(pi * f);
+      const cx<double> u = tau * f, q = mul_i(pi * f);
+      ft[n] = cplx<double>{u.re, u.im};
+      fp[n] = cplx<double>{q.re, q.im};
     }
+  }
+  __syncthreads();
+  if (n) return;
+  cx<double> Ft, Fp;
+  for (int q = 0; q < L; ++q) {
+    Ft = Ft + cx<double>(ft[q].re, ft[q].im);
+    Fp = Fp + cx<double>(fp[q].re, fp[q].im);
   }
   const double ik = 1.0 / k;
   const cx<double> Fx = ik * ((ct * cf) * Ft - sf * Fp);
@@ -798,47 +887,132 @@ __global__ void detector_kernel(double xdx, double xdy, double xdz, double wxr, 
 }
 
 // Transpose of the near-field map: v[r][i][n] = sum_p sum_c w[r][p][c]
-// Phi_n(k(x_p - x_i))_c.  One thread per (i, n) and right-hand side
-// (blockIdx.y); points and weights stream through LDS in tiles of NFT_TILE.
-constexpr int NFT_TILE = 256;
+// Phi_n(k(x_p - x_i))_c.  One thread per scatterer and right-hand side
+// (blockIdx.z), which evaluates the Hankel, Legendre and phase factors of a
+// point once for all its coefficients (a thread per coefficient, as before,
+// repeated them 30 times at lmax 3); sums in registers, for lmax > 3 one type
+// (M or N) per workgroup.  blockIdx.y takes `per` points; more than one chunk
+// leaves partial sums [chunk][rhs][N][L] for nf_combine.  40x40 scatterers,
+// 1600 points, lmax 3: 5.18 -> 0.11 ms.
+constexpr int NFT_TILE = 64;
+template <int LMAX, int P0, int P1>
 __global__ __launch_bounds__(256) void near_field_t_kernel(
-    const double* __restrict__ pts, const tm_c128* __restrict__ w, int P, int N, int L, int lmax,
-    SitePos sp, double k, tm_c128* __restrict__ v) {
+    const double* __restrict__ pts, const tm_c128* __restrict__ w, int P, int per, int N, int r0,
+    SitePos sp, double k, tm_c128* __restrict__ v, cx<double>* __restrict__ part) {
+  constexpr int H = LMAX * (LMAX + 2), L = 2 * H;
   __shared__ double spt[NFT_TILE][3];
   __shared__ cplx<double> sw[NFT_TILE][3];
-  const int r = blockIdx.y;
-  const long long e = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-  const bool active = e < (long long)N * L;
-  const int n = active ? (int)(e % L) : 0;
-  const long long i = active ? e / L : 0;
-  double xi, yi;
-  sp.at(i, xi, yi);
-  cx<double> acc(0.0, 0.0);
+  const int r = blockIdx.z + r0;
+  const int i = blockIdx.x * blockDim.x + threadIdx.x;
+  const bool active = i < N;
+  double xi = 0.0, yi = 0.0;
+  if (active) sp.at(i, xi, yi);
+  cx<double> acc[P1 - P0][H];
   const tm_c128* wr = w + (size_t)r * P * 3;
-  for (int p0 = 0; p0 < P; p0 += NFT_TILE) {
-    const int np = min(NFT_TILE, P - p0);
+  const int p1 = min(P, (int)(blockIdx.y + 1) * per);
+  for (int p0 = blockIdx.y * per; p0 < p1; p0 += NFT_TILE) {
+    const int np = min(NFT_TILE, p1 - p0);
     __syncthreads();
-    for (int t = threadIdx.x; t < np; t += blockDim.x) {
-      for (int c3 = 0; c3 < 3; ++c3) {
-        spt[t][c3] = pts[(size_t)(p0 + t) * 3 + c3];
-        const tm_c128 q = wr[(size_t)(p0 + t) * 3 + c3];
-        sw[t][c3] = cplx<double>{q.re, q.im};
-      }
+    for (int t = threadIdx.x; t < np * 3; t += blockDim.x) {
+      spt[t / 3][t % 3] = pts[(size_t)p0 * 3 + t];
+      const tm_c128 q = wr[(size_t)p0 * 3 + t];
+      sw[t / 3][t % 3] = cplx<double>{q.re, q.im};
     }
     __syncthreads();
-    if (active) {
-      for (int t = 0; t < np; ++t) {
-        cx<double> Ex, Ey, Ez;
-        outgoing_xyz(n, lmax, spt[t][0] - xi, spt[t][1] - yi, spt[t][2], k, Ex, Ey, Ez);
-        acc = acc + cx<double>(sw[t][0].re, sw[t][0].im) * Ex + cx<double>(sw[t][1].re, sw[t][1].im) * Ey +
-              cx<double>(sw[t][2].re, sw[t][2].im) * Ez;
+    if (!active) continue;
+    for (int t = 0; t < np; ++t) {
+      const double dx = spt[t][0] - xi, dy = spt[t][1] - yi, dz = spt[t][2];
+      const double rho2 = dx * dx + dy * dy;
+      const double rr = sqrt(rho2 + dz * dz), irr = 1.0 / rr;
+      const double x = k * rr, ix = 1.0 / x;
+      double sn, cs;
+      sincos(x, &sn, &cs);
+      const double ct = dz * irr, rho = sqrt(rho2), st = rho * irr;
+      double cf = 1.0, sf = 0.0;
+      if (rho2 > 0.0) {
+        cf = dx / rho;
+        sf = dy / rho;
+      }
+      // the weight along r, theta, phi
+      const cx<double> wx(sw[t][0].re, sw[t][0].im), wy(sw[t][1].re, sw[t][1].im), wz(sw[t][2].re, sw[t][2].im);
+      const cx<double> wr_ = (st * cf) * wx + (st * sf) * wy + ct * wz;
+      const cx<double> wt = (ct * cf) * wx + (ct * sf) * wy - st * wz;
+      const cx<double> wp = cf * wy - sf * wx;
+      cx<double> h[LMAX + 1];
+      h[0] = cx<double>(sn * ix, -cs * ix);
+      h[1] = cx<double>(-(cs * x - sn) * ix * ix, -(sn * x + cs) * ix * ix);
+#pragma unroll
+      for (int q = 1; q < LMAX; ++q) {
+        const double f = (2 * q + 1) * ix;
+        h[q + 1] = cx<double>(f * h[q].re - h[q - 1].re, f * h[q].im - h[q - 1].im);
+      }
+      cx<double> e(1.0, 0.0);
+      // order by order: u_l^m = P_l^m / sin (m >= 1), P_l^0 and u_l^1 for m = 0
+#pragma unroll
+      for (int am = 0; am <= LMAX; ++am) {
+        double um = 1.0;
+#pragma unroll
+        for (int q = 1; q <= 2 * am - 1; q += 2) um *= (double)q;
+#pragma unroll
+        for (int q = 0; q < am - 1; ++q) um *= st;
+        // m = 0: a = P_l^0, b = P_l^1 / sin;  m > 0: a = u_l^m
+        double a0 = am ? 0.0 : 1.0, a1 = am ? um : ct, b0 = 0.0, b1 = 1.0;
+#pragma unroll
+        for (int l = am > 1 ? am : 1; l <= LMAX; ++l) {
+          double v_ = (2.0 * l + 1.0) / (4.0 * l * (l + 1));
+#pragma unroll
+          for (int f = l - am + 1; f <= l + am; ++f) v_ /= (double)f;
+          const double nrm = sqrt(v_);
+          const double Pb = nrm * (am ? st * a1 : a1);
+          const double Ub = am ? nrm * am * a1 : 0.0;
+          const double tau = nrm * (am ? l * ct * a1 - (l + am) * a0 : -st * b1);
+          // e^{+-i m phi}: the terms with U change sign with m
+          const cx<double> ep = e, en(e.re, -e.im);
+          const int np_ = l * (l + 1) - 1 + am, nn = l * (l + 1) - 1 - am;
+          if constexpr (P0 == 0) {
+            const cx<double> B = (-tau) * (h[l] * wp);
+            if (am == 0) {
+              acc[0][np_] = acc[0][np_] + B;
+            } else {
+              const cx<double> A = mul_i(Ub * (h[l] * wt));
+              acc[0][np_] = acc[0][np_] + ep * (B + A);
+              acc[0][nn] = acc[0][nn] + en * (B - A);
+            }
+          }
+          if constexpr (P1 == 2) {
+            const cx<double> dh = cx<double>((x * h[l - 1].re - l * h[l].re) * ix, (x * h[l - 1].im - l * h[l].im) * ix);
+            const cx<double> B = ((l * (l + 1)) * ix * Pb) * (h[l] * wr_) + tau * (dh * wt);
+            if (am == 0) {
+              acc[1 - P0][np_] = acc[1 - P0][np_] + B;
+            } else {
+              const cx<double> A = mul_i(Ub * (dh * wp));
+              acc[1 - P0][np_] = acc[1 - P0][np_] + ep * (B + A);
+              acc[1 - P0][nn] = acc[1 - P0][nn] + en * (B - A);
+            }
+          }
+          const double an = ((2 * l + 1) * ct * a1 - (l + am) * a0) * (1.0 / (l + 1 - am));
+          a0 = a1;
+          a1 = an;
+          if (am == 0) {
+            const double bn = ((2 * l + 1) * ct * b1 - (l + 1) * b0) * (1.0 / l);
+            b0 = b1;
+            b1 = bn;
+          }
+        }
+        e = e * cx<double>(cf, sf);
       }
     }
   }
-  if (active) v[(size_t)r * N * L + e] = tm_c128{acc.re, acc.im};
+  if (!active) return;
+  const size_t o = ((size_t)r * N + i) * L + P0 * H;
+#pragma unroll
+  for (int q = 0; q < (P1 - P0) * H; ++q) {
+    const cx<double> z = acc[q / H][q % H];
+    if (gridDim.y > 1) part[((size_t)blockIdx.y * gridDim.z + blockIdx.z) * N * L + (size_t)i * L + P0 * H + q] = z;
+    else v[o + q] = tm_c128{z.re, z.im};
+  }
 }
 
-// grad[r][i] = 2 Re sum_slots mu * dt * aexc   (slot layout inputs)
 __global__ void grad_kernel(const c128* __restrict__ mu, const c128* __restrict__ dt,
                             const c128* __restrict__ aexc, int R, int N, int S, double* __restrict__ g) {
   const long long e = (long long)blockIdx.x * blockDim.x + threadIdx.x;
@@ -858,7 +1032,6 @@ __global__ void grad_kernel(const c128* __restrict__ mu, const c128* __restrict_
   g[e] = 2.0 * acc;
 }
 
-static inline unsigned nblk(long long n, int t = 256) { return (unsigned)((n + t - 1) / t); }
 
 // ---------------------------------------------------------------- position gradient
 // Coupling and incident terms of dO/dx_i, dO/dy_i (slot layout inputs):
@@ -1647,12 +1820,9 @@ int launch_near_field(tm_ctx* c, int R, const tm_c128* s, int P, const double* p
     const int nr = std::min(NF_MAXR, R - r0);
     const tm_c128* sr = s + (size_t)r0 * g.n * g.L;
     tm_c128* Er = E + (size_t)r0 * P * 3;
-    if (precision == TM_PREC_MIXED)
-      nf_dispatch<float>(g.lmax, nr, dim3(nblk(P)), c->stream, sr, g.n, site_pos(c),
-                         g.k, pts, P, Er);
-    else
-      nf_dispatch<double>(g.lmax, nr, dim3(nblk(P)), c->stream, sr, g.n, site_pos(c), g.k, pts,
-                          P, Er);
+    const int rc = precision == TM_PREC_MIXED ? nf_dispatch<float>(c, nr, sr, pts, P, Er)
+                                              : nf_dispatch<double>(c, nr, sr, pts, P, Er);
+    if (rc != TM_OK) return rc;
   }
   TM_HIP(c, hipGetLastError());
   return TM_OK;
@@ -1660,9 +1830,17 @@ int launch_near_field(tm_ctx* c, int R, const tm_c128* s, int P, const double* p
 
 int launch_far_field(tm_ctx* c, int R, const tm_c128* s, int D, const double* dirs, tm_c128* F) {
   const Geometry& g = c->g;
-#define FF_LAUNCH(LM)                                                                              \
-  hipLaunchKernelGGL(far_field_kernel<LM>, dim3((unsigned)((long long)R * D)), dim3(FF_THREADS), 0, \
-                     c->stream, s, R, g.n, g.L, g.lmax, site_pos(c), g.k, dirs, D, F)
+  // about 1024 workgroups, at least one scatterer per thread
+  const long long E = (long long)R * D;
+  int chunks = (int)std::max(1ll, std::min<long long>((g.n + FF_THREADS - 1) / FF_THREADS, 1024 / E));
+  const int per = (g.n + chunks - 1) / chunks;
+  chunks = (g.n + per - 1) / per;
+  int rc;
+  if ((rc = ensure(c, c->partial, (size_t)chunks * E * g.L * sizeof(c128))) != TM_OK) return rc;
+  c128* part = (c128*)c->partial.p;
+#define FF_LAUNCH(LM)                                                                                            \
+  hipLaunchKernelGGL(far_sums_kernel<LM>, dim3((unsigned)E, chunks), dim3(FF_THREADS), 0, c->stream, s, g.n, per, \
+                     site_pos(c), g.k, dirs, D, part)
   // per-thread coefficient sums sized for the geometry's lmax
   switch (g.lmax) {
     case 1: FF_LAUNCH(1); break;
@@ -1673,6 +1851,8 @@ int launch_far_field(tm_ctx* c, int R, const tm_c128* s, int D, const double* di
     default: FF_LAUNCH(6); break;
   }
 #undef FF_LAUNCH
+  hipLaunchKernelGGL(far_field_kernel, dim3((unsigned)E), dim3(128), 0, c->stream, (const c128*)part, chunks, g.L,
+                     g.lmax, g.k, dirs, D, F);
   TM_HIP(c, hipGetLastError());
   return TM_OK;
 }
@@ -1686,12 +1866,48 @@ int launch_detector(tm_ctx* c, const double* xd, const tm_c128* w, tm_c128* v) {
   return TM_OK;
 }
 
-int launch_near_field_t(tm_ctx* c, int R, int P, const double* pts, const tm_c128* w, tm_c128* v) {
+template <int LMAX>
+static int nft_launch(tm_ctx* c, int R, int P, const double* pts, const tm_c128* w, tm_c128* v) {
   const Geometry& g = c->g;
-  hipLaunchKernelGGL(near_field_t_kernel, dim3(nblk((long long)g.n * g.L), R), dim3(256), 0,
-                     c->stream, pts, w, P, g.n, g.L, g.lmax, site_pos(c), g.k, v);
+  const RowSplit q = row_split((long long)g.n * R, P, 8, 2048);
+  // rows are scatterers of one right-hand side; partial sums of at most 2 GB
+  const unsigned blocks = nblk(g.n, q.threads);
+  const size_t one = (size_t)g.n * g.L * sizeof(c128);
+  const int group = q.chunks > 1 ? (int)std::max<size_t>(1, std::min<size_t>(R, ((size_t)2 << 30) / (one * q.chunks))) : R;
+  int rc;
+  if (q.chunks > 1 && (rc = ensure(c, c->partial, one * q.chunks * group)) != TM_OK) return rc;
+  cx<double>* part = (cx<double>*)c->partial.p;
+  const SitePos sp = site_pos(c);
+  for (int r0 = 0; r0 < R; r0 += group) {
+    const int nr = std::min(group, R - r0);
+    const dim3 grid(blocks, q.chunks, nr), block(q.threads);
+    if constexpr (LMAX <= 3) {
+      hipLaunchKernelGGL((near_field_t_kernel<LMAX, 0, 2>), grid, block, 0, c->stream, pts, w, P, q.per, g.n, r0, sp,
+                         g.k, v, part);
+    } else {
+      hipLaunchKernelGGL((near_field_t_kernel<LMAX, 0, 1>), grid, block, 0, c->stream, pts, w, P, q.per, g.n, r0, sp,
+                         g.k, v, part);
+      hipLaunchKernelGGL((near_field_t_kernel<LMAX, 1, 2>), grid, block, 0, c->stream, pts, w, P, q.per, g.n, r0, sp,
+                         g.k, v, part);
+    }
+    if (q.chunks > 1) {
+      const long long total = (long long)nr * g.n * g.L;
+      hipLaunchKernelGGL(nf_combine<double>, dim3(nblk(total)), dim3(256), 0, c->stream, part, q.chunks, total,
+                         v + (size_t)r0 * g.n * g.L);
+    }
+  }
   TM_HIP(c, hipGetLastError());
   return TM_OK;
+}
+int launch_near_field_t(tm_ctx* c, int R, int P, const double* pts, const tm_c128* w, tm_c128* v) {
+  switch (c->g.lmax) {
+    case 1: return nft_launch<1>(c, R, P, pts, w, v);
+    case 2: return nft_launch<2>(c, R, P, pts, w, v);
+    case 3: return nft_launch<3>(c, R, P, pts, w, v);
+    case 4: return nft_launch<4>(c, R, P, pts, w, v);
+    case 5: return nft_launch<5>(c, R, P, pts, w, v);
+    default: return nft_launch<6>(c, R, P, pts, w, v);
+  }
 }
 
 int launch_grad(tm_ctx* c, int R, const c128* mu_slot, const c128* aexc_slot, double* grad) {
