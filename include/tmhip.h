@@ -386,9 +386,10 @@ int tm_grad_radius(tm_ctx* ctx, int n_rhs, const tm_c128* mu, const tm_c128* s,
  * with lam = T^T mu the adjoint unknown (mu from tm_adjoint_solve of the
  * objective's weighted detector vector), v_c the detector vectors of
  * tm_detector_vector.  The coupling term uses derivative blocks
- * d xi(k d)^T / d d_a per lattice displacement (FP64 tables built on first use,
- * four of the size of the FP64 translation table); the gradient is taken at
- * the current lattice positions.
+ * d xi(k d)^T / d d_a per lattice displacement, applied in FP64 by Fourier
+ * transform where the lattice fits it (see tm_set_matvec_config), else from four
+ * tables of the size of the FP64 translation table; either is built on first
+ * use.  The gradient is taken at the current lattice positions.
  * mu, s, a0: device [R][N][L]; grad: device [R][N][2] doubles (written).
  * khat: host [R][3], the plane-wave directions a0 was made with (the incident
  * term i k khat_a lam_i . a0_i), or NULL when the incident field does not

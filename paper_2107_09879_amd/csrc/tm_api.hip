@@ -139,7 +139,7 @@ void tm_destroy(tm_ctx* c) {
   hipSetDevice(c->device);
   hipStreamSynchronize(c->stream);
   for (tmh::DevBuf* b : {&c->dtab[0], &c->dtab[1], &c->dtab[2], &c->dtab[3], &c->gpos, &c->jinc_buf,
-                        &c->kry_dev, &c->tmb, &c->tmflag, &c->spec_sym, &c->spec_w, &c->spec_const})
+                        &c->kry_dev, &c->tmb, &c->tmflag, &c->spec_sym, &c->spec_w, &c->spec_const, &c->spec_d})
     tmh::release(*b);
   for (tmh::DevBuf* b : {&c->tab64, &c->tab32, &c->tabT64, &c->tabT32, &c->t64, &c->t32, &c->dt64,
                         &c->tden, &c->ttmp, &c->partial, &c->xlow, &c->work_a, &c->work_b, &c->work_c, &c->basis,
@@ -225,7 +225,7 @@ int tm_set_geometry(tm_ctx* c, int n, const double* pos, double k, int lmax) {
   tmh::host_slot_maps(lmax, g, c->maps);
   tmh::host_mblock_maps(lmax, c->mbmaps);
   c->have_geom = c->have_t = c->have_dt = c->have_tabT = c->have_dtab = c->t_dense = false;
-  c->t_mblock = c->have_spec = c->spec_known = false;
+  c->t_mblock = c->have_spec = c->have_spec_d = c->spec_known = false;
   c->plan_R[0] = c->plan_R[1] = -1;
   int rc;
   if (lattice) {
@@ -703,7 +703,9 @@ int tm_grad_position(tm_ctx* c, int R, const tm_c128* mu, const tm_c128* s, cons
   }
   const tmh::Geometry& g = c->g;
   int rc;
-  if (!c->have_dtab && (rc = tmh::build_derivative_tables(c)) != TM_OK) return rc;
+  // derivative products by transform, or by blocks on derivative tables
+  const bool spec = !c->mv_block[0] && tmh::spec_use(c, 0);
+  if (!spec && !c->have_dtab && (rc = tmh::build_derivative_tables(c)) != TM_OK) return rc;
   const long long vec = g.vec_len(), tot = (long long)R * vec;
   std::vector<c128> dcoef;
   std::vector<int> ddm;
@@ -725,11 +727,13 @@ int tm_grad_position(tm_ctx* c, int R, const tm_c128* mu, const tm_c128* s, cons
   }
   tmh::pack_slots(c->stream, g, c->maps, R, s, ss);
   if (khat) tmh::pack_slots(c->stream, g, c->maps, R, a0, aa);
-  // the four derivative products (FP64 block matvec on the derivative tables)
+  // the four derivative products
   const int tgt = c->mv_items[0] > 0 ? c->mv_items[0] : std::max(1, (16384 + 2 * R - 1) / (2 * R));
   const void* src[4] = {ss, ss, lam, lam};
   c128* dst[4] = {dxs, dys, dxtl, dytl};
-  for (int t = 0; t < 4; ++t)
+  for (int t = 0; t < 4 && spec; ++t)
+    if ((rc = tmh::spec_derivative(c, t & 1, t >> 1, R, (const c128*)src[t], dst[t])) != TM_OK) return rc;
+  for (int t = 0; t < 4 && !spec; ++t)
     if ((rc = tmh::lds_apply<double>(c, 0, R, c->dtab[t].p, src[t], nullptr, dst[t], TM_OP_COUPLING,
                                      tgt, nullptr, nullptr, 2)) != TM_OK)
       return rc;

@@ -179,9 +179,9 @@ struct tm_ctx {
   // tables of the geometry (built on first use), grid workspace, constants of
   // lmax; per precision slot whether it fits, and whether tm_set_matvec_config
   // or tm_autotune asked for the block kernels instead
-  tmh::DevBuf spec_sym, spec_w, spec_const;
+  tmh::DevBuf spec_sym, spec_w, spec_const, spec_d;  // spec_d: derivatives' symbols
   tmh::SpecPlan spec;
-  bool have_spec = false, spec_known = false, spec_fit[2] = {false, false}, mv_block[2] = {false, false};
+  bool have_spec = false, have_spec_d = false, spec_known = false, spec_fit[2] = {false, false}, mv_block[2] = {false, false};
   int spec_const_lmax = 0;
   int plan_nreg[2] = {0, 0};  // LDS plan: items of regular tiles (wide-tile items follow)
   int last_batch_graphed = 0;
@@ -233,6 +233,8 @@ bool spec_fits(const Geometry& g, int nx, int ny, SpecDim& X, SpecDim& Y);
 bool spec_use(tm_ctx* c, int which);  // whether the geometry fits it at this precision slot
 template <typename T>
 int spec_apply(tm_ctx* c, Op op, int R, const c128* x, c128* y);
+
+int spec_derivative(tm_ctx* c, int axis, bool transposed, int R, const c128* x, c128* y);
 
 // basis kernels (tm_basis.hip)
 int launch_mie(tm_ctx* c, const double* radii, double n_re, double n_im);

@@ -54,6 +54,7 @@ struct SpecArgs {
   SpecSlots slots[NCLASS];
   unsigned long long pmask[NCLASS];
   int R, S, NG, nf, members;
+  T sgn, sgn_mirror;  // of the block, and of U M U for its mirror image
 };
 enum { SPEC_FORWARD = 0, SPEC_PLAIN = 1, SPEC_MINUS = 2 };
 

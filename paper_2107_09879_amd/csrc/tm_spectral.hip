@@ -380,9 +380,10 @@ __global__ __launch_bounds__(512) void spec_columns(SpecArgs<T> a) {
           zr += mr * d.re - mi * d.im;
           zi += mr * d.im + mi * d.re;
         }
-        sh[p1 * S + i] = cplx<T>{yr, yi};
+        sh[p1 * S + i] = cplx<T>{a.sgn * yr, a.sgn * yi};
         const int own = info[i];
-        if (p2 != p1) sh[p2 * S + (own & 255)] = (own >> 8) ? cplx<T>{-zr, -zi} : cplx<T>{zr, zi};
+        const T sz = (own >> 8) ? -a.sgn_mirror : a.sgn_mirror;
+        if (p2 != p1) sh[p2 * S + (own & 255)] = cplx<T>{sz * zr, sz * zi};
       }
       __builtin_amdgcn_wave_barrier();
     }
@@ -431,11 +432,12 @@ __global__ __launch_bounds__(256) void spec_back(SpecArgs<T> a) {
 }
 
 // ---------------------------------------------------------------- symbol
-// Rows of the scalar fields and their transform along x: blockIdx.x the
-// wrapped displacement row, blockIdx.y a group of 16 fields.
+// Rows of the scalar fields (or their derivatives along x or y, axis 0 or 1) and
+// their transform along x: blockIdx.x the wrapped displacement row, blockIdx.y a
+// group of 16 fields.
 __global__ __launch_bounds__(256) void spec_symbol_rows(SpecDim X, SpecDim Y, const c128* __restrict__ tw,
                                                         const short2* __restrict__ fields, int nf,
-                                                        int qmax, double pitch, double k,
+                                                        int qmax, double pitch, double k, int axis,
                                                         c128* __restrict__ G, int ldf) {
   c128* sh = reinterpret_cast<c128*>(spec_lds);
   const int iy = blockIdx.x, f0 = blockIdx.y * SLOTS;
@@ -451,6 +453,8 @@ __global__ __launch_bounds__(256) void spec_symbol_rows(SpecDim X, SpecDim Y, co
     double sn, cs;
     sincos(z, &sn, &cs);
     const double iz = 1.0 / z;
+    // d/da (h_q e^{i mu phi}) = k (h_q' rhat_a + i mu h_q / z phihat_a) e^{i mu phi}
+    const double rho = z / k, ra = (axis == 1 ? ay : ax) / rho, pa = (axis == 1 ? ax : -ay) / rho;
     c128 prev{cs * iz, sn * iz}, h{sn * iz, -cs * iz};
     for (int q = 0; q <= qmax; ++q) {
       for (int s = 0; s < SLOTS && f0 + s < nf; ++s) {
@@ -458,7 +462,12 @@ __global__ __launch_bounds__(256) void spec_symbol_rows(SpecDim X, SpecDim Y, co
         if (fd.x != q) continue;
         double es, ec;
         sincos((double)fd.y * phi, &es, &ec);
-        sh[p * SLOTS + s] = c128{h.re * ec - h.im * es, h.re * es + h.im * ec};
+        c128 v = h;
+        if (axis >= 0) {
+          const double g = (q + 1) * iz, t = fd.y * iz * pa;
+          v = c128{k * ((prev.re - g * h.re) * ra - t * h.im), k * ((prev.im - g * h.im) * ra + t * h.re)};
+        }
+        sh[p * SLOTS + s] = c128{v.re * ec - v.im * es, v.re * es + v.im * ec};
       }
       const double f = (2 * q + 1) * iz;
       const c128 next{f * h.re - prev.re, f * h.im - prev.im};
@@ -492,7 +501,7 @@ __global__ __launch_bounds__(256) void spec_symbol_columns(SpecDim X, SpecDim Y,
     const c128 v = sh[pos[m] * SLOTS + s];
     const size_t o = ((size_t)p * pairs + m) * nf + f0 + s;
     sym64[o] = c128{v.re * scale, v.im * scale};
-    sym32[o] = c64{(float)(v.re * scale), (float)(v.im * scale)};
+    if (sym32) sym32[o] = c64{(float)(v.re * scale), (float)(v.im * scale)};
   }
 }
 
@@ -732,6 +741,26 @@ size_t spec_tmp_bytes(const Geometry& g, const SpecDim& X, const SpecDim& Y) {
   const int nf = (g.lmax + 1) * (2 * g.lmax + 1);
   return (size_t)X.P * Y.P * (SLOTS * ((nf + SLOTS - 1) / SLOTS)) * sizeof(c128);
 }
+// axis -1: of the fields, 0 and 1: of their derivatives; sym32 may be null
+static int spec_symbol(tm_ctx* c, const SpecPlan& pl, int axis, void* tmp, c128* sym64, c64* sym32) {
+  const Geometry& g = c->g;
+  const SpecConst& k = spec_constants(g);
+  const SpecDim &X = pl.X, &Y = pl.Y;
+  const int nf = k.nf, groups = (nf + SLOTS - 1) / SLOTS, ldf = groups * SLOTS;
+  const SpecConstLayout L = spec_const_layout(k.S, k.NQ, nf);
+  const short2* fields = (const short2*)((char*)c->spec_const.p + L.fields);
+  const size_t lx = (size_t)X.P * SLOTS * sizeof(c128), ly = (size_t)Y.P * SLOTS * sizeof(c128);
+  int rc;
+  if ((rc = allow_lds(c, (const void*)spec_symbol_rows, lx)) != TM_OK) return rc;
+  if ((rc = allow_lds(c, (const void*)spec_symbol_columns, ly)) != TM_OK) return rc;
+  hipLaunchKernelGGL(spec_symbol_rows, dim3(Y.P, groups), dim3(256), lx, c->stream, X, Y, pl.twx64, fields,
+                     nf, k.qmax, g.pitch, g.k, axis, (c128*)tmp, ldf);
+  hipLaunchKernelGGL(spec_symbol_columns, dim3(X.P, groups), dim3(256), ly, c->stream, X, Y, pl.twy64, pl.pos,
+                     nf, (const c128*)tmp, ldf, sym64, sym32);
+  TM_HIP(c, hipGetLastError());
+  return TM_OK;
+}
+
 int spec_build(tm_ctx* c, int nx, int ny, void* buf, void* tmp, SpecPlan& pl) {
   const Geometry& g = c->g;
   int rc;
@@ -739,7 +768,7 @@ int spec_build(tm_ctx* c, int nx, int ny, void* buf, void* tmp, SpecPlan& pl) {
   if (!spec_dim(nx, pl.X) || !spec_dim(ny, pl.Y)) return set_err(c, TM_ERR_INVALID_ARG, "lattice too long to transform");
   const SpecConst& k = spec_constants(g);
   const SpecDim &X = pl.X, &Y = pl.Y;
-  const int nf = k.nf, groups = (nf + SLOTS - 1) / SLOTS, ldf = groups * SLOTS;
+  const int nf = k.nf;
   const size_t ns = (size_t)X.P * (Y.P / 2 + 1) * nf;
   char* b = static_cast<char*>(buf);
   auto take = [&](size_t bytes) {
@@ -771,16 +800,20 @@ int spec_build(tm_ctx* c, int nx, int ny, void* buf, void* tmp, SpecPlan& pl) {
   // the upload is not ordered with a non-blocking stream: what it replaces must be done with
   TM_HIP(c, hipStreamSynchronize(c->stream));
   TM_HIP(c, hipMemcpy(tables, h.data(), h.size(), hipMemcpyHostToDevice));
-  const SpecConstLayout L = spec_const_layout(k.S, k.NQ, nf);
-  const short2* fields = (const short2*)((char*)c->spec_const.p + L.fields);
-  const size_t lx = (size_t)X.P * SLOTS * sizeof(c128), ly = (size_t)Y.P * SLOTS * sizeof(c128);
-  if ((rc = allow_lds(c, (const void*)spec_symbol_rows, lx)) != TM_OK) return rc;
-  if ((rc = allow_lds(c, (const void*)spec_symbol_columns, ly)) != TM_OK) return rc;
-  hipLaunchKernelGGL(spec_symbol_rows, dim3(Y.P, groups), dim3(256), lx, c->stream, X, Y, pl.twx64, fields,
-                     nf, k.qmax, g.pitch, g.k, (c128*)tmp, ldf);
-  hipLaunchKernelGGL(spec_symbol_columns, dim3(X.P, groups), dim3(256), ly, c->stream, X, Y, pl.twy64, pl.pos,
-                     nf, (const c128*)tmp, ldf, pl.sym64, pl.sym32);
-  TM_HIP(c, hipGetLastError());
+  return spec_symbol(c, pl, -1, tmp, pl.sym64, pl.sym32);
+}
+
+// The derivatives' symbols (FP64) of the context's own lattice, whose product has run.
+static int spec_build_derivatives(tm_ctx* c) {
+  const Geometry& g = c->g;
+  const SpecDim &X = c->spec.X, &Y = c->spec.Y;
+  const size_t ns = (size_t)X.P * (Y.P / 2 + 1) * (g.lmax + 1) * (2 * g.lmax + 1);
+  int rc;
+  if ((rc = ensure(c, c->spec_w, spec_tmp_bytes(g, X, Y))) != TM_OK) return rc;
+  if ((rc = ensure(c, c->spec_d, 2 * ns * sizeof(c128))) != TM_OK) return rc;
+  for (int axis = 0; axis < 2; ++axis)
+    if ((rc = spec_symbol(c, c->spec, axis, c->spec_w.p, (c128*)c->spec_d.p + axis * ns, nullptr)) != TM_OK) return rc;
+  c->have_spec_d = true;
   return TM_OK;
 }
 
@@ -815,6 +848,7 @@ void spec_fill_args(tm_ctx* c, bool transposed, SpecArgs<T>& a) {
   a.NG = c->g.NG;
   a.nf = k.nf;
   a.members = k.members;
+  a.sgn = a.sgn_mirror = 1;
   for (int q = 0; q < NCLASS; ++q) {
     a.slots[q] = k.slots[q];
     a.pmask[q] = k.pmask[q];
@@ -881,6 +915,30 @@ int spec_apply(tm_ctx* c, Op op, int R, const c128* x, c128* y) {
   a.active = c->mv_active;
   a.R = R;
   return spec_launch<T>(c, a, op, g.ny, c->spec.X.P, c->spec.X.P, c->spec.Y);
+}
+// y = D x (transposed: sum_s D(x_s - x_t)^T x_s) with D the derivative of the
+// blocks by the displacement along `axis`.  Mirroring y changes the sign of the
+// y derivative, inverting the displacement that of both.
+int spec_derivative(tm_ctx* c, int axis, bool transposed, int R, const c128* x, c128* y) {
+  const Geometry& g = c->g;
+  const SpecDim &X = c->spec.X, &Y = c->spec.Y;
+  const size_t w = spec_w_elems(X, Y, g.S) * R * sizeof(c128);
+  int rc;
+  if ((rc = spec_ready(c, w)) != TM_OK) return rc;
+  if (!c->have_spec_d && (rc = spec_build_derivatives(c)) != TM_OK) return rc;
+  if ((rc = ensure(c, c->spec_w, w)) != TM_OK) return rc;
+  SpecArgs<double> a{};
+  spec_fill_args<double>(c, transposed, a);
+  a.one = spec_sub<double>(c->spec);
+  a.one.sym = (const c128*)c->spec_d.p + (size_t)axis * X.P * (Y.P / 2 + 1) * a.nf;
+  a.sgn = transposed ? -1.0 : 1.0;
+  a.sgn_mirror = axis ? -a.sgn : a.sgn;
+  a.x = x;
+  a.t = (const c128*)c->t64.p;
+  a.y = y;
+  a.W = (c128*)c->spec_w.p;
+  a.R = R;
+  return spec_launch<double>(c, a, transposed ? Op::CouplingT : Op::Coupling, g.ny, X.P, X.P, Y);
 }
 template int spec_apply<float>(tm_ctx*, Op, int, const c128*, c128*);
 template int spec_apply<double>(tm_ctx*, Op, int, const c128*, c128*);

@@ -70,3 +70,29 @@ def test_new_geometry_replaces_the_transform():
         assert float(torch.linalg.vector_norm(a - b)) <= 1e-12 * float(torch.linalg.vector_norm(b))
     ctx.close()
     ref.close()
+
+
+@pytest.mark.parametrize("nx,ny,lmax,rhs", [(2, 1, 1, 1), (1, 6, 3, 2), (9, 14, 2, 1), (31, 18, 3, 2), (12, 11, 4, 1), (7, 8, 6, 3)])
+def test_position_gradient_by_transform_and_by_tables(nx, ny, lmax, rhs):
+    """The derivative products by transform against those by derivative tables (which
+    the oracle's gradient checks), FP64 in both."""
+    ctx, ref = tmhip.Context(0), tmhip.Context(0)
+    r = torch.tensor(wl.uniform_radii(nx * ny, 0.15, 0.25, 5), dtype=torch.float64, device=DEV)
+    for q in (ctx, ref):
+        q.set_geometry(wl.lattice_positions(nx, ny), wl.K, lmax)
+        q.set_spheres(r, wl.N_REL)
+    ref.set_matvec_config("fp64", 9, 0)
+    rng = np.random.default_rng(nx + ny)
+
+    def vec():
+        return torch.tensor(rng.normal(size=(rhs, nx * ny, ctx.L)) + 1j * rng.normal(size=(rhs, nx * ny, ctx.L)), device=DEV)
+
+    mu, s, a0 = vec(), vec(), vec()
+    kh = np.tile([[0.6, 0.0, 0.8]], (rhs, 1))
+    w = rng.normal(size=(rhs, 3)) + 1j * rng.normal(size=(rhs, 3))
+    xd = np.array([0.3, 0.4, 3.0])
+    for q in range(2):  # the second call finds the symbols built
+        a, b = (c.grad_position(mu, s, a0, kh, xd, w) for c in (ctx, ref))
+        assert float(torch.linalg.vector_norm(a - b)) <= 1e-12 * float(torch.linalg.vector_norm(b))
+    ctx.close()
+    ref.close()
