@@ -94,7 +94,8 @@ struct SubParams {
 constexpr int SPEC_STAGES = 5, SPEC_P_MAX = 640;
 struct SpecDim {
   int n, P, ns;
-  unsigned char r[SPEC_STAGES];
+  unsigned rad;  // six bits each: an array would be indexed in scratch memory
+  __host__ __device__ int r(int s) const { return (rad >> (6 * s)) & 63; }
 };
 // A lattice's transformed blocks: symbol, twiddle factors, y frequency order.
 struct SpecPlan {

@@ -7,29 +7,15 @@ namespace tmh {
 
 constexpr size_t SPEC_LDS_MAX = 160 * 1024;  // LDS of one CU
 
-// Number of scalar fields (staged per pair of columns) and of terms per entry:
-// at most lmax + 1, over the lmax of a slot-group count (3, 4, 6).  The staging
-// rows hold NQ - 1 more entries than fields, which zero constants multiply.
-template <int NG>
-struct SpecCfg;
-template <>
-struct SpecCfg<1> {
-  static constexpr int NQ = 4, NF = 28 + 3;
+// Per lmax: terms of an entry (over q, in steps of two from |mu|), class members,
+// slots, scalar fields (staged rows end with NQ - 1 zeros, which zero constants
+// multiply).  A class has one member per (l, m): p follows from its parity.
+// Members are numbered by m, then l; lanes and constants go by that number.
+template <int LMAX>
+struct SpecCfg {
+  static constexpr int NQ = LMAX + 1, MEM = LMAX * (LMAX + 2), NG = (MEM + SLOTS - 1) / SLOTS, S = NG * SLOTS;
+  static constexpr int NFIELD = (LMAX + 1) * (2 * LMAX + 1), NF = NFIELD + NQ - 1;
 };
-template <>
-struct SpecCfg<2> {
-  static constexpr int NQ = 5, NF = 45 + 4;
-};
-template <>
-struct SpecCfg<3> {
-  static constexpr int NQ = 7, NF = 91 + 6;
-};
-
-// slots of a class: the slot of (l, -m, p), plus 256 p
-struct SpecSlots {
-  int info[SMAX];
-};
-
 template <typename T>
 struct SpecSub {
   SpecDim X, Y;
@@ -49,33 +35,37 @@ struct SpecArgs {
   c128* y;
   cplx<T>* W;
   const T* coef;
-  const unsigned char* first;
+  const int *start, *info;
   const int *stop, *active;
-  SpecSlots slots[NCLASS];
   unsigned long long pmask[NCLASS];
-  int R, S, NG, nf, members;
+  int R, S, NG, nf, lmax;
   T sgn, sgn_mirror;  // of the block, and of U M U for its mirror image
 };
 enum { SPEC_FORWARD = 0, SPEC_PLAIN = 1, SPEC_MINUS = 2 };
 
+// Constants of one lmax in the context's buffer: coef [class][source][target][NQ]
+// for A and A^T, start [m of the source][target]: first field of their order mu,
+// info [class][member]: slot | slot of (l, -m) << 8 | p << 16, and the fields (q, mu).
 struct SpecConstLayout {
-  size_t coef64[2], coef32[2], first[2], fields, bytes;
+  size_t coef64[2], coef32[2], start[2], info, fields, bytes;
 };
-inline SpecConstLayout spec_const_layout(int S, int NQ, int nf) {
+inline SpecConstLayout spec_const_layout(int lmax) {
   SpecConstLayout L;
+  const int mem = lmax * (lmax + 2), nq = lmax + 1;
   size_t o = 0;
   auto take = [&](size_t b) {
     const size_t at = o;
     o += (b + 255) & ~(size_t)255;
     return at;
   };
-  const size_t n = (size_t)NCLASS * S * S;
+  const size_t n = (size_t)NCLASS * mem * mem * nq;
   for (int tr = 0; tr < 2; ++tr) {
-    L.coef64[tr] = take(n * NQ * sizeof(double));
-    L.coef32[tr] = take(n * NQ * sizeof(float));
-    L.first[tr] = take(n);
+    L.coef64[tr] = take(n * sizeof(double));
+    L.coef32[tr] = take(n * sizeof(float));
+    L.start[tr] = take((size_t)(2 * lmax + 1) * mem * sizeof(int));
   }
-  L.fields = take((size_t)nf * 4);
+  L.info = take((size_t)NCLASS * mem * sizeof(int));
+  L.fields = take((size_t)(lmax + 1) * (2 * lmax + 1) * 4);
   L.bytes = o;
   return L;
 }

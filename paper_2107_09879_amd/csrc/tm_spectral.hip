@@ -27,8 +27,8 @@
 // Bound: at 100x100, lmax 3 each launch moves 10-20 MB in a few microseconds and
 // the barriers and LDS round trips between stages set the time.  Operator with its
 // layout conversions, one right-hand side: 100x100 FP64 5.6 ms (block kernels) ->
-// 85 us, complex64 2.67 ms -> 78 us; 150x150 26.3 ms -> 220 us and 13.0 ms ->
-// 120 us; 33x31 at lmax 6 FP64 1.15 ms -> 128 us; 8x8 at lmax 2 100 -> 28 us, so no
+// 78 us, complex64 2.67 ms -> 58 us; 150x150 26.3 ms -> 150 us and 13.0 ms ->
+// 94 us; 33x31 at lmax 6 FP64 1.15 ms -> 70 us; 8x8 at lmax 2 100 -> 27 us, so no
 // lattice that fits is left to the block kernels.  Error against 64-bit sums of
 // the forward operator at 100x100: FP64 5.4e-16 (block kernels 1.3e-15), complex64
 // 9.7e-8 (6.1e-7).
@@ -204,7 +204,7 @@ struct Dft<T, 16, INV> {
 // One stage of a transform over positions of `P` = N blocks of the current
 // length N = R M, for W slots side by side.  ld(pos, slot), st(pos, slot, v).
 template <typename T, int R, int W, bool INV, class LD, class ST>
-__device__ __forceinline__ void fft_stage(int P, int N, const cplx<T>* __restrict__ tw, LD ld, ST st) {
+__device__ __forceinline__ void fft_stage(int P, int N, const cplx<T>* tw, LD ld, ST st) {
   const int M = N / R, stride = P / N;
   const unsigned magic = (1u << 20) / (unsigned)M + 1u;  // b / M for b < 640
   const int items = (P / R) * W;
@@ -215,21 +215,26 @@ __device__ __forceinline__ void fft_stage(int P, int N, const cplx<T>* __restric
     cplx<T> a[R];
 #pragma unroll
     for (int k = 0; k < R; ++k) a[k] = ld(base + k * M, slot);
+    // (the stage of single butterflies, M = 1, has no twiddle factors)
     if (INV) {
+      if (M > 1) {
 #pragma unroll
-      for (int k = 1; k < R; ++k) a[k] = cmulw(a[k], tw[j * k * stride], true);
+        for (int k = 1; k < R; ++k) a[k] = cmulw(a[k], tw[j * k * stride], true);
+      }
       Dft<T, R, true>::run(a);
     } else {
       Dft<T, R, false>::run(a);
+      if (M > 1) {
 #pragma unroll
-      for (int k = 1; k < R; ++k) a[k] = cmulw(a[k], tw[j * k * stride], false);
+        for (int k = 1; k < R; ++k) a[k] = cmulw(a[k], tw[j * k * stride], false);
+      }
     }
 #pragma unroll
     for (int k = 0; k < R; ++k) st(base + k * M, slot, a[k]);
   }
 }
 template <typename T, int W, bool INV, class LD, class ST>
-__device__ __forceinline__ void fft_any(int R, int P, int N, const cplx<T>* __restrict__ tw, LD ld, ST st) {
+__device__ __forceinline__ void fft_any(int R, int P, int N, const cplx<T>* tw, LD ld, ST st) {
   switch (R) {
     case 2: fft_stage<T, 2, W, INV>(P, N, tw, ld, st); break;
     case 3: fft_stage<T, 3, W, INV>(P, N, tw, ld, st); break;
@@ -245,37 +250,38 @@ __device__ __forceinline__ void fft_any(int R, int P, int N, const cplx<T>* __re
 }
 // Forward transform: the first stage reads through `ld`, the last writes
 // through `st` (at least two stages), LDS `sh` in between; inverse likewise
-// in the opposite stage order.
+// in the opposite stage order.  The first forward stage takes its twiddle factors
+// from memory (`twg`, their latency overlaps the data's), the others from `tw`, a
+// copy in LDS complete at the next barrier where there is one.
 template <typename T, int W, class LD, class ST>
-__device__ __forceinline__ void fft_forward(const SpecDim& d, const cplx<T>* __restrict__ tw, cplx<T>* sh,
-                                            LD ld, ST st) {
+__device__ __forceinline__ void fft_forward(const SpecDim& d, const cplx<T>* __restrict__ twg, const cplx<T>* tw,
+                                            cplx<T>* sh, LD ld, ST st) {
   auto lds_ld = [&](int p, int s) { return sh[p * W + s]; };
   auto lds_st = [&](int p, int s, cplx<T> v) { sh[p * W + s] = v; };
   int N = d.P;
-  fft_any<T, W, false>(d.r[0], d.P, N, tw, ld, lds_st);
-  N /= d.r[0];
+  fft_any<T, W, false>(d.r(0), d.P, N, twg, ld, lds_st);
+  N /= d.r(0);
   for (int s = 1; s + 1 < d.ns; ++s) {
     __syncthreads();
-    fft_any<T, W, false>(d.r[s], d.P, N, tw, lds_ld, lds_st);
-    N /= d.r[s];
+    fft_any<T, W, false>(d.r(s), d.P, N, tw, lds_ld, lds_st);
+    N /= d.r(s);
   }
   __syncthreads();
-  fft_any<T, W, false>(d.r[d.ns - 1], d.P, N, tw, lds_ld, st);
+  fft_any<T, W, false>(d.r(d.ns - 1), d.P, N, tw, lds_ld, st);
 }
 template <typename T, int W, class LD, class ST>
-__device__ __forceinline__ void fft_inverse(const SpecDim& d, const cplx<T>* __restrict__ tw, cplx<T>* sh,
-                                            LD ld, ST st) {
+__device__ __forceinline__ void fft_inverse(const SpecDim& d, const cplx<T>* tw, cplx<T>* sh, LD ld, ST st) {
   auto lds_ld = [&](int p, int s) { return sh[p * W + s]; };
   auto lds_st = [&](int p, int s, cplx<T> v) { sh[p * W + s] = v; };
-  int N = d.r[d.ns - 1];
-  fft_any<T, W, true>(d.r[d.ns - 1], d.P, N, tw, ld, lds_st);
+  int N = d.r(d.ns - 1);
+  fft_any<T, W, true>(d.r(d.ns - 1), d.P, N, tw, ld, lds_st);
   for (int s = d.ns - 2; s > 0; --s) {
     __syncthreads();
-    N *= d.r[s];
-    fft_any<T, W, true>(d.r[s], d.P, N, tw, lds_ld, lds_st);
+    N *= d.r(s);
+    fft_any<T, W, true>(d.r(s), d.P, N, tw, lds_ld, lds_st);
   }
   __syncthreads();
-  fft_any<T, W, true>(d.r[0], d.P, d.P, tw, lds_ld, st);
+  fft_any<T, W, true>(d.r(0), d.P, d.P, tw, lds_ld, st);
 }
 
 // ---------------------------------------------------------------- kernels
@@ -292,13 +298,30 @@ __device__ __forceinline__ bool spec_skip(const SpecArgs<T>& a, int k, int r) {
   return (a.stop && *a.stop) || (a.active && !a.active[k * a.R + r]);
 }
 
+// Pointers out of a table in memory are generic ones to the compiler, and their
+// accesses flat: these are all to global memory.
+template <typename U>
+__device__ __forceinline__ U* global_ptr(U* p) {
+  return (U*)(__attribute__((address_space(1))) U*)p;
+}
+template <typename T>
+__device__ __forceinline__ SpecSub<T> spec_subregion(const SpecArgs<T>& a, int k) {
+  SpecSub<T> s = a.one;
+  if (a.subs) s = a.subs[k];
+  s.twx = global_ptr(s.twx);
+  s.twy = global_ptr(s.twy);
+  s.sym = global_ptr(s.sym);
+  s.pos = global_ptr(s.pos);
+  return s;
+}
+
 // blockIdx.x: row (of a subregion), blockIdx.y: (rhs, class, slot group)
 template <typename T, bool MULT>
 __global__ __launch_bounds__(256) void spec_rows(SpecArgs<T> a) {
   const int g = blockIdx.y % a.NG, c = (blockIdx.y / a.NG) & 1, r = blockIdx.y / (2 * a.NG);
   const SpecJob job = a.row_jobs ? a.row_jobs[blockIdx.x] : SpecJob{0, (int)blockIdx.x};
   if (spec_skip(a, job.sub, r)) return;
-  const SpecSub<T> s = a.subs ? a.subs[job.sub] : a.one;
+  const SpecSub<T> s = spec_subregion(a, job.sub);
   cplx<T>* sh = reinterpret_cast<cplx<T>*>(spec_lds);
   const int S = a.S, n = s.X.n, N = n * s.Y.n;
   const size_t off = ((size_t)c * N + (size_t)job.index * n) * S + g * SLOTS;
@@ -308,7 +331,7 @@ __global__ __launch_bounds__(256) void spec_rows(SpecArgs<T> a) {
   const unsigned long long pm = a.pmask[c] >> (g * SLOTS);
   const size_t wp = (size_t)s.Y.n * S;
   fft_forward<T, SLOTS>(
-      s.X, s.twx, sh,
+      s.X, s.twx, s.twx, sh,
       [&](int p, int slot) {
         if (p >= n) return cplx<T>{(T)0, (T)0};
         c128 v = x[(size_t)p * S + slot];
@@ -321,78 +344,225 @@ __global__ __launch_bounds__(256) void spec_rows(SpecArgs<T> a) {
       [&](int p, int slot, cplx<T> v) { W[(size_t)p * wp + slot] = v; });
 }
 
+// Where a column workgroup's LDS goes: the column, a symbol row per pair in work;
+// and if they fit (FULL) the twiddle factors, the position of every frequency and
+// at lmax <= 3 the class's constants.
+template <typename T, int LMAX, bool FULL>
+struct ColumnLds {
+  using Cfg = SpecCfg<LMAX>;
+  static constexpr int GROUPS = Cfg::NG == 1 ? 4 : Cfg::NG == 2 ? 2 : 1;  // pairs side by side in a wave
+  static constexpr int PB = FULL ? 2 : 1;                                 // pairs at once per lane
+  size_t sym, tw, pos, coef, bytes;
+  __host__ __device__ ColumnLds(int P, int threads) {
+    sym = (size_t)P * Cfg::S * sizeof(cplx<T>);
+    tw = sym + (size_t)(threads / 64) * GROUPS * PB * Cfg::NF * sizeof(cplx<T>);
+    pos = tw + (FULL ? (size_t)P * sizeof(cplx<T>) : 0);
+    coef = pos + (FULL ? ((size_t)P * 2 + 15) / 16 * 16 : 0);
+    bytes = coef + (FULL && Cfg::NG == 1 ? (size_t)Cfg::MEM * Cfg::MEM * Cfg::NQ * sizeof(T) : 0);
+  }
+};
+
+// v of lane J of the 16 that share a row
+template <int J>
+__device__ __forceinline__ float row_bcast(float v) {
+  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x150 + J, 0xf, 0xf, true));
+}
+template <int J>
+__device__ __forceinline__ double row_bcast(double v) {
+  const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), 0x150 + J, 0xf, 0xf, true);
+  const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), 0x150 + J, 0xf, 0xf, true);
+  return __hiloint2double(hi, lo);
+}
+
+// y += M u, z += M v for a pair, M = sum_t c_t f_t
+template <typename T, int NQ>
+__device__ __forceinline__ void block_entry(const T* c, const cplx<T>* f, cplx<T> u, cplx<T> v, cplx<T>& y, cplx<T>& z) {
+  T mr = c[0] * f[0].re, mi = c[0] * f[0].im;
+#pragma unroll
+  for (int t = 1; t < NQ; ++t) {
+    mr += c[t] * f[t].re;
+    mi += c[t] * f[t].im;
+  }
+  y.re += mr * u.re - mi * u.im;
+  y.im += mr * u.im + mi * u.re;
+  z.re += mr * v.re - mi * v.im;
+  z.im += mr * v.im + mi * v.re;
+}
+
+// The products of PB pairs for lmax <= 3, every source unrolled: fields once per
+// order m of the source, constants once for the PB pairs, the vectors' entries
+// from the row's lanes.
+template <typename T, int LMAX, int M, int L, int E, int PB>
+__device__ __forceinline__ void block_rows(const T* cf, const cplx<T>* const* frow, const int* start, cplx<T> (*f)[LMAX + 1],
+                                           cplx<T>* u, cplx<T>* v, cplx<T>* y, cplx<T>* z) {
+  constexpr int NQ = LMAX + 1, MEM = LMAX * (LMAX + 2), AM = M < 0 ? -M : M, L0 = AM > 1 ? AM : 1;
+  if constexpr (M <= LMAX) {
+    if constexpr (L == L0) {
+      const int s = start[M + LMAX];
+#pragma unroll
+      for (int k = 0; k < PB; ++k)
+#pragma unroll
+        for (int t = 0; t < NQ; ++t) f[k][t] = frow[k][s + t];
+    }
+    T c[NQ];
+#pragma unroll
+    for (int t = 0; t < NQ; ++t) c[t] = cf[(size_t)E * MEM * NQ + t];
+    // an order for the compiler: with every broadcast at the front they spill
+#pragma unroll
+    for (int k = 0; k < PB; ++k) {
+      asm volatile("" : "+v"(u[k].re), "+v"(u[k].im), "+v"(y[k].re), "+v"(y[k].im));
+      asm volatile("" : "+v"(v[k].re), "+v"(v[k].im), "+v"(z[k].re), "+v"(z[k].im));
+    }
+#pragma unroll
+    for (int k = 0; k < PB; ++k)
+      block_entry<T, NQ>(c, f[k], cplx<T>{row_bcast<E>(u[k].re), row_bcast<E>(u[k].im)},
+                         cplx<T>{row_bcast<E>(v[k].re), row_bcast<E>(v[k].im)}, y[k], z[k]);
+    constexpr bool LAST = L == LMAX;
+    constexpr int M1 = LAST ? M + 1 : M, A1 = M1 < 0 ? -M1 : M1, L1 = LAST ? (A1 > 1 ? A1 : 1) : L + 1;
+    block_rows<T, LMAX, M1, L1, E + 1, PB>(cf, frow, start, f, u, v, y, z);
+  }
+}
+
 // blockIdx.x: column (position of kx), blockIdx.y: (rhs, class).
-// Block products: S lanes per (ky, -ky) pair, lane i the target slot.
-template <typename T, int NG>
+// Block products: 64 / GROUPS lanes per (ky, -ky) pair, lane i < MEM the target.
+// Bound by LDS: forming an entry takes NQ constants and NQ fields.  So a lane works
+// on PB pairs with one load of the constants, fields are loaded once for all
+// sources of an order m, and at lmax <= 3 (a pair's lanes are one row of 16) the
+// vectors' entries come by DPP instead of LDS broadcasts.  The next pairs' symbol
+// is loaded during the current ones' products.  Whole kernel, one pair per lane and
+// the vectors by LDS -> so: 40x40 FP32 16 -> 11 us, 100x100 FP64 64 -> 40 (the
+// transforms alone take 9 and 21); operator of 17x16 at lmax 6, FP32, 78 -> 42 us.
+template <typename T, int LMAX, bool FULL>
 __global__ __launch_bounds__(512) void spec_columns(SpecArgs<T> a) {
-  constexpr int S = NG * SLOTS, NQ = SpecCfg<NG>::NQ, NF = SpecCfg<NG>::NF;
-  constexpr int GROUPS = NG == 1 ? 4 : NG == 2 ? 2 : 1;  // pairs a wave works on
+  using Cfg = SpecCfg<LMAX>;
+  using Lay = ColumnLds<T, LMAX, FULL>;
+  constexpr int S = Cfg::S, NQ = Cfg::NQ, MEM = Cfg::MEM, NF = Cfg::NF, GROUPS = Lay::GROUPS, PB = Lay::PB;
+  constexpr int GL = 64 / GROUPS, NL = (NF + GL - 1) / GL, NM = 2 * LMAX + 1;
   const int c = blockIdx.y & 1, r = blockIdx.y >> 1;
   const SpecJob job = a.col_jobs ? a.col_jobs[blockIdx.x] : SpecJob{0, (int)blockIdx.x};
   if (spec_skip(a, job.sub, r)) return;
-  const SpecSub<T> s = a.subs ? a.subs[job.sub] : a.one;
-  cplx<T>* sh = reinterpret_cast<cplx<T>*>(spec_lds);
-  cplx<T>* stage = sh + (size_t)s.Y.P * S;
+  const SpecSub<T> s = spec_subregion(a, job.sub);
   const int ny = s.Y.n, P = s.Y.P;
-  cplx<T>* W = a.W + s.w_off + ((size_t)(r * 2 + c) * s.X.P + job.index) * ny * S;
-  auto lds_st = [&](int p, int slot, cplx<T> v) { sh[p * S + slot] = v; };
-  auto lds_ld = [&](int p, int slot) { return sh[p * S + slot]; };
-  fft_forward<T, S>(
-      s.Y, s.twy, sh,
-      [&](int p, int slot) { return p < ny ? W[p * S + slot] : cplx<T>{(T)0, (T)0}; }, lds_st);
-  __syncthreads();
-  {
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int grp = GROUPS == 1 ? 0 : lane / S, i = GROUPS == 1 ? lane : lane % S;
-    const int pairs = P / 2 + 1;
-    cplx<T>* f = stage + (size_t)(wave * GROUPS + grp) * NF;
-    const int* info = a.slots[c].info;
-    const T* cf = a.coef + (size_t)c * S * S * NQ + (size_t)i * NQ;
-    const unsigned char* f0 = a.first + (size_t)c * S * S + i;
-    const cplx<T>* sym = s.sym + (size_t)job.index * pairs * a.nf;
-    const int members = a.members;
-    for (int m = wave * GROUPS + grp; m - grp < pairs; m += GROUPS * (blockDim.x >> 6)) {
-      const bool ok = m < pairs && i < S;
-      if (ok)
-        for (int q = i; q < NF; q += S) f[q] = q < a.nf ? sym[(size_t)m * a.nf + q] : cplx<T>{(T)0, (T)0};
-      // one wave wrote what it reads: LDS operations of a wave stay in order
-      __builtin_amdgcn_wave_barrier();
-      if (ok && i < members) {
-        const int p1 = s.pos[m], p2 = m ? s.pos[P - m] : p1;
-        const cplx<T>* u = sh + p1 * S;
-        const cplx<T>* v = sh + p2 * S;
-        T yr = 0, yi = 0, zr = 0, zi = 0;
-        for (int j = 0; j < members; ++j) {
-          const T* cj = cf + (size_t)j * S * NQ;
-          const cplx<T>* fj = f + f0[j * S];
-          T mr = 0, mi = 0;
+  const Lay lay(P, blockDim.x);
+  cplx<T>* sh = reinterpret_cast<cplx<T>*>(spec_lds);
+  unsigned short* lpos = reinterpret_cast<unsigned short*>(spec_lds + lay.pos);
+  cplx<T>* ltw = reinterpret_cast<cplx<T>*>(spec_lds + lay.tw);
+  T* lcoef = reinterpret_cast<T*>(spec_lds + lay.coef);
+  const unsigned short* pos = FULL ? lpos : s.pos;
+  const cplx<T>* tw = FULL ? ltw : s.twy;
+  const T* gcoef = a.coef + (size_t)c * MEM * MEM * NQ;
+  const int pairs = P / 2 + 1;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, grp = lane / GL, i = lane % GL;
+  const int ii = min(i, MEM - 1);  // lanes past the members compute along and write nothing
+  const int across = GROUPS * (blockDim.x >> 6), step = across * PB;
+  const cplx<T>* sym = s.sym + (size_t)job.index * pairs * a.nf;
+  cplx<T>* f = reinterpret_cast<cplx<T>*>(spec_lds + lay.sym) + (size_t)(wave * GROUPS + grp) * PB * NF;
+  const int m0 = wave * GROUPS + grp;
+  cplx<T> next[PB][NL];
+  auto fetch = [&](int m) {
 #pragma unroll
-          for (int q = 0; q < NQ; ++q) {
-            const T cq = cj[q];
-            mr += cq * fj[q].re;
-            mi += cq * fj[q].im;
-          }
-          const cplx<T> b = u[j];
-          yr += mr * b.re - mi * b.im;
-          yi += mr * b.im + mi * b.re;
-          cplx<T> d = v[info[j] & 255];
-          if (info[j] >> 8) d = cplx<T>{-d.re, -d.im};
-          zr += mr * d.re - mi * d.im;
-          zi += mr * d.im + mi * d.re;
-        }
-        sh[p1 * S + i] = cplx<T>{a.sgn * yr, a.sgn * yi};
-        const int own = info[i];
-        const T sz = (own >> 8) ? -a.sgn_mirror : a.sgn_mirror;
-        if (p2 != p1) sh[p2 * S + (own & 255)] = cplx<T>{sz * zr, sz * zi};
+    for (int k = 0; k < PB; ++k)
+#pragma unroll
+      for (int q = 0; q < NL; ++q) {
+        const int e = i + q * GL, mm = m + k * across;
+        next[k][q] = mm < pairs && e < Cfg::NFIELD ? sym[(size_t)mm * a.nf + e] : cplx<T>{(T)0, (T)0};
       }
-      __builtin_amdgcn_wave_barrier();
+  };
+  fetch(m0);
+  const int own = a.info[c * MEM + ii];
+  const int slot = own & 255, mirror = (own >> 8) & 255;
+  const T sz = (own >> 16) ? (T)-1 : (T)1;
+  int start[NM];
+#pragma unroll
+  for (int q = 0; q < NM; ++q) start[q] = a.start[q * MEM + ii];
+  if (FULL)
+    for (int q = threadIdx.x; q < P; q += blockDim.x) {
+      lpos[q] = s.pos[q];
+      ltw[q] = s.twy[q];
     }
+  if (FULL && Cfg::NG == 1)
+    for (int q = threadIdx.x; q < MEM * MEM * NQ; q += blockDim.x) lcoef[q] = gcoef[q];
+  cplx<T>* W = a.W + s.w_off + ((size_t)(r * 2 + c) * s.X.P + job.index) * ny * S;
+  auto lds_st = [&](int p, int sl, cplx<T> v) { sh[p * S + sl] = v; };
+  auto lds_ld = [&](int p, int sl) { return sh[p * S + sl]; };
+  fft_forward<T, S>(
+      s.Y, s.twy, tw, sh,
+      [&](int p, int sl) { return p < ny ? W[p * S + sl] : cplx<T>{(T)0, (T)0}; }, lds_st);
+  __syncthreads();
+  const T* cls = FULL && Cfg::NG == 1 ? lcoef : gcoef;
+  const T* cf = cls + (size_t)ii * NQ;
+  for (int m = m0; m - grp < pairs; m += step) {
+#pragma unroll
+    for (int k = 0; k < PB; ++k)
+#pragma unroll
+      for (int q = 0; q < NL; ++q)
+        if (i + q * GL < NF) f[k * NF + i + q * GL] = next[k][q];
+    fetch(m + step);
+    // one wave wrote what it reads: LDS operations of a wave stay in order
+    __builtin_amdgcn_wave_barrier();
+    int p1[PB], p2[PB];
+    cplx<T> y[PB], z[PB];
+#pragma unroll
+    for (int k = 0; k < PB; ++k) {
+      const int mm = min(m + k * across, pairs - 1);
+      p1[k] = pos[mm];
+      p2[k] = mm ? pos[P - mm] : p1[k];
+      y[k] = z[k] = cplx<T>{(T)0, (T)0};
+    }
+    if constexpr (Cfg::NG == 1) {
+      cplx<T> u[PB], v[PB], ft[PB][NQ];
+      const cplx<T>* frow[PB];
+#pragma unroll
+      for (int k = 0; k < PB; ++k) {
+        u[k] = sh[p1[k] * S + slot];
+        v[k] = sh[p2[k] * S + mirror];
+        v[k] = cplx<T>{sz * v[k].re, sz * v[k].im};
+        frow[k] = f + k * NF;
+      }
+      int o = ii * NQ;
+      asm volatile("" : "+v"(o));  // keeps the constants' loads in the loop: held, they spill
+      block_rows<T, LMAX, -LMAX, LMAX, 0, PB>(cls + o, frow, start, ft, u, v, y, z);
+    } else {
+      int e = 0;
+#pragma unroll
+      for (int mi = 0; mi < NM; ++mi) {
+        const int am = mi < LMAX ? LMAX - mi : mi - LMAX;
+        cplx<T> ft[PB][NQ];
+#pragma unroll
+        for (int k = 0; k < PB; ++k)
+#pragma unroll
+          for (int t = 0; t < NQ; ++t) ft[k][t] = f[k * NF + start[mi] + t];
+        const int e1 = e + LMAX - (am > 1 ? am : 1) + 1;
+#pragma unroll 2
+        for (; e < e1; ++e) {
+          T cq[NQ];
+#pragma unroll
+          for (int t = 0; t < NQ; ++t) cq[t] = cf[(size_t)e * MEM * NQ + t];
+          const int in = a.info[c * MEM + e];
+          const T sj = (in >> 16) ? (T)-1 : (T)1;
+#pragma unroll
+          for (int k = 0; k < PB; ++k) {
+            asm volatile("" : "+v"(y[k].re), "+v"(y[k].im), "+v"(z[k].re), "+v"(z[k].im));  // as in block_rows
+            const cplx<T> u = sh[p1[k] * S + (in & 255)], v = sh[p2[k] * S + ((in >> 8) & 255)];
+            block_entry<T, NQ>(cq, ft[k], u, cplx<T>{sj * v.re, sj * v.im}, y[k], z[k]);
+          }
+        }
+      }
+    }
+#pragma unroll
+    for (int k = 0; k < PB; ++k)
+      if (m + k * across < pairs && i < MEM) {
+        sh[p1[k] * S + slot] = cplx<T>{a.sgn * y[k].re, a.sgn * y[k].im};
+        const T g = sz * a.sgn_mirror;
+        if (p2[k] != p1[k]) sh[p2[k] * S + mirror] = cplx<T>{g * z[k].re, g * z[k].im};
+      }
+    __builtin_amdgcn_wave_barrier();
   }
   __syncthreads();
   fft_inverse<T, S>(
-      s.Y, s.twy, sh, lds_ld,
-      [&](int p, int slot, cplx<T> v) {
-        if (p < ny) W[p * S + slot] = v;
+      s.Y, tw, sh, lds_ld,
+      [&](int p, int sl, cplx<T> v) {
+        if (p < ny) W[p * S + sl] = v;
       });
 }
 
@@ -402,7 +572,7 @@ __global__ __launch_bounds__(256) void spec_back(SpecArgs<T> a) {
   const int g = blockIdx.y % a.NG, c = (blockIdx.y / a.NG) & 1, r = blockIdx.y / (2 * a.NG);
   const SpecJob job = a.row_jobs ? a.row_jobs[blockIdx.x] : SpecJob{0, (int)blockIdx.x};
   if (spec_skip(a, job.sub, r)) return;
-  const SpecSub<T> s = a.subs ? a.subs[job.sub] : a.one;
+  const SpecSub<T> s = spec_subregion(a, job.sub);
   cplx<T>* sh = reinterpret_cast<cplx<T>*>(spec_lds);
   const int S = a.S, n = s.X.n, N = n * s.Y.n;
   const size_t off = ((size_t)c * N + (size_t)job.index * n) * S + g * SLOTS;
@@ -477,7 +647,7 @@ __global__ __launch_bounds__(256) void spec_symbol_rows(SpecDim X, SpecDim Y, co
   }
   __syncthreads();
   auto lds_ld = [&](int p, int s) { return sh[p * SLOTS + s]; };
-  fft_forward<double, SLOTS>(X, tw, sh, lds_ld, [&](int p, int s, c128 v) {
+  fft_forward<double, SLOTS>(X, tw, tw, sh, lds_ld, [&](int p, int s, c128 v) {
     G[((size_t)p * Y.P + iy) * ldf + f0 + s] = v;
   });
 }
@@ -492,7 +662,7 @@ __global__ __launch_bounds__(256) void spec_symbol_columns(SpecDim X, SpecDim Y,
   const int p = blockIdx.x, f0 = blockIdx.y * SLOTS, pairs = Y.P / 2 + 1;
   const double scale = 1.0 / ((double)X.P * (double)Y.P);
   fft_forward<double, SLOTS>(
-      Y, tw, sh, [&](int q, int s) { return G[((size_t)p * Y.P + q) * ldf + f0 + s]; },
+      Y, tw, tw, sh, [&](int q, int s) { return G[((size_t)p * Y.P + q) * ldf + f0 + s]; },
       [&](int q, int s, c128 v) { sh[q * SLOTS + s] = v; });
   __syncthreads();
   for (int e = threadIdx.x; e < pairs * SLOTS; e += blockDim.x) {
@@ -510,22 +680,22 @@ namespace {
 
 const int kRadices[] = {16, 15, 12, 10, 8, 6, 5, 4, 3, 2};
 
-// Fewest stages (at least two) with radices of the set; 0 if there are none.
+// P as `depth` radices of the set, the most even ones (the least sum: a stage's
+// threads number P over its radix); the sum, 0 if there are none.
 int factor(int P, int depth, unsigned char* r) {
-  if (depth == 1) {
-    for (int v : kRadices)
-      if (v == P) {
-        r[0] = (unsigned char)v;
-        return 1;
-      }
-    return 0;
-  }
+  int best = 0;
   for (int v : kRadices) {
     if (P % v) continue;
-    r[0] = (unsigned char)v;
-    if (factor(P / v, depth - 1, r + 1)) return depth;
+    unsigned char rest[SPEC_STAGES] = {0};
+    const int sum = depth > 1 ? factor(P / v, depth - 1, rest) : (P == v ? 0 : -1);
+    if (sum < 0 || (depth > 1 && !sum)) continue;
+    if (!best || sum + v < best) {
+      best = sum + v;
+      r[0] = (unsigned char)v;
+      for (int q = 1; q < depth; ++q) r[q] = rest[q - 1];
+    }
   }
-  return 0;
+  return best;
 }
 
 }  // namespace
@@ -538,7 +708,7 @@ bool spec_dim(int n, SpecDim& d) {
   for (int P = std::max(4, 2 * n - 1); P <= SPEC_P_MAX && P < 3 * n + 8; ++P) {
     unsigned char r[SPEC_STAGES] = {0};
     int ns = 0;
-    for (int depth = 2; depth <= SPEC_STAGES && !ns; ++depth) ns = factor(P, depth, r);
+    for (int depth = 2; depth <= SPEC_STAGES && !ns; ++depth) ns = factor(P, depth, r) ? depth : 0;
     if (!ns) continue;
     const double cost = P * (1.0 + 0.15 * ns);
     if (cost < best) {
@@ -546,7 +716,8 @@ bool spec_dim(int n, SpecDim& d) {
       d.n = n;
       d.P = P;
       d.ns = ns;
-      for (int s = 0; s < SPEC_STAGES; ++s) d.r[s] = r[s];
+      d.rad = 0;
+      for (int s = 0; s < SPEC_STAGES; ++s) d.rad |= (unsigned)r[s] << (6 * s);
     }
   }
   return d.P > 0;
@@ -561,9 +732,9 @@ void spec_tables(const SpecDim& d, std::vector<c128>& tw, std::vector<unsigned s
     tw[k] = c128{(double)cosl(w * k), (double)-sinl(w * k)};
     int f = k, p = 0, len = d.P;
     for (int s = 0; s < d.ns; ++s) {
-      len /= d.r[s];
-      p += (f % d.r[s]) * len;
-      f /= d.r[s];
+      len /= d.r(s);
+      p += (f % d.r(s)) * len;
+      f /= d.r(s);
     }
     pos[k] = (unsigned short)p;
   }
@@ -571,14 +742,12 @@ void spec_tables(const SpecDim& d, std::vector<c128>& tw, std::vector<unsigned s
 
 namespace {
 
-// What depends on lmax alone: the scalar fields, and for A and A^T the real
-// constants [class][source j][target i][NQ] with the index of their first field.
+// What depends on lmax alone (see spec_const_layout).
 struct SpecConst {
-  int nf = 0, NQ = 0, S = 0, members = 0, qmax = 0;
+  int nf = 0, qmax = 0;
   std::vector<short2> fields;
   std::vector<double> coef[2];
-  std::vector<unsigned char> first[2];
-  SpecSlots slots[2];
+  std::vector<int> start[2], info;
   unsigned long long pmask[2] = {0, 0};
 };
 
@@ -588,84 +757,75 @@ const SpecConst& spec_constants(const Geometry& g) {
   std::lock_guard<std::mutex> lk(mu);
   SpecConst& k = cache[g.lmax];
   if (k.nf) return k;
-  const int S = g.S, Q = 2 * g.lmax + 1;
-  k.S = S;
-  k.qmax = 2 * g.lmax;
-  k.members = g.L / 2;
-  k.NQ = g.NG == 1 ? SpecCfg<1>::NQ : g.NG == 2 ? SpecCfg<2>::NQ : SpecCfg<3>::NQ;
+  const int lmax = g.lmax, Q = 2 * lmax + 1, S = g.S, mem = lmax * (lmax + 2), NQ = lmax + 1;
+  k.qmax = 2 * lmax;
   // fields in order of mu, then of q (steps of two)
-  std::vector<int> start(2 * k.qmax + 1, 0);
+  std::vector<int> first(2 * k.qmax + 1, 0);
   int nf = 0;
-  for (int mu_ = -k.qmax; mu_ <= k.qmax; ++mu_) {
-    start[mu_ + k.qmax] = nf;
-    for (int q = std::abs(mu_); q <= k.qmax; q += 2, ++nf) {
+  for (int m = -k.qmax; m <= k.qmax; ++m) {
+    first[m + k.qmax] = nf;
+    for (int q = std::abs(m); q <= k.qmax; q += 2, ++nf) {
       short2 f;
       f.x = (short)q;
-      f.y = (short)mu_;
+      f.y = (short)m;
       k.fields.push_back(f);
     }
   }
   std::vector<double> coef;
   std::vector<int> dm, sig;
   table_constants(g, Q, coef, dm, sig);
-  std::vector<int> pt(g.L), bar(g.L);
-  const int half = g.L / 2;
-  for (int n = 0; n < g.L; ++n) {
-    pt[n] = n / half;
-    const int rr = n % half;
-    int l = 1;
-    while ((l + 1) * (l + 1) - 1 <= rr) ++l;
-    const int m = rr - (l * (l + 1) - 1);
-    bar[n] = n - 2 * m;  // (l, -m, p)
-  }
+  // members by m, then l
+  std::vector<int> ml, mm;
+  for (int m = -lmax; m <= lmax; ++m)
+    for (int l = std::max(1, std::abs(m)); l <= lmax; ++l) {
+      ml.push_back(l);
+      mm.push_back(m);
+    }
+  std::vector<int> slot[2], type[2];
+  k.info.assign((size_t)NCLASS * mem, 0);
   for (int c = 0; c < NCLASS; ++c) {
-    for (int i = 0; i < S; ++i) {
-      const int n = g.n_of[c][i];
-      k.slots[c].info[i] = n < 0 ? i : g.slot_of[bar[n]] | (pt[n] << 8);
-      if (n >= 0 && pt[n]) k.pmask[c] |= 1ull << i;
+    for (int e = 0; e < mem; ++e) {
+      const int p = (((c - ml[e] - mm[e]) % 2) + 2) % 2;
+      auto at = [&](int m) { return g.slot_of[p * (g.L / 2) + ml[e] * (ml[e] + 1) - 1 + m]; };
+      slot[c].push_back(at(mm[e]));
+      type[c].push_back(p);
+      k.info[c * mem + e] = at(mm[e]) | (at(-mm[e]) << 8) | (p << 16);
+      if (p) k.pmask[c] |= 1ull << at(mm[e]);
     }
   }
   for (int tr = 0; tr < 2; ++tr) {
-    k.coef[tr].assign((size_t)NCLASS * S * S * k.NQ, 0.0);
-    k.first[tr].assign((size_t)NCLASS * S * S, 0);
+    k.coef[tr].assign((size_t)NCLASS * mem * mem * NQ, 0.0);
+    k.start[tr].assign((size_t)Q * mem, 0);
+    // A: order mu = m_j - m_i.  A^T at k is the transpose of M^(-k): mu = m_i - m_j
+    // with the sign (-1)^mu
+    for (int m = -lmax; m <= lmax; ++m)
+      for (int i = 0; i < mem; ++i) k.start[tr][(m + lmax) * mem + i] = first[(tr ? mm[i] - m : m - mm[i]) + k.qmax];
     for (int c = 0; c < NCLASS; ++c)
-      for (int i = 0; i < S; ++i)
-        for (int j = 0; j < S; ++j) {
-          if (g.n_of[c][i] < 0 || g.n_of[c][j] < 0) continue;
-          // A: C_ij on field mu = m_j - m_i.  A^T at k is the transpose of M^(-k): C_ji on
-          // field m_i - m_j with the sign (-1)^mu
-          const int ti = tr ? j : i, sj = tr ? i : j;
-          const int mu_ = dm[(c * S + ti) * S + sj];
-          const double sgn = (tr && (mu_ & 1)) ? -1.0 : 1.0;
-          const int pi = pt[g.n_of[c][i]], pj = pt[g.n_of[c][j]];
-          const double* cq = coef.data() + (((size_t)(c * S + ti) * S + sj) * Q) * 2;
-          int q0 = -1, terms = 0;
-          double* out = k.coef[tr].data() + ((size_t)(c * S + j) * S + i) * k.NQ;
-          for (int q = std::abs(mu_); q <= k.qmax; q += 2) {
-            const double re = cq[2 * q], im = cq[2 * q + 1];
-            if (re == 0.0 && im == 0.0 && q0 < 0) continue;
-            if (q0 < 0) q0 = q;
-            const int t = (q - q0) / 2;
-            // i^(p_i - p_j) C is real
-            const double v = pi == pj ? re : (pi < pj ? im : -im);
-            if (v != 0.0) terms = t + 1;
-            if (t < k.NQ) out[t] = sgn * v;
-          }
-          if (q0 < 0) q0 = std::abs(mu_);
-          if (terms > k.NQ) k.nf = -1;  // not reached: at most lmax + 1 terms
-          k.first[tr][(size_t)(c * S + j) * S + i] =
-              (unsigned char)(start[mu_ + k.qmax] + (q0 - std::abs(mu_)) / 2);
+      for (int j = 0; j < mem; ++j)
+        for (int i = 0; i < mem; ++i) {
+          const int si = slot[c][i], sj = slot[c][j], ti = tr ? sj : si, tj = tr ? si : sj;
+          const int mu = tr ? mm[i] - mm[j] : mm[j] - mm[i], pi = type[c][i], pj = type[c][j];
+          const double sgn = (tr && (mu & 1)) ? -1.0 : 1.0;
+          const double* cq = coef.data() + (((size_t)(c * S + ti) * S + tj) * Q) * 2;
+          double* out = k.coef[tr].data() + ((size_t)(c * mem + j) * mem + i) * NQ;
+          for (int q = std::abs(mu), t = 0; q <= k.qmax; q += 2, ++t)  // i^(p_i - p_j) C is real
+            out[t] = sgn * (pi == pj ? cq[2 * q] : (pi < pj ? cq[2 * q + 1] : -cq[2 * q + 1]));
         }
   }
   k.nf = nf;
   return k;
 }
 
-template <typename T>
-size_t columns_lds(const SpecDim& Y, int S, int NG, int threads) {
-  const int groups = (threads / 64) * (NG == 1 ? 4 : NG == 2 ? 2 : 1);
-  const int NF = NG == 1 ? SpecCfg<1>::NF : NG == 2 ? SpecCfg<2>::NF : SpecCfg<3>::NF;
-  return ((size_t)Y.P * S + (size_t)groups * NF) * sizeof(cplx<T>);
+template <typename T, bool FULL>
+size_t columns_lds(int P, int lmax, int threads) {
+  switch (lmax) {
+    case 1: return ColumnLds<T, 1, FULL>(P, threads).bytes;
+    case 2: return ColumnLds<T, 2, FULL>(P, threads).bytes;
+    case 3: return ColumnLds<T, 3, FULL>(P, threads).bytes;
+    case 4: return ColumnLds<T, 4, FULL>(P, threads).bytes;
+    case 5: return ColumnLds<T, 5, FULL>(P, threads).bytes;
+    default: return ColumnLds<T, 6, FULL>(P, threads).bytes;
+  }
 }
 size_t align256(size_t b) { return (b + 255) & ~(size_t)255; }
 
@@ -679,9 +839,9 @@ size_t spec_w_elems(const SpecDim& X, const SpecDim& Y, int S) {
 template <typename T>
 bool spec_fits(const Geometry& g, int nx, int ny, SpecDim& X, SpecDim& Y) {
   if (!g.lattice || !spec_dim(nx, X) || !spec_dim(ny, Y)) return false;
+  // (the symbol's transforms are FP64)
   return (size_t)X.P * SLOTS * sizeof(c128) <= SPEC_LDS_MAX &&
-         (size_t)Y.P * SLOTS * sizeof(c128) <= SPEC_LDS_MAX &&
-         columns_lds<T>(Y, g.S, g.NG, 256) <= SPEC_LDS_MAX;
+         (size_t)Y.P * SLOTS * sizeof(c128) <= SPEC_LDS_MAX && columns_lds<T, false>(Y.P, g.lmax, 256) <= SPEC_LDS_MAX;
 }
 template bool spec_fits<float>(const Geometry&, int, int, SpecDim&, SpecDim&);
 template bool spec_fits<double>(const Geometry&, int, int, SpecDim&, SpecDim&);
@@ -706,18 +866,14 @@ static int allow_lds(tm_ctx* c, const void* f, size_t bytes) {
 static int spec_upload_constants(tm_ctx* c) {
   if (c->spec_const_lmax == c->g.lmax) return TM_OK;
   const SpecConst& k = spec_constants(c->g);
-  const size_t nc = k.coef[0].size(), nb = k.first[0].size();
-  SpecConstLayout L = spec_const_layout(k.S, k.NQ, (int)k.fields.size());
+  const SpecConstLayout L = spec_const_layout(c->g.lmax);
   std::vector<unsigned char> h(L.bytes, 0);
   for (int tr = 0; tr < 2; ++tr) {
-    double* d = reinterpret_cast<double*>(h.data() + L.coef64[tr]);
-    float* f = reinterpret_cast<float*>(h.data() + L.coef32[tr]);
-    for (size_t e = 0; e < nc; ++e) {
-      d[e] = k.coef[tr][e];
-      f[e] = (float)k.coef[tr][e];
-    }
-    std::copy(k.first[tr].begin(), k.first[tr].begin() + nb, h.begin() + L.first[tr]);
+    std::copy(k.coef[tr].begin(), k.coef[tr].end(), reinterpret_cast<double*>(h.data() + L.coef64[tr]));
+    std::copy(k.coef[tr].begin(), k.coef[tr].end(), reinterpret_cast<float*>(h.data() + L.coef32[tr]));
+    std::copy(k.start[tr].begin(), k.start[tr].end(), reinterpret_cast<int*>(h.data() + L.start[tr]));
   }
+  std::copy(k.info.begin(), k.info.end(), reinterpret_cast<int*>(h.data() + L.info));
   std::copy(k.fields.begin(), k.fields.end(), reinterpret_cast<short2*>(h.data() + L.fields));
   int rc;
   if ((rc = ensure(c, c->spec_const, L.bytes)) != TM_OK) return rc;
@@ -747,7 +903,7 @@ static int spec_symbol(tm_ctx* c, const SpecPlan& pl, int axis, void* tmp, c128*
   const SpecConst& k = spec_constants(g);
   const SpecDim &X = pl.X, &Y = pl.Y;
   const int nf = k.nf, groups = (nf + SLOTS - 1) / SLOTS, ldf = groups * SLOTS;
-  const SpecConstLayout L = spec_const_layout(k.S, k.NQ, nf);
+  const SpecConstLayout L = spec_const_layout(g.lmax);
   const short2* fields = (const short2*)((char*)c->spec_const.p + L.fields);
   const size_t lx = (size_t)X.P * SLOTS * sizeof(c128), ly = (size_t)Y.P * SLOTS * sizeof(c128);
   int rc;
@@ -840,19 +996,17 @@ template SpecSub<double> spec_sub<double>(const SpecPlan&);
 template <typename T>
 void spec_fill_args(tm_ctx* c, bool transposed, SpecArgs<T>& a) {
   const SpecConst& k = spec_constants(c->g);
-  const SpecConstLayout L = spec_const_layout(k.S, k.NQ, k.nf);
+  const SpecConstLayout L = spec_const_layout(c->g.lmax);
   char* b = (char*)c->spec_const.p;
   a.coef = (const T*)(b + (std::is_same<T, double>::value ? L.coef64[transposed] : L.coef32[transposed]));
-  a.first = (const unsigned char*)(b + L.first[transposed]);
+  a.start = (const int*)(b + L.start[transposed]);
+  a.info = (const int*)(b + L.info);
   a.S = c->g.S;
   a.NG = c->g.NG;
   a.nf = k.nf;
-  a.members = k.members;
+  a.lmax = c->g.lmax;
   a.sgn = a.sgn_mirror = 1;
-  for (int q = 0; q < NCLASS; ++q) {
-    a.slots[q] = k.slots[q];
-    a.pmask[q] = k.pmask[q];
-  }
+  for (int q = 0; q < NCLASS; ++q) a.pmask[q] = k.pmask[q];
 }
 template void spec_fill_args<float>(tm_ctx*, bool, SpecArgs<float>&);
 template void spec_fill_args<double>(tm_ctx*, bool, SpecArgs<double>&);
@@ -862,15 +1016,24 @@ template void spec_fill_args<double>(tm_ctx*, bool, SpecArgs<double>&);
 template <typename T>
 int spec_launch(tm_ctx* c, const SpecArgs<T>& a, Op op, int rows, int columns, int Pxmax, const SpecDim& Ymax) {
   const size_t lx = (size_t)Pxmax * SLOTS * sizeof(cplx<T>);
-  // longer columns get more waves (one workgroup per CU then)
-  int threads = Ymax.P * a.S * (int)sizeof(cplx<T>) > 80 * 1024 ? 512 : 256;
-  if (columns_lds<T>(Ymax, a.S, a.NG, threads) > SPEC_LDS_MAX) threads = 256;
-  const size_t ly = columns_lds<T>(Ymax, a.S, a.NG, threads);
+  // a column with many pairs, or whose LDS leaves one workgroup per CU, gets eight waves
+  // 512 threads where a CU has one workgroup (few of them, or a column of half its
+  // LDS) or the products outweigh the transforms (lmax > 3; 17x16 lmax 6 FP32 33 ->
+  // 24 us).  Else 256 for short columns, and in FP64, whose registers leave room
+  // for 12 waves a CU (100x100 FP64: 45 us with 512, 40 with 256; FP32 62 with 256,
+  // 57 with 512).
+  const bool one = columns * 2 * a.R <= 256 || Ymax.P * a.S * (int)sizeof(cplx<T>) > 80 * 1024 || a.NG > 1;
+  int threads = one || (sizeof(T) == 4 && Ymax.P * a.S > 1200) ? 512 : 256;
+  if (columns_lds<T, true>(Ymax.P, a.lmax, threads) > SPEC_LDS_MAX) threads = 256;
+  const bool full = columns_lds<T, true>(Ymax.P, a.lmax, threads) <= SPEC_LDS_MAX;
+  const size_t ly = full ? columns_lds<T, true>(Ymax.P, a.lmax, threads) : columns_lds<T, false>(Ymax.P, a.lmax, threads);
   const dim3 gr(rows, 2 * a.NG * a.R), gc(columns, 2 * a.R);
   int rc;
   const void* kr = op == Op::Adjoint ? (const void*)spec_rows<T, true> : (const void*)spec_rows<T, false>;
-  const void* kc = a.NG == 1 ? (const void*)spec_columns<T, 1>
-                   : a.NG == 2 ? (const void*)spec_columns<T, 2> : (const void*)spec_columns<T, 3>;
+#define SPEC_COLUMNS(LM) {(const void*)spec_columns<T, LM, false>, (const void*)spec_columns<T, LM, true>}
+  const void* const kcs[6][2] = {SPEC_COLUMNS(1), SPEC_COLUMNS(2), SPEC_COLUMNS(3), SPEC_COLUMNS(4), SPEC_COLUMNS(5), SPEC_COLUMNS(6)};
+#undef SPEC_COLUMNS
+  const void* kc = kcs[a.lmax - 1][full];
   const void* kb = op == Op::Forward   ? (const void*)spec_back<T, SPEC_FORWARD>
                    : op == Op::Adjoint ? (const void*)spec_back<T, SPEC_MINUS> : (const void*)spec_back<T, SPEC_PLAIN>;
   if ((rc = allow_lds(c, kr, lx)) != TM_OK || (rc = allow_lds(c, kc, ly)) != TM_OK ||
