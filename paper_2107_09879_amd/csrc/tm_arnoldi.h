@@ -24,12 +24,14 @@ struct Kry {
   const int *dof, *uof;  // first block of every system [nsys + 1]
   c128 *V, *w;
   long long stride;  // elements of a packed vector
-  c128* part;        // dot partial sums [dot block][m]
-  double* npart;     // norm partial sums [update block]
-  c128 *h1, *h2, *R, *cs, *sn, *g, *y;  // [nsys][m], R [nsys][column][m], g [nsys][m + 1]
-  double *beta, *target;
-  int *jend, *active, *live, *limit, *ctl;
-  int nsys, m;
+  double *part, *sums;  // dot sums: [dot block][group][set, vector, re/im], [nsys][set][m + 1] complex
+  double* npart;        // norm partial sums [update block]
+  // Hessenberg columns H [nsys][column][m + 1], rotated R [nsys][column][m], the
+  // next column t and the rotated right-hand side g [nsys][m + 1], cs, y [nsys][m]
+  c128 *H, *R, *t, *g, *cs, *y;
+  double *sn, *beta, *target;
+  int *jend, *active, *live, *limit, *ctl, *arrived;  // arrived: dot blocks [nsys][group]
+  int nsys, m, ngroup;
   // pinned host memory: read once a cycle (kry_begin), written by the kernels
   int *h_ctl, *h_jend, *h_bad, *h_live, *h_limit;
   double *h_beta, *h_target, *h_est;

@@ -1,24 +1,25 @@
 // Restarted GMRES (App. I, App. I.D) over several independent systems at once.
 //
-// An Arnoldi step is the product and five launches over all systems:
-//   kry_dots     h1 = V^H w, partial sums per block
-//   kry_update   w -= V h1 (every block adds up its system's partial sums itself)
-//   kry_dots     h2 = V^H w
-//   kry_update   w -= V h2, partial sums of |w|^2
-//   kry_finish   v_next = w / |w|; one block per system rotates the Hessenberg
-//                column (Givens), tests convergence and reports the step
-// (classical Gram-Schmidt with one re-orthogonalisation, FP64).  At the sizes
-// of subregions a step is bound by the launches' latency, not by bytes: the
-// previous form had ten launches after the product (separate reductions, norm,
-// rotation, scaling; the rotation alone 9-24 us through global memory, the back
-// substitution of a cycle 550 us on one thread) and ran to the end of a cycle
-// after it had converged.  The kernels report steps and convergence in pinned
-// host memory; the host stays at most KRY_AHEAD steps ahead and ends the cycle
-// when it sees the flag, so a stopped cycle costs a few empty launches.
-// Several right-hand sides share the launches.  Solves to 1e-12 before -> after:
-// 8x8 at lmax 2 FP64 7.0 -> 5.2 ms, 37x53 at lmax 3 mixed with two right-hand sides
-// 97 -> 57 ms, six subregions of 14 to 36 sites with two (their vectors had 60
-// workgroups for every reduction) 365 -> 54 ms with the transformed product.
+// An Arnoldi step is the product and two launches over all systems.  Classical
+// Gram-Schmidt with one re-orthogonalisation (FP64), the second pass put off into
+// the next step (delayed re-orthogonalisation as in Bielich et al. 2022, DCGS2), so
+// that V is read twice and not four times:
+//   product      w = A u_j, u_j orthogonal to q_0 .. q_{j-1} but for a first pass
+//   kry_dots     s = Q^H u, z = Q^H w, |u|^2, u^H w
+//   kry_update   alpha = (|u|^2 - |s|^2)^(1/2), q_j = (u - Q s) / alpha,
+//                u_{j+1} = (w - Q z - q_j (q_j^H w)) / alpha;
+//                one block per system meanwhile completes Hessenberg column j - 1
+//                (its first pass + s, alpha below), rotates it (Givens), tests
+//                convergence and reports the step
+// A system so needs one product and one kry_dots more than it has steps.
+// The kernels report steps and convergence in pinned host memory; the host stays
+// at most KRY_AHEAD steps ahead and ends the cycle when it sees the flag, so a
+// stopped cycle costs a few empty launches.  Several right-hand sides share the
+// launches.
+// Solves to 1e-12 with ten launches a step that ran to the cycle's end -> with both
+// passes in the step, five launches -> so: 8x8 at lmax 2 FP64 7.0 -> 5.3 -> 3.1 ms, 37x53
+// at lmax 3 mixed with two right-hand sides 97 -> 50 -> 28 ms, 150x150 8.1 -> 4.8 ms, six
+// subregions of 14 to 36 sites with two 365 (block products) -> 47 -> 28 ms.
 //
 // Every sum has a fixed order: results are reproducible run to run.
 #include "tm_arnoldi.h"
@@ -70,119 +71,97 @@ __device__ inline c128 zmul(c128 a, c128 b) { return c128{a.re * b.re - a.im * b
 __device__ inline c128 zmulc(c128 a, c128 b) { return c128{a.re * b.re + a.im * b.im, a.re * b.im - a.im * b.re}; }
 __device__ inline double zabs(c128 a) { return hypot(a.re, a.im); }
 
-// part[block][k] = sum over the block's elements of conj(V_k) w for the KC
-// vectors of blockIdx.y: V is read once, the reductions come once at the end.
-__global__ __launch_bounds__(KT) void kry_dots(Kry k, int nvec) {
-  if (k.ctl[KRY_DONE]) return;
-  const KrySeg sg = dot_seg(k, blockIdx.x);
-  if (!k.active[sg.sys]) return;
-  __shared__ double sh[KT / 64][2 * KC];
-  const int wv = threadIdx.x >> 6, ln = threadIdx.x & 63;
-  const int k0 = blockIdx.y * KC, nk = min(KC, nvec - k0);
-  const c128* Vk = k.V + (size_t)k0 * k.stride;
-  double sr[KC], si[KC];
+// Sums of 2^n values over the wave: half of them change lanes at every step, lane
+// 2 i ends up with value i (32 shuffles for 32 values where one by one takes 192).
+template <int N, int O = 32>
+__device__ __forceinline__ double wave_sums(double* v, int ln) {
+  if constexpr (N > 1) {
+    const bool up = ln & O;
 #pragma unroll
-  for (int i = 0; i < KC; ++i) sr[i] = si[i] = 0.0;
-  if (nk == KC) {
-#pragma unroll 2
-    for (long long e = sg.lo + threadIdx.x; e < sg.hi; e += KT) {
-      const c128 b = k.w[e];
-#pragma unroll
-      for (int i = 0; i < KC; ++i) {
-        const c128 a = Vk[(size_t)i * k.stride + e];
-        sr[i] += a.re * b.re + a.im * b.im;
-        si[i] += a.re * b.im - a.im * b.re;
-      }
+    for (int i = 0; i < N / 2; ++i) {
+      const double send = up ? v[i] : v[i + N / 2], keep = up ? v[i + N / 2] : v[i];
+      v[i] = keep + __shfl_xor(send, O, 64);
     }
+    return wave_sums<N / 2, O / 2>(v, ln);
   } else {
-    for (long long e = sg.lo + threadIdx.x; e < sg.hi; e += KT) {
-      const c128 b = k.w[e];
-#pragma unroll
-      for (int i = 0; i < KC; ++i) {
-        if (i < nk) {
-          const c128 a = Vk[(size_t)i * k.stride + e];
-          sr[i] += a.re * b.re + a.im * b.im;
-          si[i] += a.re * b.im - a.im * b.re;
-        }
-      }
-    }
-  }
-#pragma unroll
-  for (int i = 0; i < KC; ++i) {
-    const double r = wave_sum(sr[i]), m = wave_sum(si[i]);
-    if (ln == 0) {
-      sh[wv][2 * i] = r;
-      sh[wv][2 * i + 1] = m;
-    }
-  }
-  __syncthreads();
-  if (threadIdx.x < 2 * nk) {
-    double s = 0.0;
-    for (int q = 0; q < KT / 64; ++q) s += sh[q][threadIdx.x];
-    reinterpret_cast<double*>(k.part + (size_t)blockIdx.x * k.m + k0)[threadIdx.x] = s;
+    return v[0] + __shfl_xor(v[0], O, 64);
   }
 }
 
-// w -= V h with h the sum of the system's dot partials; LAST: also the partial
-// sums of |w|^2.  LDS: nvec + 256 complex.
-template <bool LAST>
-__global__ __launch_bounds__(KT) void kry_update(Kry k, int nvec) {
-  if (k.ctl[KRY_DONE]) return;
-  const KrySeg sg = upd_seg(k, blockIdx.x);
+// Step j: V_k^H u (set 0) and V_k^H w (set 1) for k <= j, u = V_j.  blockIdx.y: KC
+// vectors; a system's last block adds up the partial sums.
+// Bound by the reads of V where the basis is large, else by latency: the block's
+// reduction and the last block's reads.
+template <bool W>
+__global__ __launch_bounds__(KT) void kry_dots(Kry k, int j) {
+  const KrySeg sg = dot_seg(k, blockIdx.x);
   if (!k.active[sg.sys]) return;
-  extern __shared__ __align__(16) unsigned char kry_lds[];
-  c128* h = reinterpret_cast<c128*>(kry_lds);
-  c128* quart = h + nvec;
+  __shared__ double sh[KT / 64][32];
+  __shared__ double rows[KT / 32][32];
+  __shared__ int last;
   const int wv = threadIdx.x >> 6, ln = threadIdx.x & 63;
-  const int r0 = dot_first(k, sg.sys), r1 = dot_first(k, sg.sys + 1);
-  // 64 columns at a time: wave q adds the rows q, q + 4, ...
-  for (int c0 = 0; c0 < nvec; c0 += 64) {
-    const int col = c0 + ln;
-    c128 s{0.0, 0.0};
-    if (col < nvec) {
-#pragma unroll 8
-      for (int r = r0 + wv; r < r1; r += KT / 64) {
-        const c128 v = k.part[(size_t)r * k.m + col];
-        s.re += v.re;
-        s.im += v.im;
-      }
-    }
-    quart[threadIdx.x] = s;
-    __syncthreads();
-    if (wv == 0 && col < nvec) {
+  const int k0 = blockIdx.y * KC, nk = min(KC, j + 1 - k0);
+  const c128* Vk = k.V + (size_t)k0 * k.stride;
+  const c128* u = k.V + (size_t)j * k.stride;
+  double s[4 * KC];  // [set][vector][re, im]
 #pragma unroll
-      for (int q = 1; q < KT / 64; ++q) {
-        s.re += quart[q * 64 + ln].re;
-        s.im += quart[q * 64 + ln].im;
-      }
-      h[col] = s;
+  for (int i = 0; i < 4 * KC; ++i) s[i] = 0.0;
+  auto add = [&](int i, c128 a, c128 p, c128 q) {
+    s[2 * i] += a.re * p.re + a.im * p.im;
+    s[2 * i + 1] += a.re * p.im - a.im * p.re;
+    if (W) {
+      s[2 * (KC + i)] += a.re * q.re + a.im * q.im;
+      s[2 * (KC + i) + 1] += a.re * q.im - a.im * q.re;
+    }
+  };
+  // a group's missing vectors: its last one again, from the L1, not summed up
+  size_t off[KC];
+#pragma unroll
+  for (int i = 0; i < KC; ++i) off[i] = (size_t)min(i, nk - 1) * k.stride;
+#pragma unroll 2
+  for (long long e = sg.lo + threadIdx.x; e < sg.hi; e += KT) {
+    const c128 p = u[e], q = W ? k.w[e] : c128{0.0, 0.0};
+#pragma unroll
+    for (int i = 0; i < KC; ++i) add(i, Vk[off[i] + e], p, q);
+  }
+  const double r = wave_sums<32>(s, ln);
+  if (!(ln & 1)) sh[wv][ln >> 1] = r;
+  __syncthreads();
+  const int b0 = dot_first(k, sg.sys), b1 = dot_first(k, sg.sys + 1), m1 = k.m + 1;
+  double* out = k.sums + (size_t)sg.sys * 4 * m1;
+  double t = 0.0;
+  if (threadIdx.x < 32)
+    for (int q = 0; q < KT / 64; ++q) t += sh[q][threadIdx.x];
+  if (b1 - b0 > 1) {
+    double* part = k.part + (size_t)blockIdx.y * 32;
+    const size_t ld = (size_t)k.ngroup * 32;
+    int* arrived = k.arrived + (size_t)sg.sys * k.ngroup + blockIdx.y;
+    // Written through the L2 and waited for before the block counts itself, and read
+    // past the L2: a device-wide fence here writes the whole L2 back, in every block
+    // (37x53 with two right-hand sides: 127 us; so 32, with 1024 blocks 24).
+    if (wv == 0) {
+      if (ln < 32) __hip_atomic_store(&part[blockIdx.x * ld + ln], t, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      __builtin_amdgcn_s_waitcnt(0);
+      asm volatile("" ::: "memory");
+      if (ln == 0)
+        last = __hip_atomic_fetch_add(arrived, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == b1 - b0 - 1;
     }
     __syncthreads();
-  }
-  if ((int)blockIdx.x == upd_first(k, sg.sys)) {
-    c128* out = (LAST ? k.h2 : k.h1) + (size_t)sg.sys * k.m;
-    for (int q = threadIdx.x; q < nvec; q += KT) out[q] = h[q];
-  }
-  double nrm = 0.0;
-  for (long long e = sg.lo + threadIdx.x; e < sg.hi; e += KT) {
-    double sr = 0.0, si = 0.0;
+    if (!last) return;
+    const int col = threadIdx.x & 31, row = threadIdx.x >> 5;
+    double v = 0.0;
 #pragma unroll 8
-    for (int q = 0; q < nvec; ++q) {
-      const c128 v = k.V[(size_t)q * k.stride + e], c = h[q];
-      sr += v.re * c.re - v.im * c.im;
-      si += v.re * c.im + v.im * c.re;
-    }
-    c128 o = k.w[e];
-    o.re -= sr;
-    o.im -= si;
-    k.w[e] = o;
-    nrm += o.re * o.re + o.im * o.im;
+    for (int q = b0 + row; q < b1; q += KT / 32)
+      v += __hip_atomic_load(&part[q * ld + col], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    rows[row][col] = v;
+    __syncthreads();
+    t = 0.0;
+    if (threadIdx.x < 32)
+      for (int q = 0; q < KT / 32; ++q) t += rows[q][threadIdx.x];
+    if (threadIdx.x == 0) *arrived = 0;
   }
-  if (LAST) {
-    __shared__ double sh[KT / 64];
-    nrm = block_sum(nrm, sh);
-    if (threadIdx.x == 0) k.npart[blockIdx.x] = nrm;
-  }
+  const int set = threadIdx.x >> 4, i = (threadIdx.x & 15) >> 1;
+  if (threadIdx.x < 32 && i < nk) out[((size_t)set * m1 + k0 + i) * 2 + (threadIdx.x & 1)] = t;
 }
 
 __device__ inline double system_norm(const Kry& k, int s, double* sh) {
@@ -191,32 +170,55 @@ __device__ inline double system_norm(const Kry& k, int s, double* sh) {
   return sqrt(block_sum(t, sh));
 }
 
-// Column j of the Hessenberg matrix h1 + h2 with |w| = hn below it: the earlier
-// rotations, a new one, the residual estimate.  First wave of the block; the
-// rotations are a serial chain, 64 of them at a time in LDS.
-__device__ inline void kry_rotate(const Kry& k, int s, int j, double hn, c128 (*sh)[64]) {
+// The step's scalars from its sums, alike in every wave: alpha = |u - Q s|, and the
+// component of w along the new q_j.
+struct KryStep {
+  double alpha, f;
+  c128 zeta;
+};
+__device__ inline KryStep step_scalars(const c128* s, const c128* z, int j) {
+  const int ln = threadIdx.x & 63;
+  double n2 = 0.0, pr = 0.0, pi = 0.0;
+  for (int q = ln; q < j; q += 64) {
+    const c128 a = s[q], b = z[q];
+    n2 += a.re * a.re + a.im * a.im;
+    pr += a.re * b.re + a.im * b.im;
+    pi += a.re * b.im - a.im * b.re;
+  }
+  n2 = wave_sum(n2);
+  pr = wave_sum(pr);
+  pi = wave_sum(pi);
+  const double a2 = s[j].re - n2;
+  KryStep r;
+  r.alpha = a2 > 0.0 ? sqrt(a2) : (a2 <= 0.0 ? 0.0 : a2);  // NaN stays
+  r.f = r.alpha > 0.0 ? 1.0 / r.alpha : 0.0;
+  r.zeta = c128{r.f * (z[j].re - pr), r.f * (z[j].im - pi)};
+  return r;
+}
+
+// Column c of the Hessenberg matrix, col[0 .. c] with hn below it: the earlier
+// rotations, a new one, the residual estimate.  One wave; the rotations are a
+// serial chain, 64 of them at a time in LDS, the first 128 loaded ahead (pc, ps).
+__device__ inline void kry_rotate(const Kry& k, int s, int c, double hn, const c128* col, c128 pc0,
+                                  c128 pc1, double ps0, double ps1, c128 (*sh)[64], double* shs) {
   const int ln = threadIdx.x & 63;
   const size_t o = (size_t)s * k.m;
-  c128* R = k.R + o * k.m + (size_t)j * k.m;
-  auto column = [&](int i) {
-    const c128 a = k.h1[o + i], b = k.h2[o + i];
-    return c128{a.re + b.re, a.im + b.im};
-  };
-  c128 a = column(0);
-  for (int c0 = 0; c0 < j; c0 += 64) {
-    const int n = min(64, j - c0);
+  c128* R = k.R + o * k.m + (size_t)c * k.m;
+  c128 a = col[0];
+  for (int c0 = 0; c0 < c; c0 += 64) {
+    const int n = min(64, c - c0);
     if (ln < n) {
-      sh[0][ln] = column(c0 + ln + 1);
-      sh[1][ln] = k.cs[o + c0 + ln];
-      sh[2][ln] = k.sn[o + c0 + ln];
+      sh[1][ln] = c0 == 0 ? pc0 : c0 == 64 ? pc1 : k.cs[o + c0 + ln];
+      shs[ln] = c0 == 0 ? ps0 : c0 == 64 ? ps1 : k.sn[o + c0 + ln];
     }
     __builtin_amdgcn_wave_barrier();
 #pragma unroll 4
     for (int t = 0; t < n; ++t) {
-      const c128 b = sh[0][t], c = sh[1][t], sn = sh[2][t];
-      const c128 u = zmulc(c, a), v = zmulc(sn, b), x = zmul(c, b), y = zmul(sn, a);
-      if (ln == 0) sh[0][t] = c128{u.re + v.re, u.im + v.im};
-      a = c128{x.re - y.re, x.im - y.im};
+      const c128 b = col[c0 + t + 1], cs = sh[1][t];
+      const double sn = shs[t];
+      const c128 u = zmulc(cs, a), x = zmul(cs, b);
+      if (ln == 0) sh[0][t] = c128{u.re + sn * b.re, u.im + sn * b.im};
+      a = c128{x.re - sn * a.re, x.im - sn * a.im};
     }
     __builtin_amdgcn_wave_barrier();
     if (ln < n) R[c0 + ln] = sh[0][ln];
@@ -224,72 +226,208 @@ __device__ inline void kry_rotate(const Kry& k, int s, int j, double hn, c128 (*
   }
   if (ln) return;
   const double den = hypot(zabs(a), hn);
-  c128 c{1.0, 0.0}, sn{0.0, 0.0};
+  c128 cs{1.0, 0.0};
+  double sn = 0.0;
   if (den != 0.0) {
-    c = c128{a.re / den, a.im / den};
-    sn = c128{hn / den, 0.0};
+    cs = c128{a.re / den, a.im / den};
+    sn = hn / den;
   }
-  k.cs[o + j] = c;
-  k.sn[o + j] = sn;
-  R[j] = c128{den, 0.0};
+  k.cs[o + c] = cs;
+  k.sn[o + c] = sn;
+  R[c] = c128{den, 0.0};
   c128* g = k.g + (size_t)s * (k.m + 1);
-  const c128 gj = g[j], gn = zmul(sn, gj);
-  g[j + 1] = c128{-gn.re, -gn.im};
-  g[j] = zmulc(c, gj);
-  const double est = zabs(gn);
-  k.jend[s] = j + 1;
+  const c128 gc = g[c];
+  g[c + 1] = c128{-sn * gc.re, -sn * gc.im};
+  g[c] = zmulc(cs, gc);
+  const double est = zabs(g[c + 1]);
+  k.jend[s] = c + 1;
   k.h_est[s] = est;
   const bool bad = !isfinite(est);
   if (bad) k.h_bad[s] = 1;
-  if (est <= k.target[s] || hn == 0.0 || bad || j + 1 >= k.limit[s]) {
+  if (est <= k.target[s] || hn == 0.0 || bad || c + 1 >= k.limit[s]) {
     k.active[s] = 0;
     atomicSub(&k.ctl[KRY_ACTIVE], 1);
   }
 }
 
-__global__ __launch_bounds__(KT) void kry_finish(Kry k, int j) {
-  if (k.ctl[KRY_DONE]) return;
-  const KrySeg sg = upd_seg(k, blockIdx.x);
-  const bool first = (int)blockIdx.x == upd_first(k, sg.sys);
-  __shared__ double sh[KT / 64];
-  __shared__ c128 rot[3][64];
-  // the first block clears the flag when the system stops: its other blocks may
-  // or may not see that, and v_next is not used then
-  const bool active = k.active[sg.sys] != 0;
-  if (active) {
-    const double hn = system_norm(k, sg.sys, sh);
-    const double f = hn > 0.0 ? 1.0 / hn : 0.0;
-    c128* v = k.V + (size_t)(j + 1) * k.stride;
-    for (long long e = sg.lo + threadIdx.x; e < sg.hi; e += KT) {
-      const c128 x = k.w[e];
-      v[e] = c128{f * x.re, f * x.im};
-    }
-    if (first && threadIdx.x < 64) {
-      if (isfinite(hn)) {
-        kry_rotate(k, sg.sys, j, hn, rot);
-      } else if (threadIdx.x == 0) {  // jend stays: the earlier columns are finite
-        k.h_bad[sg.sys] = 1;
-        k.active[sg.sys] = 0;
-        atomicSub(&k.ctl[KRY_ACTIVE], 1);
+constexpr int KH = 256;  // rows of H whose product is split over three waves
+
+// Column j - 1 is final: rotate it; the next column before its second pass,
+// t = (c - H s) / alpha with c = (z, zeta), follows from A q_j = (w - A Q s) / alpha.
+// LDS after s and z: the column [j + 1], partial products [3][min(j + 1, KH)].
+__device__ inline void kry_hessenberg(const Kry& k, int s, int j, const c128* ss, const c128* zs, c128* col,
+                                      bool last) {
+  __shared__ c128 rot[2][64];
+  __shared__ double rots[64];
+  const int wv = threadIdx.x >> 6, ln = threadIdx.x & 63;
+  const size_t o = (size_t)s * k.m;
+  c128* H = k.H + o * (k.m + 1);
+  c128* tv = k.t + (size_t)s * (k.m + 1);
+  c128 pc[2] = {{0.0, 0.0}, {0.0, 0.0}};
+  double ps[2] = {0.0, 0.0};
+  if (wv == 0)
+#pragma unroll
+    for (int q = 0; q < 2; ++q)
+      if (ln + 64 * q < j - 1) {
+        pc[q] = k.cs[o + ln + 64 * q];
+        ps[q] = k.sn[o + ln + 64 * q];
       }
+  const KryStep st = step_scalars(ss, zs, j);
+  if (!isfinite(st.alpha)) {  // jend stays: the earlier columns are finite
+    if (threadIdx.x == 0) {
+      k.h_bad[s] = 1;
+      k.active[s] = 0;
+      atomicSub(&k.ctl[KRY_ACTIVE], 1);
     }
+    return;
   }
-  // the last system's first block reports the step
-  if (first && threadIdx.x == 0) {
-    __threadfence();
-    if (atomicAdd(&k.ctl[KRY_ARRIVED], 1) == k.nsys - 1) {
-      k.ctl[KRY_ARRIVED] = 0;
-      const bool done = atomicAdd(&k.ctl[KRY_ACTIVE], 0) == 0;
-      if (done) {
-        k.ctl[KRY_DONE] = 1;
-        __hip_atomic_store(&k.h_ctl[KRY_HOST_DONE], 1, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
-      }
-      __hip_atomic_store(&k.h_ctl[KRY_HOST_STEPS], j + 1, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+  if (j == 0) {
+    if (threadIdx.x == 0) {
+      k.g[(size_t)s * (k.m + 1)] = c128{k.beta[s] * st.alpha, 0.0};
+      tv[0] = c128{st.f * st.zeta.re, st.f * st.zeta.im};
+    }
+    return;
+  }
+  c128* Hc = H + (size_t)(j - 1) * (k.m + 1);
+  for (int i = threadIdx.x; i <= j; i += KT) {
+    c128 v{st.alpha, 0.0};
+    if (i < j) {
+      const c128 a = tv[i], b = ss[i];
+      v = c128{a.re + b.re, a.im + b.im};
+    }
+    col[i] = v;
+    Hc[i] = v;
+  }
+  __syncthreads();
+  c128* hs = col + j + 1;
+  const int rows = min(j + 1, KH);
+  auto row_sum = [&](int i, int k0, int step) {
+    double re = 0.0, im = 0.0;
+    const int first = max(i - 1, 0);
+    const c128* h = H + i;
+#pragma unroll 8
+    for (int q = first + k0; q < j - 1; q += step) {
+      const c128 a = h[(size_t)q * (k.m + 1)], b = ss[q];
+      re += a.re * b.re - a.im * b.im;
+      im += a.re * b.im + a.im * b.re;
+    }
+    if (k0 == 0) {  // the new column is in LDS
+      const c128 a = col[i], b = ss[j - 1];
+      re += a.re * b.re - a.im * b.im;
+      im += a.re * b.im + a.im * b.re;
+    }
+    return c128{re, im};
+  };
+  auto next = [&](int i, c128 h) {
+    const c128 c = i < j ? zs[i] : st.zeta;
+    tv[i] = c128{st.f * (c.re - h.re), st.f * (c.im - h.im)};
+  };
+  if (wv == 0) {
+    kry_rotate(k, s, j - 1, st.alpha, col, pc[0], pc[1], ps[0], ps[1], rot, rots);
+  } else if (!last) {
+    for (int i = ln; i < rows; i += 64) hs[(wv - 1) * rows + i] = row_sum(i, wv - 1, 3);
+  }
+  if (last) return;
+  __syncthreads();
+  for (int i = threadIdx.x; i <= j; i += KT) {
+    if (i < rows) {
+      const c128 a = hs[i], b = hs[rows + i], c = hs[2 * rows + i];
+      next(i, c128{a.re + b.re + c.re, a.im + b.im + c.im});
+    } else {
+      next(i, row_sum(i, 0, 1));
     }
   }
 }
 
-// A cycle's start: v_0 = r / beta, the systems that take part, g = beta e_1.
+// Step j: q_j = (u - Q s) / alpha in the place of u, and u_next = (w - Q z - q_j
+// zeta) / alpha.  The first nsys blocks do the Hessenberg matrix meanwhile, stop
+// their system and report the step (LAST: they alone).  KP: waves that share a
+// block's elements, each with every KP-th vector.
+// Bound by the reads of V, and on short vectors by the chain of loads over k, which
+// KP = 4 cuts: 40x40 with 50 vectors 17 us (KP = 1, one output) -> 12.6 us.
+template <int KP, bool LAST>
+__global__ __launch_bounds__(KT) void kry_update(Kry k, int j) {
+  extern __shared__ __align__(16) unsigned char kry_lds[];
+  c128* ss = reinterpret_cast<c128*>(kry_lds);
+  c128* zs = ss + j + 1;
+  const bool hess = (int)blockIdx.x < k.nsys;
+  const int ub = (int)blockIdx.x - k.nsys;
+  KrySeg sg{(int)blockIdx.x, 0, 0, 0};
+  if (!hess) sg = upd_seg(k, ub);
+  if (hess && k.ctl[KRY_DONE]) return;
+  const bool active = k.active[sg.sys] != 0;
+  if (active) {
+    const c128* sums = reinterpret_cast<const c128*>(k.sums) + (size_t)sg.sys * 2 * (k.m + 1);
+    for (int q = threadIdx.x; q <= j; q += KT) {
+      ss[q] = sums[q];
+      zs[q] = sums[k.m + 1 + q];
+    }
+    __syncthreads();
+  }
+  if (hess) {
+    if (active) kry_hessenberg(k, sg.sys, j, ss, zs, zs + j + 1, LAST);
+    // the last system's block reports the step
+    if (threadIdx.x == 0) {
+      __threadfence();
+      if (atomicAdd(&k.ctl[KRY_ARRIVED], 1) == k.nsys - 1) {
+        k.ctl[KRY_ARRIVED] = 0;
+        const bool done = atomicAdd(&k.ctl[KRY_ACTIVE], 0) == 0;
+        if (done) {
+          k.ctl[KRY_DONE] = 1;
+          __hip_atomic_store(&k.h_ctl[KRY_HOST_DONE], 1, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+        }
+        __hip_atomic_store(&k.h_ctl[KRY_HOST_STEPS], j + 1, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+      }
+    }
+    return;
+  }
+  // a system that its first block stops meanwhile no longer uses what this writes
+  if (LAST || !active) return;
+  const KryStep st = step_scalars(ss, zs, j);
+  __shared__ double comb[KP > 1 ? KP - 1 : 1][4][64];
+  const int part = KP > 1 ? threadIdx.x >> 6 : 0, ln = threadIdx.x & 63;
+  const long long e = sg.lo + (KP > 1 ? ln : (int)threadIdx.x);
+  const bool in = e < sg.hi;
+  double ar = 0.0, ai = 0.0, br = 0.0, bi = 0.0;
+  if (in) {
+#pragma unroll 8
+    for (int q = part; q < j; q += KP) {
+      const c128 v = k.V[(size_t)q * k.stride + e], a = ss[q], b = zs[q];
+      ar += v.re * a.re - v.im * a.im;
+      ai += v.re * a.im + v.im * a.re;
+      br += v.re * b.re - v.im * b.im;
+      bi += v.re * b.im + v.im * b.re;
+    }
+  }
+  if (KP > 1) {
+    if (part) {
+      double* o = &comb[part - 1][0][ln];
+      o[0] = ar;
+      o[64] = ai;
+      o[128] = br;
+      o[192] = bi;
+    }
+    __syncthreads();
+    if (part) return;
+#pragma unroll
+    for (int q = 0; q < KP - 1; ++q) {
+      const double* o = &comb[q][0][ln];
+      ar += o[0];
+      ai += o[64];
+      br += o[128];
+      bi += o[192];
+    }
+  }
+  if (!in) return;
+  c128* u = k.V + (size_t)j * k.stride + e;
+  const c128 p = *u, w = k.w[e];
+  const c128 q{st.f * (p.re - ar), st.f * (p.im - ai)};
+  const c128 t = zmul(q, st.zeta);
+  *u = q;
+  u[k.stride] = c128{st.f * (w.re - br - t.re), st.f * (w.im - bi - t.im)};
+}
+
+// A cycle's start: v_0 = r / beta, the systems that take part.
 __global__ __launch_bounds__(KT) void kry_begin(Kry k, const c128* __restrict__ r) {
   const KrySeg sg = upd_seg(k, blockIdx.x);
   const int s = sg.sys;
@@ -309,7 +447,7 @@ __global__ __launch_bounds__(KT) void kry_begin(Kry k, const c128* __restrict__ 
     k.target[q] = k.h_target[q];
     k.limit[q] = k.h_limit[q];
     k.jend[q] = 0;
-    k.g[(size_t)q * (k.m + 1)] = c128{bq, 0.0};
+    for (int i = 0; i < k.ngroup; ++i) k.arrived[q * k.ngroup + i] = 0;
     n += act;
   }
   __shared__ double sh[KT / 64];
@@ -352,25 +490,44 @@ __global__ __launch_bounds__(KT) void kry_backsub(Kry k) {
   }
 }
 
-// x += V y
+// x += V y, KP as in kry_update
+template <int KP>
 __global__ __launch_bounds__(KT) void kry_solution(Kry k, c128* __restrict__ x) {
   const KrySeg sg = upd_seg(k, blockIdx.x);
   if (!k.live[sg.sys]) return;
   const int n = k.jend[sg.sys];
   const c128* y = k.y + (size_t)sg.sys * k.m;
-  for (long long e = sg.lo + threadIdx.x; e < sg.hi; e += KT) {
-    double sr = 0.0, si = 0.0;
+  __shared__ double comb[KP > 1 ? KP - 1 : 1][2][64];
+  const int part = KP > 1 ? threadIdx.x >> 6 : 0, ln = threadIdx.x & 63;
+  const long long e = sg.lo + (KP > 1 ? ln : (int)threadIdx.x);
+  const bool in = e < sg.hi;
+  double sr = 0.0, si = 0.0;
+  if (in) {
 #pragma unroll 8
-    for (int q = 0; q < n; ++q) {
+    for (int q = part; q < n; q += KP) {
       const c128 v = k.V[(size_t)q * k.stride + e], c = y[q];
       sr += v.re * c.re - v.im * c.im;
       si += v.re * c.im + v.im * c.re;
     }
-    c128 o = x[e];
-    o.re += sr;
-    o.im += si;
-    x[e] = o;
   }
+  if (KP > 1) {
+    if (part) {
+      comb[part - 1][0][ln] = sr;
+      comb[part - 1][1][ln] = si;
+    }
+    __syncthreads();
+    if (part) return;
+#pragma unroll
+    for (int q = 0; q < KP - 1; ++q) {
+      sr += comb[q][0][ln];
+      si += comb[q][1][ln];
+    }
+  }
+  if (!in) return;
+  c128 o = x[e];
+  o.re += sr;
+  o.im += si;
+  x[e] = o;
 }
 
 // out = a - b (b null: a) and the partial sums of |out|^2, live systems (all if
@@ -428,16 +585,21 @@ struct Graphs {
   }
 };
 
-// Elements per block.  Dots: at most 64 rows of partial sums per system (every
-// update block adds them up), 128 on vectors of over a million elements.
-// Updates: one element per thread on short vectors, where more blocks hide the
-// latency, else four.
-void block_sizes(long long len, int& nd, long long& dper, int& nu, long long& uper) {
-  const long long most = len > (1 << 20) ? 128 : 64;
-  long long n = std::max(1ll, std::min(most, (len + 1023) / 1024));
-  dper = (len + n - 1) / n;
+// Elements per block.  Dots: whole passes of the block's threads, so many blocks
+// that all groups and systems (`others`) together make about 1024, but 512 elements
+// at least (256 up to 8192: 8x8 at lmax 2 8.1 -> 6.2 us; 512 or 1024 beyond that: 40x40
+// 18.2, 17.6, 18.0 us with 256, 512, 1024) and 512 rows of partial sums per system at
+// most.  Updates: 64 shared by four waves up to 131072 elements in all (512 to 2048
+// blocks), else one per thread.
+void dot_blocks(long long len, long long others, int& nd, long long& dper) {
+  const long long most = std::max(1ll, std::min(512ll, len / (len > 8192 ? 512 : 256)));
+  const long long n = std::max(1ll, std::min(most, 1024 / others));
+  dper = ((len + n - 1) / n + KT - 1) / KT * KT;
   nd = (int)((len + dper - 1) / dper);
-  uper = len > 65536 ? 4 * KT : KT;
+}
+void block_sizes(long long len, long long total, long long others, int& nd, long long& dper, int& nu, long long& uper) {
+  dot_blocks(len, others, nd, dper);
+  uper = total > 131072 ? KT : 64;
   nu = (int)((len + uper - 1) / uper);
 }
 
@@ -469,6 +631,7 @@ int kry_solve(tm_ctx* c, KryProblem& p, tm_solve_info* info) {
   Kry k{};
   k.nsys = ns;
   k.m = m;
+  k.ngroup = (m + 1 + KC - 1) / KC;
   k.stride = p.total;
   k.w = p.w;
   int rc;
@@ -478,7 +641,7 @@ int kry_solve(tm_ctx* c, KryProblem& p, tm_solve_info* info) {
   int ndots, nupd;
   if (p.len) {
     k.len = p.len;
-    block_sizes(p.len, k.nd, k.dper, k.nu, k.uper);
+    block_sizes(p.len, p.total, ns, k.nd, k.dper, k.nu, k.uper);
     ndots = ns * k.nd;
     nupd = ns * k.nu;
   } else {
@@ -487,7 +650,7 @@ int kry_solve(tm_ctx* c, KryProblem& p, tm_solve_info* info) {
       const long long len = p.off[s + 1] - p.off[s];
       int nd, nu;
       long long dper, uper;
-      block_sizes(len, nd, dper, nu, uper);
+      block_sizes(len, p.total, 4 * ns, nd, dper, nu, uper);
       of[s] = (int)dseg.size();
       of[ns + 1 + s] = (int)useg.size();
       for (long long e = 0; e < len; e += dper) dseg.push_back(KrySeg{s, 0, p.off[s] + e, p.off[s] + std::min(len, e + dper)});
@@ -510,14 +673,16 @@ int kry_solve(tm_ctx* c, KryProblem& p, tm_solve_info* info) {
     auto carve = [&] {
       at = 0;
       const size_t sm = (size_t)ns * m * sizeof(c128);
-      k.part = (c128*)take((size_t)ndots * m * sizeof(c128));
+      const size_t sm1 = sm + (size_t)ns * sizeof(c128);
+      k.part = (double*)take((size_t)ndots * k.ngroup * 4 * KC * sizeof(double));
+      k.sums = (double*)take(2 * sm1);
       k.npart = (double*)take((size_t)nupd * sizeof(double));
-      k.h1 = (c128*)take(sm);
-      k.h2 = (c128*)take(sm);
+      k.H = (c128*)take(sm1 * m);
       k.R = (c128*)take(sm * m);
+      k.t = (c128*)take(sm1);
+      k.g = (c128*)take(sm1);
       k.cs = (c128*)take(sm);
-      k.sn = (c128*)take(sm);
-      k.g = (c128*)take(sm + ns * sizeof(c128));
+      k.sn = (double*)take((size_t)ns * m * sizeof(double));
       k.y = (c128*)take(sm);
       k.beta = (double*)take(ns * sizeof(double));
       k.target = (double*)take(ns * sizeof(double));
@@ -526,6 +691,7 @@ int kry_solve(tm_ctx* c, KryProblem& p, tm_solve_info* info) {
       k.jend = (int*)take(ns * sizeof(int));
       k.active = (int*)take(ns * sizeof(int));
       k.ctl = (int*)take(4 * sizeof(int));
+      k.arrived = (int*)take((size_t)ns * k.ngroup * sizeof(int));
       if (!p.len) {
         k.dseg = (const KrySeg*)take(dseg.size() * sizeof(KrySeg));
         k.useg = (const KrySeg*)take(useg.size() * sizeof(KrySeg));
@@ -568,20 +734,29 @@ int kry_solve(tm_ctx* c, KryProblem& p, tm_solve_info* info) {
     TM_HIP(c, hipStreamSynchronize(st));
     return TM_OK;
   };
-  // one Arnoldi step on c->stream (also recorded into graphs)
-  auto step = [&](int j) -> int {
-    c->mv_stop = &k.ctl[KRY_DONE];
-    int e = p.apply(prec, k.V + (size_t)j * k.stride, k.w, k.active);
-    c->mv_stop = nullptr;
-    if (e != TM_OK) return e;
-    const int nv = j + 1;
-    const dim3 gd(ndots, (nv + KC - 1) / KC);
-    const size_t lds = (size_t)(nv + KT) * sizeof(c128);
-    hipLaunchKernelGGL(kry_dots, gd, dim3(KT), 0, c->stream, k, nv);
-    hipLaunchKernelGGL(kry_update<false>, dim3(nupd), dim3(KT), lds, c->stream, k, nv);
-    hipLaunchKernelGGL(kry_dots, gd, dim3(KT), 0, c->stream, k, nv);
-    hipLaunchKernelGGL(kry_update<true>, dim3(nupd), dim3(KT), lds, c->stream, k, nv);
-    hipLaunchKernelGGL(kry_finish, dim3(nupd), dim3(KT), 0, c->stream, k, j);
+  const bool shared = p.total <= 131072;  // as block_sizes
+  const Kry& cycle = k;
+  // one Arnoldi step on c->stream (also recorded into graphs); `last` only makes
+  // column j - 1 final
+  auto step = [&](int j, bool last) -> int {
+    if (!last) {
+      c->mv_stop = &k.ctl[KRY_DONE];
+      int e = p.apply(prec, k.V + (size_t)j * k.stride, k.w, k.active);
+      c->mv_stop = nullptr;
+      if (e != TM_OK) return e;
+    }
+    const int groups = (j + KC) / KC;
+    int nd = ndots;
+    Kry k = cycle;
+    if (p.len) {
+      dot_blocks(p.len, (long long)ns * groups, k.nd, k.dper);
+      nd = ns * k.nd;
+    }
+    const dim3 gd(nd, groups), gu(last ? ns : ns + nupd);
+    const size_t lds = (size_t)(3 * (j + 1) + 3 * std::min(j + 1, KH)) * sizeof(c128);
+    hipLaunchKernelGGL((last ? kry_dots<false> : kry_dots<true>), gd, dim3(KT), 0, c->stream, k, j);
+    hipLaunchKernelGGL((last ? kry_update<1, true> : shared ? kry_update<4, false> : kry_update<1, false>), gu, dim3(KT), lds,
+                       c->stream, k, j);
     TM_HIP(c, hipGetLastError());
     return TM_OK;
   };
@@ -672,10 +847,10 @@ int kry_solve(tm_ctx* c, KryProblem& p, tm_solve_info* info) {
                        hipEventCreateWithFlags(&gr.in, hipEventDisableTiming) != hipSuccess ||
                        hipEventCreateWithFlags(&gr.out, hipEventDisableTiming) != hipSuccess))
         return set_err(c, TM_ERR_HIP, "stream/event creation for the solve's graphs failed");
-      gr.exec.resize((m + KRY_CHUNK - 1) / KRY_CHUNK, nullptr);
+      gr.exec.resize(m / KRY_CHUNK + 1, nullptr);
       TM_HIP(c, hipEventRecord(gr.in, st));
       TM_HIP(c, hipStreamWaitEvent(gr.side, gr.in, 0));
-      for (int q = 0; q * KRY_CHUNK < jmax; ++q) {
+      for (int q = 0; q * KRY_CHUNK <= jmax; ++q) {
         if (!gr.exec[q]) {
           // recorded on the private stream (the context's may be the null
           // stream, which cannot be captured)
@@ -683,7 +858,7 @@ int kry_solve(tm_ctx* c, KryProblem& p, tm_solve_info* info) {
           c->stream = gr.side;
           if (hipStreamBeginCapture(gr.side, hipStreamCaptureModeThreadLocal) == hipSuccess) {
             rc = TM_OK;
-            for (int j = q * KRY_CHUNK; j < std::min(m, (q + 1) * KRY_CHUNK) && rc == TM_OK; ++j) rc = step(j);
+            for (int j = q * KRY_CHUNK; j < std::min(m + 1, (q + 1) * KRY_CHUNK) && rc == TM_OK; ++j) rc = step(j, j == m);
             const hipError_t e = hipStreamEndCapture(gr.side, &g);
             if (rc == TM_OK && e == hipSuccess && g && hipGraphInstantiateWithFlags(&gr.exec[q], g, 0) != hipSuccess)
               gr.exec[q] = nullptr;
@@ -707,22 +882,22 @@ int kry_solve(tm_ctx* c, KryProblem& p, tm_solve_info* info) {
       TM_HIP(c, hipStreamWaitEvent(st, gr.out, 0));
     }
     if (eager) {
-      for (int j = launched; j < jmax; ++j) {
+      for (int j = launched; j <= jmax; ++j) {
         if (j >= KRY_AHEAD && (rc = wait_steps(j - KRY_AHEAD + 1, st)) != TM_OK) return rc;
         if (hctl[KRY_HOST_DONE]) break;
-        if ((rc = step(j)) != TM_OK) return rc;
-        ++launched;
+        if ((rc = step(j, j == jmax)) != TM_OK) return rc;
+        if (j < jmax) ++launched;
         // a long cycle also reports every 50 steps
-        if (p.progress_inside && (j + 1) % 50 == 0 && j + 1 < jmax) {
+        if (p.progress_inside && j && j % 50 == 0 && j < jmax) {
           TM_HIP(c, hipStreamSynchronize(st));
           if (hctl[KRY_HOST_DONE]) break;
-          p.progress_inside(cyc, it_most + j + 1, k.h_est[0] / bnorm[0]);
+          p.progress_inside(cyc, it_most + j, k.h_est[0] / bnorm[0]);
         }
       }
     }
     const size_t prof_mark = c->prof ? c->prof_pending[which_prof].size() : 0;
     hipLaunchKernelGGL(kry_backsub, dim3(ns), dim3(KT), back_lds, st, k);
-    hipLaunchKernelGGL(kry_solution, dim3(nupd), dim3(KT), 0, st, k, p.x);
+    hipLaunchKernelGGL((shared ? kry_solution<4> : kry_solution<1>), dim3(nupd), dim3(KT), 0, st, k, p.x);
     // true residual in FP64; kry_norm's wait is the cycle's one wait
     if ((rc = p.apply(TM_PREC_FP64, p.x, p.w, nlive < ns ? k.live : nullptr)) != TM_OK) return rc;
     if ((rc = residual_norms(p.b, p.w, p.r, 0)) != TM_OK) return rc;
