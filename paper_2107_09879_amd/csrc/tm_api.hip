@@ -141,7 +141,7 @@ void tm_destroy(tm_ctx* c) {
   for (tmh::DevBuf* b : {&c->dtab[0], &c->dtab[1], &c->dtab[2], &c->dtab[3], &c->gpos, &c->jinc_buf,
                         &c->kry_dev, &c->tmb, &c->tmflag, &c->spec_sym, &c->spec_w, &c->spec_const, &c->spec_d})
     tmh::release(*b);
-  for (tmh::DevBuf* b : {&c->tab64, &c->tab32, &c->tabT64, &c->tabT32, &c->t64, &c->t32, &c->dt64,
+  for (tmh::DevBuf* b : {&c->tab64, &c->tab32, &c->tabT64, &c->tabT32, &c->tab_work, &c->t64, &c->t32, &c->dt64,
                         &c->tden, &c->ttmp, &c->partial, &c->xlow, &c->work_a, &c->work_b, &c->work_c, &c->basis,
                         &c->plan_items[0], &c->plan_items[1],
                         &c->plan_ibeg[0], &c->plan_ibeg[1]})
@@ -233,7 +233,7 @@ int tm_set_geometry(tm_ctx* c, int n, const double* pos, double k, int lmax) {
     c->host_xy.clear();
   } else {
     // no displacement tables: release a previous lattice's
-    for (tmh::DevBuf* b : {&c->tab64, &c->tab32, &c->tabT64, &c->tabT32})
+    for (tmh::DevBuf* b : {&c->tab64, &c->tab32, &c->tabT64, &c->tabT32, &c->tab_work})
       if (b->p) {
         TM_HIP(c, hipStreamSynchronize(c->stream));
         tmh::release(*b);

@@ -136,6 +136,7 @@ struct tm_ctx {
   bool t_mblock = false;  // ... and zero between different m: applied from tmb
   // translation tables [D][2][S][S]
   tmh::DevBuf tab64, tab32, tabT64, tabT32;
+  tmh::DevBuf tab_work;  // constants, radial and angular factors of the tables
   bool have_tabT = false;
   // FP64 derivative tables of the position gradient: d/dx, d/dy, and the
   // transposed operator's d/dx, d/dy (built on first use)

@@ -21,6 +21,7 @@
 // S xi(x_t - x_s) S with S = diag((-1)^(l+p)), so MT(dx,dy)[i][j] =
 // sigma_i sigma_j M(dx,dy)[j][i].
 #include <cmath>
+#include <mutex>
 
 #include <algorithm>
 
@@ -405,31 +406,51 @@ int build_derivative_tables(tm_ctx* c) {
   return TM_OK;
 }
 
-static int build_impl(tm_ctx* c, DevBuf& t64, DevBuf& t32, int transpose) {
-  const Geometry& g = c->g;
+// The constants of one lmax as the device reads them: coef, dm, sig.
+struct TableConst {
+  std::vector<unsigned char> bytes;
+  size_t dm = 0, sig = 0;
+};
+static const TableConst& packed_constants(const Geometry& g) {
+  static std::mutex mu;
+  static TableConst cache[LMAX_SUPPORTED + 1];
+  std::lock_guard<std::mutex> lk(mu);
+  TableConst& t = cache[g.lmax];
+  if (!t.bytes.empty()) return t;
   std::vector<double> coef;
   std::vector<int> dm, sig;
+  table_constants(g, 2 * g.lmax + 1, coef, dm, sig);
+  t.dm = coef.size() * sizeof(double);
+  t.sig = t.dm + dm.size() * sizeof(int);
+  std::vector<unsigned char> b((t.sig + sig.size() * sizeof(int) + 255) & ~(size_t)255);
+  std::copy(coef.begin(), coef.end(), reinterpret_cast<double*>(b.data()));
+  std::copy(dm.begin(), dm.end(), reinterpret_cast<int*>(b.data() + t.dm));
+  std::copy(sig.begin(), sig.end(), reinterpret_cast<int*>(b.data() + t.sig));
+  t.bytes = std::move(b);
+  return t;
+}
+
+// The kernel writes at the card's copy rate (100x100 at lmax 3: 487 MB, 104 us); around
+// it five allocations, their frees, three copies and the constants' Wigner symbols
+// took longer than it, so the constants are kept per lmax and the workspace per
+// context: a new 100x100 layout with T and two right-hand
+// sides 510 -> 245 us.
+static int build_impl(tm_ctx* c, DevBuf& t64, DevBuf& t32, int transpose) {
+  const Geometry& g = c->g;
   const int qmax = 2 * g.lmax;
-  table_constants(g, qmax + 1, coef, dm, sig);
+  const TableConst& tc = packed_constants(g);
   const long long D = g.n_disp();
   const size_t blk = (size_t)NCLASS * g.S * g.S;
   int rc;
   if ((rc = ensure(c, t64, (size_t)D * blk * sizeof(c128))) != TM_OK) return rc;
   if ((rc = ensure(c, t32, (size_t)D * blk * sizeof(c64))) != TM_OK) return rc;
-  double* dcoef = nullptr;
-  int *ddm = nullptr, *dsig = nullptr;
-  c128 *rad = nullptr, *ang = nullptr;
-  TM_HIP(c, hipMalloc((void**)&dcoef, coef.size() * sizeof(double)));
-  TM_HIP(c, hipMalloc((void**)&ddm, dm.size() * sizeof(int)));
-  TM_HIP(c, hipMalloc((void**)&dsig, sig.size() * sizeof(int)));
-  TM_HIP(c, hipMalloc((void**)&rad, (size_t)D * (qmax + 1) * sizeof(c128)));
-  TM_HIP(c, hipMalloc((void**)&ang, (size_t)D * (2 * qmax + 1) * sizeof(c128)));
-  TM_HIP(c, hipMemcpyAsync(dcoef, coef.data(), coef.size() * sizeof(double),
-                           hipMemcpyHostToDevice, c->stream));
-  TM_HIP(c, hipMemcpyAsync(ddm, dm.data(), dm.size() * sizeof(int), hipMemcpyHostToDevice,
-                           c->stream));
-  TM_HIP(c, hipMemcpyAsync(dsig, sig.data(), sig.size() * sizeof(int), hipMemcpyHostToDevice,
-                           c->stream));
+  const size_t nrad = (size_t)D * (qmax + 1), nang = (size_t)D * (2 * qmax + 1);
+  if ((rc = ensure(c, c->tab_work, tc.bytes.size() + (nrad + nang) * sizeof(c128))) != TM_OK) return rc;
+  unsigned char* base = (unsigned char*)c->tab_work.p;
+  const double* dcoef = (const double*)base;
+  const int *ddm = (const int*)(base + tc.dm), *dsig = (const int*)(base + tc.sig);
+  c128 *rad = (c128*)(base + tc.bytes.size()), *ang = rad + nrad;
+  TM_HIP(c, hipMemcpyAsync(base, tc.bytes.data(), tc.bytes.size(), hipMemcpyHostToDevice, c->stream));
   hipLaunchKernelGGL(table_radial_kernel, dim3((unsigned)((D + 255) / 256)), dim3(256), 0, c->stream,
                      g.tnx, g.tny, g.pitch, g.k, qmax, D, rad, ang);
   const unsigned nchunk = (unsigned)((blk + 511) / 512);
@@ -450,13 +471,8 @@ static int build_impl(tm_ctx* c, DevBuf& t64, DevBuf& t32, int transpose) {
   }
 #undef TB_LAUNCH
   TM_HIP(c, hipGetLastError());
-  // the host vectors above are read by the async copies; wait before they go
+  // complete when the call returns: the next product may be on another stream
   TM_HIP(c, hipStreamSynchronize(c->stream));
-  TM_HIP(c, hipFree(dcoef));
-  TM_HIP(c, hipFree(ddm));
-  TM_HIP(c, hipFree(dsig));
-  TM_HIP(c, hipFree(rad));
-  TM_HIP(c, hipFree(ang));
   return TM_OK;
 }
 
