@@ -405,9 +405,9 @@ int tm_grad_position(tm_ctx* ctx, int n_rhs, const tm_c128* mu, const tm_c128* s
 /* ---- matvec launch configuration (autotuner) ----------------------------- */
 
 /* The product with A runs by Fourier transform of the lattice by default,
- * where a lattice fits it (a row or a column of at most 320 sites, and its
- * column of coefficients in LDS: 320 sites to lmax 3, 150 at lmax 4, 100 (FP64)
- * or 200 (complex64) above); else by the block kernels below, which this call
+ * where a lattice fits it (a row of at most 320 sites, and a column of
+ * coefficients in LDS: 300 sites to lmax 3, 150 at lmax 4, 100 above in FP64; 320,
+ * 300, 200 in complex64); else by the block kernels below, which this call
  * also selects for its precision.
  * Kernel variant and work split of the block matvec for one precision.
  * variant 0..7 (operands read from global memory): bit 0 = complex products

@@ -250,11 +250,13 @@ __device__ inline void kry_rotate(const Kry& k, int s, int c, double hn, const c
   }
 }
 
-constexpr int KH = 256;  // rows of H whose product is split over three waves
+// Rows of H whose product with s is split over three waves: what LDS holds beside
+// s, z and the column (64 KB with 9 KB of fixed arrays, up to j = 1000).
+__host__ __device__ inline int kry_rows(int j) { return j < 512 ? (j < 255 ? j + 1 : 256) : 128; }
 
 // Column j - 1 is final: rotate it; the next column before its second pass,
 // t = (c - H s) / alpha with c = (z, zeta), follows from A q_j = (w - A Q s) / alpha.
-// LDS after s and z: the column [j + 1], partial products [3][min(j + 1, KH)].
+// LDS after s and z: the column [j + 1], partial products [3][kry_rows(j)].
 __device__ inline void kry_hessenberg(const Kry& k, int s, int j, const c128* ss, const c128* zs, c128* col,
                                       bool last) {
   __shared__ c128 rot[2][64];
@@ -300,7 +302,7 @@ __device__ inline void kry_hessenberg(const Kry& k, int s, int j, const c128* ss
   }
   __syncthreads();
   c128* hs = col + j + 1;
-  const int rows = min(j + 1, KH);
+  const int rows = kry_rows(j);
   auto row_sum = [&](int i, int k0, int step) {
     double re = 0.0, im = 0.0;
     const int first = max(i - 1, 0);
@@ -753,7 +755,7 @@ int kry_solve(tm_ctx* c, KryProblem& p, tm_solve_info* info) {
       nd = ns * k.nd;
     }
     const dim3 gd(nd, groups), gu(last ? ns : ns + nupd);
-    const size_t lds = (size_t)(3 * (j + 1) + 3 * std::min(j + 1, KH)) * sizeof(c128);
+    const size_t lds = (size_t)(3 * (j + 1) + 3 * kry_rows(j)) * sizeof(c128);
     hipLaunchKernelGGL((last ? kry_dots<false> : kry_dots<true>), gd, dim3(KT), 0, c->stream, k, j);
     hipLaunchKernelGGL((last ? kry_update<1, true> : shared ? kry_update<4, false> : kry_update<1, false>), gu, dim3(KT), lds,
                        c->stream, k, j);

@@ -1,5 +1,5 @@
 """GMRES with its second Gram-Schmidt pass one step late, where its kernels split:
-one cycle of more steps than rows that three waves share (256) and than rotations
+one cycle of more steps than rows that three waves share (256; 128 from step 512 on) and than rotations
 loaded ahead (128), long after convergence (the basis has to stay orthogonal), and
 vectors on both sides of the switch between elements shared by four waves and one
 per thread (131072 in all).
@@ -53,7 +53,7 @@ def least_residual(B, b, steps):
     return np.linalg.norm(b - B @ (y @ V[:steps])) / beta
 
 
-@pytest.mark.parametrize("steps", [64, 65, 129, 130, 255, 256, 257, 300])
+@pytest.mark.parametrize("steps", [64, 65, 129, 130, 255, 256, 257, 300, 512, 513])
 def test_long_cycles(steps):
     print(f"[case] {steps} steps", flush=True)
     ctx, pos, radii = setup(12, 11, 2)
