@@ -196,6 +196,12 @@ __device__ inline KryStep step_scalars(const c128* s, const c128* z, int j) {
   return r;
 }
 
+// The system leaves the cycle; this launch's update blocks may still read the flag.
+__device__ inline void kry_stop(const Kry& k, int s) {
+  __hip_atomic_store(&k.active[s], 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  atomicSub(&k.ctl[KRY_ACTIVE], 1);
+}
+
 // Column c of the Hessenberg matrix, col[0 .. c] with hn below it: the earlier
 // rotations, a new one, the residual estimate.  One wave; the rotations are a
 // serial chain, 64 of them at a time in LDS, the first 128 loaded ahead (pc, ps).
@@ -245,8 +251,7 @@ __device__ inline void kry_rotate(const Kry& k, int s, int c, double hn, const c
   const bool bad = !isfinite(est);
   if (bad) k.h_bad[s] = 1;
   if (est <= k.target[s] || hn == 0.0 || bad || c + 1 >= k.limit[s]) {
-    k.active[s] = 0;
-    atomicSub(&k.ctl[KRY_ACTIVE], 1);
+    kry_stop(k, s);
   }
 }
 
@@ -278,8 +283,7 @@ __device__ inline void kry_hessenberg(const Kry& k, int s, int j, const c128* ss
   if (!isfinite(st.alpha)) {  // jend stays: the earlier columns are finite
     if (threadIdx.x == 0) {
       k.h_bad[s] = 1;
-      k.active[s] = 0;
-      atomicSub(&k.ctl[KRY_ACTIVE], 1);
+      kry_stop(k, s);
     }
     return;
   }
@@ -357,15 +361,17 @@ __global__ __launch_bounds__(KT) void kry_update(Kry k, int j) {
   KrySeg sg{(int)blockIdx.x, 0, 0, 0};
   if (!hess) sg = upd_seg(k, ub);
   if (hess && k.ctl[KRY_DONE]) return;
-  const bool active = k.active[sg.sys] != 0;
-  if (active) {
-    const c128* sums = reinterpret_cast<const c128*>(k.sums) + (size_t)sg.sys * 2 * (k.m + 1);
-    for (int q = threadIdx.x; q <= j; q += KT) {
-      ss[q] = sums[q];
-      zs[q] = sums[k.m + 1 + q];
-    }
-    __syncthreads();
+  // One thread reads the flag, which the system's Hessenberg block may clear meanwhile:
+  // a block's waves have to agree on the barriers below.
+  __shared__ int flag;
+  if (threadIdx.x == 0) flag = __hip_atomic_load(&k.active[sg.sys], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  const c128* sums = reinterpret_cast<const c128*>(k.sums) + (size_t)sg.sys * 2 * (k.m + 1);
+  for (int q = threadIdx.x; q <= j; q += KT) {
+    ss[q] = sums[q];
+    zs[q] = sums[k.m + 1 + q];
   }
+  __syncthreads();
+  const bool active = flag != 0;
   if (hess) {
     if (active) kry_hessenberg(k, sg.sys, j, ss, zs, zs + j + 1, LAST);
     // the last system's block reports the step
@@ -383,7 +389,7 @@ __global__ __launch_bounds__(KT) void kry_update(Kry k, int j) {
     }
     return;
   }
-  // a system that its first block stops meanwhile no longer uses what this writes
+  // a system that its Hessenberg block stops meanwhile no longer uses what this writes
   if (LAST || !active) return;
   const KryStep st = step_scalars(ss, zs, j);
   __shared__ double comb[KP > 1 ? KP - 1 : 1][4][64];

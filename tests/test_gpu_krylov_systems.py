@@ -1,0 +1,46 @@
+"""GMRES over several systems that leave a cycle at different steps: a system that stops
+while another launch still works on its vectors must not disturb the others, nor the
+bits of the results from one run to the next (every sum has a fixed order)."""
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+if not torch.cuda.is_available():
+    pytest.skip("needs a GPU", allow_module_level=True)
+
+import workloads as wl  # noqa: E402
+from paper_2107_09879_amd import tmhip  # noqa: E402
+
+pytestmark = pytest.mark.gpu
+DEV = torch.device("cuda", 0)
+
+
+def setup(nx, ny, lmax, seed=7):
+    ctx = tmhip.Context(0)
+    ctx.set_geometry(wl.lattice_positions(nx, ny), wl.K, lmax)
+    ctx.set_spheres(torch.tensor(wl.uniform_radii(nx * ny, 0.15, 0.2, seed), device=DEV), wl.N_REL)
+    return ctx
+
+
+def rhs(ctx, R, seed):
+    rng = np.random.default_rng(seed)
+    return torch.tensor(rng.normal(size=(R, ctx.n, ctx.L)) + 1j * rng.normal(size=(R, ctx.n, ctx.L)), device=DEV)
+
+
+@pytest.mark.parametrize("nx,ny,precision", [(17, 13, "fp64"), (40, 37, "mixed")])
+def test_systems_that_stop_at_different_steps(nx, ny, precision):
+    """From start vectors of different accuracy, so that the systems stop steps apart."""
+    print(f"[case] {nx}x{ny} {precision}", flush=True)
+    ctx = setup(nx, ny, 2)
+    a0 = rhs(ctx, 5, 1)
+    s, _ = ctx.solve(a0, tol=1e-12, precision=precision)
+    x0 = s + rhs(ctx, 5, 2) * torch.tensor([1e-10, 1e-8, 1e-5, 1e-2, 1.0], device=DEV)[:, None, None]
+    first = None
+    for rep in range(4):
+        got, info = ctx.solve(a0, x0=x0.clone(), tol=1e-11, restart=60, precision=precision)
+        assert all(i["status"] == 0 and i["rel_residual"] <= 1e-11 for i in info)
+        assert len({i["iters"] for i in info}) >= 4
+        if first is None:
+            first = got, info
+        assert torch.equal(torch.view_as_real(got), torch.view_as_real(first[0])) and info == first[1]
+    ctx.close()
