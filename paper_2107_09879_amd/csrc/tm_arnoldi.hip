@@ -138,9 +138,11 @@ __global__ __launch_bounds__(KT) void kry_dots(Kry k, int j) {
     int* arrived = k.arrived + (size_t)sg.sys * k.ngroup + blockIdx.y;
     // Written through the L2 and waited for before the block counts itself, and read
     // past the L2: a device-wide fence here writes the whole L2 back, in every block
-    // (37x53 with two right-hand sides: 127 us; so 32, with 1024 blocks 24).
+    // (37x53 with two right-hand sides: 127 us; so 32, with 1024 blocks 24).  The empty
+    // asms keep the compiler from moving the store or the count across the wait.
     if (wv == 0) {
       if (ln < 32) __hip_atomic_store(&part[blockIdx.x * ld + ln], t, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      asm volatile("" ::: "memory");
       __builtin_amdgcn_s_waitcnt(0);
       asm volatile("" ::: "memory");
       if (ln == 0)
