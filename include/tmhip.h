@@ -204,7 +204,11 @@ void tm_default_opts(tm_solve_opts* opts);
 /* Solve (I - T A) s = T a0 for each right-hand side.
  * a0: device [R][N][L]; s: device [R][N][L] (initial guess if use_x0);
  * info: host [R].  Returns TM_OK if every RHS converged, TM_NOT_CONVERGED if
- * any did not (its best iterate is still written). */
+ * any did not (its best iterate is still written).  Right-hand sides advance
+ * together, as many at a time as a quarter of the card's memory holds (fewer
+ * where less can be allocated; one at a time under a progress callback).
+ * Results are reproducible run to run; how many are solved together changes
+ * them by rounding. */
 int tm_solve(tm_ctx* ctx, int n_rhs, const tm_c128* a0, tm_c128* s,
              const tm_solve_opts* opts, tm_solve_info* info);
 

@@ -499,6 +499,21 @@ static int validate_opts(tm_ctx* c, const tm_solve_opts* o) {
   return TM_OK;
 }
 
+// How many right-hand sides a solve takes at once: as many as leave three quarters of
+// the card's memory for the rest.  Of the card's memory and not of what is free, so that
+// a solve's sums are cut alike whatever else is allocated.
+static int solve_group(tm_ctx* c, int R, int restart, int& group) {
+  const tmh::Geometry& g = c->g;
+  size_t card = 0;
+  TM_HIP(c, hipDeviceTotalMem(&card, c->device));
+  // basis, residual and product (whose grid or partial sums take about six vectors
+  // more), H and R, partial sums of the dots
+  const size_t m = (size_t)restart, one = (m + 9) * (size_t)g.vec_len() * sizeof(c128) +
+                                          2 * m * (m + 1) * sizeof(c128) + 512 * (m / 8 + 1) * 256;
+  group = (int)std::max<size_t>(1, std::min<size_t>(R, card / 4 / one));
+  return TM_OK;
+}
+
 static int solve_common(tm_ctx* c, Op op, int R, const tm_c128* rhs, tm_c128* out,
                         const tm_solve_opts* o, tm_solve_info* info) {
   CHECK_CTX(c);
@@ -523,20 +538,14 @@ static int solve_common(tm_ctx* c, Op op, int R, const tm_c128* rhs, tm_c128* ou
     }
   }
   if (o->use_x0) tmh::pack_slots(c->stream, g, c->maps, R, out, xsl);
-  // right-hand sides share the launches of every step, as many as their bases
-  // leave three quarters of the free memory for; one at a time under a progress
+  // right-hand sides share the launches of every step; one at a time under a progress
   // callback, which reports each by itself
   int group = 1;
-  if (R > 1 && !c->progress) {
-    size_t free_b = 0, total_b = 0;
-    TM_HIP(c, hipMemGetInfo(&free_b, &total_b));
-    const size_t one = (size_t)(o->restart + 1) * len * sizeof(c128);
-    group = (int)std::max<size_t>(1, std::min<size_t>(R, std::max(free_b / 4, c->basis.bytes) / one));
-  }
+  if (R > 1 && !c->progress && (rc = solve_group(c, R, o->restart, group)) != TM_OK) return rc;
   bool all_ok = true;
-  for (int r = 0; r < R; r += group) {
-    const int n = std::min(group, R - r);
-    if ((rc = tmh::ensure(c, c->work_c, (size_t)2 * n * len * sizeof(c128))) != TM_OK) return rc;
+  for (int r = 0, n; r < R; r += n) {
+    n = std::min(group, R - r);
+    rc = tmh::ensure(c, c->work_c, (size_t)2 * n * len * sizeof(c128));
     tmh::KryProblem p;
     p.nsys = n;
     p.len = len;
@@ -557,8 +566,15 @@ static int solve_common(tm_ctx* c, Op op, int R, const tm_c128* rhs, tm_c128* ou
       p.progress = [&](int cyc, int it, int live, double res) { c->progress(c->progress_user, cyc, it, live, res); };
       p.progress_inside = [&](int cyc, int it, double res) { c->progress(c->progress_user, cyc, it, 1, res); };
     }
-    rc = tmh::kry_solve(c, p, info + r);
+    if (rc == TM_OK) rc = tmh::kry_solve(c, p, info + r);
     c->mv_stop = nullptr;
+    // fewer at a time, from the start (a start vector is still as it was: a solve has
+    // allocated everything before it changes one)
+    if (rc == TM_ERR_OOM && n > 1) {
+      group = n / 2;
+      n = 0;
+      continue;
+    }
     if (rc != TM_OK) return rc;
     for (int q = r; q < r + n; ++q) all_ok = all_ok && info[q].status == TM_OK;
   }

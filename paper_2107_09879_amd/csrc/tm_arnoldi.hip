@@ -21,7 +21,8 @@
 // at lmax 3 mixed with two right-hand sides 97 -> 50 -> 28 ms, 150x150 8.1 -> 4.8 ms, six
 // subregions of 14 to 36 sites with two 365 (block products) -> 47 -> 28 ms.
 //
-// Every sum has a fixed order: results are reproducible run to run.
+// Every sum has a fixed order, cut by the number of systems solved together and their
+// lengths: results are reproducible run to run.
 #include "tm_arnoldi.h"
 
 #include <algorithm>

@@ -44,3 +44,28 @@ def test_systems_that_stop_at_different_steps(nx, ny, precision):
             first = got, info
         assert torch.equal(torch.view_as_real(got), torch.view_as_real(first[0])) and info == first[1]
     ctx.close()
+
+
+def test_bits_do_not_depend_on_free_memory():
+    """Twelve bases of 1001 vectors (61 GB), with the card empty, with two fifths of it
+    taken, and with too little left for all twelve (then solved in two halves, whose sums
+    are cut otherwise: equal to rounding)."""
+    ctx = setup(100, 100, 3)
+    a0 = rhs(ctx, 12, 3)
+
+    def solve():
+        s, info = ctx.solve(a0, tol=1e-30, restart=1000, max_iter=25)
+        assert all(i["iters"] == 25 and i["status"] == tmhip.TM_NOT_CONVERGED for i in info)
+        return s
+
+    ref = solve()
+    hold = torch.empty(torch.cuda.mem_get_info()[1] * 2 // 5, dtype=torch.uint8, device=DEV)
+    assert torch.equal(torch.view_as_real(solve()), torch.view_as_real(ref))
+    del hold
+    torch.cuda.empty_cache()
+    hold = torch.empty(torch.cuda.mem_get_info()[0] - (44 << 30), dtype=torch.uint8, device=DEV)
+    s = solve()
+    del hold
+    torch.cuda.empty_cache()
+    assert float(torch.linalg.vector_norm(s - ref)) < 1e-11 * float(torch.linalg.vector_norm(ref))
+    ctx.close()
