@@ -234,13 +234,15 @@ __global__ void set_t_kernel(const tm_c128* __restrict__ t, int N, SlotMaps mp,
 // (modes 0, 2) or x (mode 1, where x's pads are 0).
 __global__ void tdense_kernel(const tm_c128* __restrict__ T, SlotMaps mp, long long N, int mode,
                               const c128* __restrict__ x, const c128* __restrict__ z,
-                              c128* __restrict__ y, long long total) {
+                              c128* __restrict__ y, long long total,
+                              const int* __restrict__ stop, const int* __restrict__ active) {
   const long long e = (long long)blockIdx.x * blockDim.x + threadIdx.x;
   if (e >= total) return;
   const int slot = (int)(e % mp.S);
   const long long site = (e / mp.S) % N;
   const long long rc = e / (mp.S * N);
   const long long r = rc / NCLASS;
+  if ((stop && *stop) || (active && !active[r])) return;  // as the products
   const int c = (int)(rc % NCLASS);
   const int n = mp.n_of[c][slot];
   const int L = mp.L;
@@ -299,13 +301,15 @@ __global__ void tdense_mpack_kernel(const tm_c128* __restrict__ T, MbMaps mb, in
 // block in increasing n), reading nm_b instead of L entries per output.
 __global__ void tdense_mb_kernel(const c128* __restrict__ Tm, MbMaps mb, SlotMaps mp, long long N,
                                  int mode, const c128* __restrict__ x, const c128* __restrict__ z,
-                                 c128* __restrict__ y, long long total) {
+                                 c128* __restrict__ y, long long total, const int* __restrict__ stop,
+                                 const int* __restrict__ active) {
   const long long e = (long long)blockIdx.x * blockDim.x + threadIdx.x;
   if (e >= total) return;
   const int slot = (int)(e % mp.S);
   const long long site = (e / mp.S) % N;
   const long long rc = e / (mp.S * N);
   const long long r = rc / NCLASS;
+  if ((stop && *stop) || (active && !active[r])) return;  // as the products
   const int c = (int)(rc % NCLASS);
   const int n = mp.n_of[c][slot];
   double ar = 0.0, ai = 0.0;
@@ -1755,10 +1759,11 @@ int launch_tdense(tm_ctx* c, int R, int mode, const c128* x, const c128* z, c128
   if (c->t_mblock)
     hipLaunchKernelGGL(tdense_mb_kernel, dim3(nblk(total)), dim3(256), 0, c->stream,
                        (const c128*)c->tmb.p, c->mbmaps, c->maps, (long long)g.n, mode, x, z, y,
-                       total);
+                       total, c->mv_stop, c->mv_active);
   else
     hipLaunchKernelGGL(tdense_kernel, dim3(nblk(total)), dim3(256), 0, c->stream,
-                       (const tm_c128*)c->tden.p, c->maps, (long long)g.n, mode, x, z, y, total);
+                       (const tm_c128*)c->tden.p, c->maps, (long long)g.n, mode, x, z, y, total,
+                       c->mv_stop, c->mv_active);
   TM_HIP(c, hipGetLastError());
   return TM_OK;
 }

@@ -87,6 +87,7 @@ struct MvArgs {
   int nx, ny, tnx, tny;
   int tiles_x, R;
   long long n_sites;
+  const int *active, *done;  // as LdsArgs
 };
 
 template <typename T>
@@ -136,6 +137,7 @@ __global__ __launch_bounds__(256, OCC) void block_matvec_kernel(MvArgs a) {
   const MvItem it = a.items[blockIdx.x];
   const int rc = blockIdx.y;
   const int r = rc >> 1, c = rc & 1;
+  if ((a.done && *a.done) || (a.active && !a.active[r])) return;
   const int X0 = (it.tile % a.tiles_x) * 16;
   const int Y0 = (it.tile / a.tiles_x) * 16;
   const int nx = a.nx, ny = a.ny;
@@ -274,12 +276,15 @@ template <typename T>
 __global__ void combine_kernel(const cplx<T>* __restrict__ partial, const int* __restrict__ ibeg,
                                int R, int nx, int tiles_x, long long N,
                                const c128* __restrict__ x, const c128* __restrict__ t,
-                               c128* __restrict__ y, long long vec, long long total, int mode) {
+                               c128* __restrict__ y, long long vec, long long total, int mode,
+                               const int* __restrict__ stop, const int* __restrict__ active) {
+  if (stop && *stop) return;
   const long long idx = (long long)blockIdx.x * blockDim.x + threadIdx.x;
   if (idx >= total) return;
   const int slot = (int)(idx % SLOTS);
   const long long site = (idx / SLOTS) % N;
   const int rc = (int)(idx / (SLOTS * N));  // r*2 + c
+  if (active && !active[rc >> 1]) return;
   const int sx = (int)(site % nx), sy = (int)(site / nx);
   const int tile = (sy >> 4) * tiles_x + (sx >> 4);
   const int ls = ((sy & 15) << 4) + (sx & 15);
@@ -515,6 +520,8 @@ static int apply_impl(tm_ctx* c, Op op, int R, const c128* x, c128* y) {
   a.tiles_x = tiles_x;
   a.R = R;
   a.n_sites = g.n;
+  a.active = c->mv_active;
+  a.done = c->mv_stop;
   hipEvent_t e0 = nullptr, e1 = nullptr;
   if (c->prof) {
     TM_HIP(c, hipEventCreate(&e0));
@@ -531,7 +538,8 @@ static int apply_impl(tm_ctx* c, Op op, int R, const c128* x, c128* y) {
   const int nb = (int)((total + 255) / 256);
   hipLaunchKernelGGL(combine_kernel<T>, dim3(nb), dim3(256), 0, c->stream,
                      (const cplx<T>*)c->partial.p, (const int*)c->plan_ibeg[which].p, R, g.nx, tiles_x,
-                     (long long)g.n, x, (const c128*)c->t64.p, y, vec, total, (int)op);
+                     (long long)g.n, x, (const c128*)c->t64.p, y, vec, total, (int)op, c->mv_stop,
+                     c->mv_active);
   TM_HIP(c, hipGetLastError());
   return TM_OK;
 }

@@ -76,7 +76,8 @@ struct LdsArgs {
   long long n_sites;
   // batched subregions (null for one lattice): per-subregion lattice and the
   // offset of its [R][2][N_k][16] block in the packed vector; a system
-  // (subregion, rhs) whose flag is 0 is skipped; a nonzero *done skips all
+  // (subregion, rhs) whose flag is 0 is skipped (one lattice is subregion 0);
+  // a nonzero *done skips all
   const SubParams* subs;
   const int* active;
   const int* done;
@@ -177,11 +178,11 @@ __global__ __launch_bounds__(256, 2) void block_matvec_lds_kernel(LdsArgs a) {
   const int NG = a.NG, S = a.S;
   const int gg = rc % NG;
   const int r = (rc / NG) >> 1, c = (rc / NG) & 1;
+  if (a.active && !a.active[it.sub * a.R + r]) return;
   int nx = a.nx, ny = a.ny, tiles_x = a.tiles_x;
   size_t N = (size_t)a.n_sites, voff = 0;
   if (a.subs) {
     const SubParams sp = a.subs[it.sub];
-    if (a.active && !a.active[it.sub * a.R + r]) return;
     nx = sp.nx;
     ny = sp.ny;
     tiles_x = sp.tiles_x;
@@ -419,14 +420,17 @@ __global__ void lds_combine_kernel(const cplx<T>* __restrict__ partial, const in
                                    int R, int nx, LdsTiling tl, long long N,
                                    const c128* __restrict__ x, const c128* __restrict__ t,
                                    c128* __restrict__ y, long long vec, long long total, int mode,
-                                   int S, int NG, const int* __restrict__ stop) {
+                                   int S, int NG, const int* __restrict__ stop,
+                                   const int* __restrict__ active) {
   if (stop && *stop) return;
   const long long idx = (long long)blockIdx.x * blockDim.x + threadIdx.x;
   if (idx >= total) return;
   const int sl = (int)(idx % S);
   const long long site = (idx / S) % N;
   // partial-sum row: ((r * 2 + c) * NG + slot group), slot within the group
-  const int rc = (int)(idx / (S * N)) * NG + sl / SLOTS;
+  const int rcls = (int)(idx / (S * N));
+  if (active && !active[rcls / NCLASS]) return;
+  const int rc = rcls * NG + sl / SLOTS;
   const int slot = sl % SLOTS;
   const int sx = (int)(site % nx), sy = (int)(site / nx);
   const int TW = tl.TW;
@@ -576,8 +580,8 @@ int lds_apply(tm_ctx* c, int which, int R, const void* table, const void* xin, c
   a.R = R;
   a.n_sites = g.n;
   a.subs = nullptr;
-  a.active = nullptr;
-  a.done = c->mv_stop;  // a stopped GMRES cycle skips its remaining matvecs
+  a.active = c->mv_active;  // right-hand sides that have left a GMRES cycle are skipped,
+  a.done = c->mv_stop;      // and the remaining matvecs of a stopped one
   a.y_base = 0;
   a.tile_base = 0;
   a.item_base = 0;
@@ -623,7 +627,7 @@ int lds_apply(tm_ctx* c, int which, int R, const void* table, const void* xin, c
     hipLaunchKernelGGL(lds_combine_kernel<T>, dim3(nb), dim3(256), 0, c->stream,
                        (const cplx<T>*)c->partial.p, (const int*)c->plan_ibeg[which].p, R, g.nx, tl,
                        (long long)g.n, x, (const c128*)c->t64.p, y, vec, total, op, g.S, g.NG,
-                       c->mv_stop);
+                       c->mv_stop, c->mv_active);
   }
   TM_HIP(c, hipGetLastError());
   return TM_OK;
@@ -740,7 +744,7 @@ int lds_apply_fixed(tm_ctx* c, int R, const void* table, const void* xin, const 
   const long long vec = g.vec_len(), total = vec * R;
   hipLaunchKernelGGL(lds_combine_kernel<T>, dim3((int)((total + 255) / 256)), dim3(256), 0, c->stream,
                      (const cplx<T>*)partial, (const int*)ibeg, R, g.nx, tl, (long long)g.n, x,
-                     (const c128*)c->t64.p, y, vec, total, op, g.S, g.NG, (const int*)nullptr);
+                     (const c128*)c->t64.p, y, vec, total, op, g.S, g.NG, (const int*)nullptr, (const int*)nullptr);
   TM_HIP(c, hipGetLastError());
   return TM_OK;
 }

@@ -509,9 +509,11 @@ __device__ __forceinline__ void ol_body(const double* __restrict__ xy, const cpl
 template <typename T, int LMAX, bool TR>
 __global__ __launch_bounds__((OlCfg<T, LMAX>::THREADS), 2) void offlattice_kernel(
     const double* __restrict__ xy, const cplx<T>* __restrict__ x, int N, double k, int chunk,
-    unsigned long long pm0, unsigned long long pm1, cplx<T>* __restrict__ partial, const int* __restrict__ stop) {
+    unsigned long long pm0, unsigned long long pm1, cplx<T>* __restrict__ partial, const int* __restrict__ stop,
+    const int* __restrict__ active) {
   constexpr int NH = LMAX * (LMAX + 2), S = 16 * ((NH + 15) / 16);
-  if (stop && *stop) return;  // a stopped GMRES cycle
+  // a stopped GMRES cycle, a right-hand side that has left it
+  if ((stop && *stop) || (active && !active[OlCfg<T, LMAX>::BOTH ? blockIdx.y : blockIdx.y >> 1])) return;
   extern __shared__ __align__(16) unsigned char ol_lds[];
   const int s0 = blockIdx.z * chunk, s1 = min(N, s0 + chunk);
   const size_t one = (size_t)2 * N * S;
@@ -536,11 +538,13 @@ template <typename T>
 __global__ void offlattice_combine_kernel(const cplx<T>* __restrict__ partial, int nchunk,
                                           long long total, const c128* __restrict__ x,
                                           const c128* __restrict__ t, long long vec,
-                                          c128* __restrict__ y, int mode, const int* __restrict__ stop) {
+                                          c128* __restrict__ y, int mode, const int* __restrict__ stop,
+                                          const int* __restrict__ active) {
   if (stop && *stop) return;
   const long long e = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (e >= total) return;
+  if (e >= total || (active && !active[e / vec])) return;
   double sr = 0.0, si = 0.0;
+#pragma unroll 8
   for (int q = 0; q < nchunk; ++q) {
     const cplx<T> v = partial[(size_t)q * total + e];
     sr += (double)v.re;
@@ -571,9 +575,13 @@ static int ol_launch(tm_ctx* c, bool tr, int R, int& nchunk, const void* xin, un
   const Geometry& g = c->g;
   const int N = g.n;
   // about 1500 waves (the chip's 1024 SIMDs with some to spare), at least 8
-  // sources each so that the sums' way through LDS and memory stays small
-  const int tb = (N + OL_TARGETS - 1) / OL_TARGETS, gy = R * (3 - NC), W = Cfg::WAVES;
-  nchunk = std::max(1, std::min((N + 8 * W - 1) / (8 * W), 1536 / (W * tb * gy) + 1));
+  // sources each so that the sums' way through LDS and memory stays small.  For each
+  // right-hand side, as the others may have left the solve (512 MB of partial sums at
+  // most), else for all together.
+  const int tb = (N + OL_TARGETS - 1) / OL_TARGETS, gy = 3 - NC, W = Cfg::WAVES;
+  auto chunks = [&](int rows) { return std::max(1, std::min((N + 8 * W - 1) / (8 * W), 1536 / (W * tb * rows) + 1)); };
+  const size_t one = (size_t)g.vec_len() * R * sizeof(cplx<T>);
+  nchunk = std::max<int>(chunks(gy * R), (int)std::min<size_t>(chunks(gy), ((size_t)512 << 20) / one));
   const int chunk = (N + nchunk - 1) / nchunk;
   nchunk = (N + chunk - 1) / chunk;
   int rc;
@@ -585,8 +593,8 @@ static int ol_launch(tm_ctx* c, bool tr, int R, int& nchunk, const void* xin, un
   cplx<T>* partial = (cplx<T>*)c->partial.p;
   double k = g.k;
   int n = N, ch = chunk;
-  void* args[] = {&xy, &x, &n, &k, &ch, &pm0, &pm1, &partial, &c->mv_stop};
-  TM_HIP(c, hipLaunchKernel(f, dim3(tb, gy, nchunk), dim3(Cfg::THREADS), args, lds, c->stream));
+  void* args[] = {&xy, &x, &n, &k, &ch, &pm0, &pm1, &partial, &c->mv_stop, &c->mv_active};
+  TM_HIP(c, hipLaunchKernel(f, dim3(tb, gy * R, nchunk), dim3(Cfg::THREADS), args, lds, c->stream));
   return TM_OK;
 }
 
@@ -611,7 +619,7 @@ int offlattice_apply(tm_ctx* c, Op op, int R, const void* xin, const c128* x, c1
   if (rc != TM_OK) return rc;
   hipLaunchKernelGGL(offlattice_combine_kernel<T>, dim3((unsigned)((total + 255) / 256)), dim3(256), 0,
                      c->stream, (const cplx<T>*)c->partial.p, nchunk, total, x, (const c128*)c->t64.p,
-                     g.vec_len(), y, (int)op, c->mv_stop);
+                     g.vec_len(), y, (int)op, c->mv_stop, c->mv_active);
   TM_HIP(c, hipGetLastError());
   return TM_OK;
 }

@@ -69,3 +69,46 @@ def test_bits_do_not_depend_on_free_memory():
     torch.cuda.empty_cache()
     assert float(torch.linalg.vector_norm(s - ref)) < 1e-11 * float(torch.linalg.vector_norm(ref))
     ctx.close()
+
+
+@pytest.mark.parametrize("product", ["staged", "direct", "pairwise", "dense"])
+@pytest.mark.parametrize("precision", ["fp64", "mixed"])
+def test_solved_right_hand_sides_cost_no_product(product, precision):
+    """One right-hand side of four is not zero: the products of a solve take what its own
+    would, and not four times that (twice, at most), and the solution is its own."""
+    n, lmax = 48, 3
+    print(f"[case] {product} {precision}", flush=True)
+    pos = wl.lattice_positions(n, n)
+    if product == "pairwise":
+        pos[:, :2] += np.random.default_rng(1).uniform(-0.03, 0.03, (n * n, 2))
+    ctx = tmhip.Context(0)
+    ctx.set_geometry(pos, wl.K, lmax)
+    ctx.set_spheres(torch.full((n * n,), 0.17, dtype=torch.float64, device=DEV), wl.N_REL)
+    if product == "dense":
+        ctx.set_tmatrix_dense(torch.diag_embed(ctx.get_tmatrix_diag()[0]).contiguous())
+    if product != "pairwise":
+        for prec in ("fp64", "mixed"):
+            ctx.set_matvec_config(prec, 3 if product == "direct" else 8, 0)
+    one = rhs(ctx, 1, 5)
+    four = torch.zeros(4, ctx.n, ctx.L, dtype=torch.complex128, device=DEV)
+    four[2] = one[0]
+
+    def timed(a0):
+        ms = []
+        for _ in range(3):
+            e = [torch.cuda.Event(enable_timing=True) for _ in range(2)]
+            e[0].record()
+            s, info = ctx.solve(a0, tol=1e-10, precision=precision)
+            e[1].record()
+            e[1].synchronize()
+            ms.append(e[0].elapsed_time(e[1]))
+        return s, info, min(ms)
+
+    s1, i1, t1 = timed(one)
+    s4, i4, t4 = timed(four)
+    print(f"[info] {t1:.2f} ms alone, {t4:.2f} ms of four", flush=True)
+    assert i1[0]["status"] == 0 and [i["status"] for i in i4] == [0] * 4
+    assert float(torch.linalg.vector_norm(s4[2] - s1[0])) < 1e-7 * float(torch.linalg.vector_norm(s1[0]))
+    assert float(s4[[0, 1, 3]].abs().max()) == 0.0
+    assert t4 < 2.0 * t1
+    ctx.close()
