@@ -411,9 +411,14 @@ int tm_grad_position(tm_ctx* ctx, int n_rhs, const tm_c128* mu, const tm_c128* s
 /* The product with A runs by Fourier transform of the lattice by default,
  * where a lattice fits it (a row of at most 320 sites, and a column of
  * coefficients in LDS: 300 sites to lmax 3, 150 at lmax 4, 100 above in FP64; 320,
- * 300, 200 in complex64); else by the block kernels below, which this call
- * also selects for its precision.
- * Kernel variant and work split of the block matvec for one precision.
+ * 300, 200 in complex64); else by the block kernels below.
+ * items >= 0 selects the block kernels, with a variant and work split, for one
+ * precision: for its products, its position gradients (FP64) and its batched
+ * solves, on lattices of the current size (or of the first geometry, before
+ * one is set); a lattice of other dimensions or lmax starts with the
+ * transformed product again.  items < 0 selects the transformed product where
+ * a lattice fits it, and variant with -1 - items work items elsewhere.  What
+ * tm_get_matvec_config returns selects the same again.
  * variant 0..7 (operands read from global memory): bit 0 = complex products
  * from three real matrix-core products (else four), bit 1 = operands of the
  * next displacement loaded during the current one's products, bit 2 =
@@ -422,19 +427,20 @@ int tm_grad_position(tm_ctx* ctx, int n_rhs, const tm_c128* mu, const tm_c128* s
  * fetched 1, 2, 3 displacements ahead (FP64 runs variant 10 as 9: depth 3
  * does not fit its register budget), with 4-row "wide" tiles for rows past
  * the last multiple of 16.  items: target work items per (rhs, class) pair,
- * 0 = default.  All variants compute the same product.  Variants 0..7 are
- * written for lmax <= 3 (one 16-slot group per z-mirror class); at lmax 4..6
- * a request for them runs the LDS-staged kernel (variant 9 FP64, 10
- * complex64) instead. */
+ * 0 = default (-1 the same, under the transformed product).  All variants
+ * compute the same product.  Variants 0..7 are written for lmax <= 3 (one
+ * 16-slot group per z-mirror class); at lmax 4..6 a request for them runs the
+ * LDS-staged kernel (variant 9 FP64, 10 complex64) instead. */
 int tm_set_matvec_config(tm_ctx* ctx, int precision, int variant, int items);
 int tm_get_matvec_config(tm_ctx* ctx, int precision, int* variant, int* items);
 
 /* Time the LDS-staged variants (8..10; FP64: 8, 9) with a few work-item
  * counts (4k..64k workgroups) on the current geometry for n_rhs right-hand
  * sides, and the transformed product where the lattice fits it, and keep the
- * fastest for `precision`.  Synchronises; best_ms (host, nullable) receives
- * the best time of a product.  Without a call, FP64 uses
- * variant 9 and complex64 variant 8 with the default work split. */
+ * fastest for `precision` on lattices of this size; a failed call changes
+ * nothing.  Synchronises; best_ms (host, nullable) receives the best time of a
+ * product.  Without a call, FP64 uses variant 9 and complex64 variant 8 with
+ * the default work split where the transformed product does not fit. */
 int tm_autotune(tm_ctx* ctx, int n_rhs, int precision, double* best_ms);
 
 /* ---- progress ------------------------------------------------------------- */

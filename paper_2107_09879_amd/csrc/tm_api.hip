@@ -210,6 +210,8 @@ int tm_set_geometry(tm_ctx* c, int n, const double* pos, double k, int lmax) {
                             "scatterer " + std::to_string(i) + " is off the z = 0 plane");
   }
   tmh::Geometry& g = c->g;
+  // the choice of block kernels holds for the lattice size it was made (or timed) on
+  if (g.n && (g.lattice != lattice || g.nx != nx || g.ny != ny || g.lmax != lmax)) c->mv_block[0] = c->mv_block[1] = false;
   g = tmh::Geometry{};
   g.n = n;
   g.lattice = lattice;
@@ -830,13 +832,12 @@ int tm_grad_radius(tm_ctx* c, int R, const tm_c128* mu, const tm_c128* s, const 
 
 int tm_set_matvec_config(tm_ctx* c, int precision, int variant, int items) {
   CHECK_CTX(c);
-  if ((precision != TM_PREC_FP64 && precision != TM_PREC_MIXED) || variant < 0 || variant > 10 ||
-      items < 0)
+  if ((precision != TM_PREC_FP64 && precision != TM_PREC_MIXED) || variant < 0 || variant > 10)
     return tmh::set_err(c, TM_ERR_INVALID_ARG, "bad matvec configuration");
   const int w = precision == TM_PREC_MIXED ? 1 : 0;
   c->mv_variant[w] = variant;
-  c->mv_items[w] = items;
-  c->mv_block[w] = true;
+  c->mv_items[w] = items < 0 ? -1 - items : items;
+  c->mv_block[w] = items >= 0;
   return TM_OK;
 }
 
@@ -846,7 +847,7 @@ int tm_get_matvec_config(tm_ctx* c, int precision, int* variant, int* items) {
     return tmh::set_err(c, TM_ERR_INVALID_ARG, "bad precision");
   const int w = precision == TM_PREC_MIXED ? 1 : 0;
   if (variant) *variant = c->mv_variant[w];
-  if (items) *items = c->mv_items[w];
+  if (items) *items = c->mv_block[w] ? c->mv_items[w] : -1 - c->mv_items[w];
   return TM_OK;
 }
 

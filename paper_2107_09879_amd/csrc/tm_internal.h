@@ -180,7 +180,7 @@ struct tm_ctx {
   // transformed block matvec, the default where the lattice fits it: symbol and
   // tables of the geometry (built on first use), grid workspace, constants of
   // lmax; per precision slot whether it fits, and whether tm_set_matvec_config
-  // or tm_autotune asked for the block kernels instead
+  // or tm_autotune asked for the block kernels instead (for this lattice size)
   tmh::DevBuf spec_sym, spec_w, spec_const, spec_d;  // spec_d: derivatives' symbols
   tmh::SpecPlan spec;
   bool have_spec = false, have_spec_d = false, spec_known = false, spec_fit[2] = {false, false}, mv_block[2] = {false, false};

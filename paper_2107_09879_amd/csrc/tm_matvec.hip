@@ -547,7 +547,7 @@ static int apply_impl(tm_ctx* c, Op op, int R, const c128* x, c128* y) {
 // Autotuner: time every kernel variant with a few work-item counts on the
 // current geometry for R right-hand sides; keep the fastest per precision.
 template <typename T>
-static int autotune_impl(tm_ctx* c, int R, double* best_ms) {
+static int autotune_timed(tm_ctx* c, int R, hipEvent_t e0, hipEvent_t e1, double* best_ms) {
   const Geometry& g = c->g;
   const int which = std::is_same<T, double>::value ? 0 : 1;
   const long long total = g.vec_len() * R;
@@ -557,9 +557,6 @@ static int autotune_impl(tm_ctx* c, int R, double* best_ms) {
   // workgroup counts (items x 2R); smaller equal-work items keep every CU
   // busy to the end of the launch, at the price of more partial sums
   const int wg_targets[] = {4096, 8192, 16384, 32768, 65536};
-  hipEvent_t e0, e1;
-  TM_HIP(c, hipEventCreate(&e0));
-  TM_HIP(c, hipEventCreate(&e1));
   double best = 1e300;
   int bv = c->mv_variant[which], bi = c->mv_items[which];
   // only the LDS-staged variants: the direct kernels (0..7) never won at any
@@ -590,8 +587,8 @@ static int autotune_impl(tm_ctx* c, int R, double* best_ms) {
   }
   c->mv_variant[which] = bv;
   c->mv_items[which] = bi;
-  // the transformed product stays unless the block kernels beat it
-  c->mv_block[which] = true;
+  // the transformed product where the lattice fits it, unless the block kernels beat it
+  bool block = false;
   if (spec_use(c, which)) {
     const size_t vb = (size_t)total * sizeof(c128);
     if ((rc = ensure(c, c->work_a, vb)) != TM_OK || (rc = ensure(c, c->work_b, vb)) != TM_OK) return rc;
@@ -607,13 +604,31 @@ static int autotune_impl(tm_ctx* c, int R, double* best_ms) {
       TM_HIP(c, hipEventElapsedTime(&ms, e0, e1));
       if (rep > 0) tmin = std::min(tmin, (double)ms);
     }
-    c->mv_block[which] = best < tmin;
+    block = best < tmin;
     best = std::min(best, tmin);
   }
-  hipEventDestroy(e0);
-  hipEventDestroy(e1);
+  c->mv_block[which] = block;
   if (best_ms) *best_ms = best;
   return TM_OK;
+}
+// A failed call leaves the configuration as it was.
+template <typename T>
+static int autotune_impl(tm_ctx* c, int R, double* best_ms) {
+  const int which = std::is_same<T, double>::value ? 0 : 1;
+  const int variant = c->mv_variant[which], items = c->mv_items[which];
+  hipEvent_t e0 = nullptr, e1 = nullptr;
+  int rc;
+  if (hipEventCreate(&e0) == hipSuccess && hipEventCreate(&e1) == hipSuccess)
+    rc = autotune_timed<T>(c, R, e0, e1, best_ms);
+  else
+    rc = set_err(c, TM_ERR_HIP, "event creation for the autotuner failed");
+  if (e0) hipEventDestroy(e0);
+  if (e1) hipEventDestroy(e1);
+  if (rc != TM_OK) {
+    c->mv_variant[which] = variant;
+    c->mv_items[which] = items;
+  }
+  return rc;
 }
 
 int autotune(tm_ctx* c, int R, int prec, double* best_ms) {

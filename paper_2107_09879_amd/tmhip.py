@@ -557,9 +557,12 @@ class Context:
         return g
 
     def set_matvec_config(self, precision, variant, items=0):
+        """Block kernels of `precision` (items >= 0), or the transformed product (items < 0)."""
         self._check(self.lib.tm_set_matvec_config(self.h, PRECISIONS[precision], int(variant), int(items)))
 
     def get_matvec_config(self, precision):
+        """(variant, items) that set_matvec_config takes for the same choice; items < 0: the
+        transformed product wherever the lattice fits it."""
         v, i = ctypes.c_int(), ctypes.c_int()
         self._check(self.lib.tm_get_matvec_config(self.h, PRECISIONS[precision], ctypes.byref(v),
                                                   ctypes.byref(i)))
