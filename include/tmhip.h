@@ -339,6 +339,11 @@ int tm_get_batch_config(const tm_ctx* ctx, int precision, int* prefetch, int* it
 
 /* ---- readout ------------------------------------------------------------- */
 
+/* The near field, its transpose and the far field enqueue kernels only and can
+ * be captured into a graph, also as a context's first call; they are then not
+ * split over scatterers or points, and the graph refers to no memory but the
+ * caller's arrays and the geometry. */
+
 /* Scattered field E_sca(x) = sum_i s_i^T Phi(k(x - x_i)) (App. I.C, eq.
  * "sca_fld_concise") at points: pts device [P][3] (each outside every
  * scatterer's enclosing sphere); E device [R][P][3] complex128.

@@ -53,6 +53,13 @@ void release(DevBuf& b) {
   b.bytes = 0;
 }
 
+bool capturing(tm_ctx* c) {
+  hipStreamCaptureStatus s = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(c->stream, &s) == hipSuccess) return s == hipStreamCaptureStatusActive;
+  (void)hipGetLastError();
+  return false;
+}
+
 // Plane-wave incidences: khat unit vectors, pol finite and transverse.
 int validate_incidence(tm_ctx* c, int R, const double* khat, const tm_c128* pol) {
   for (int r = 0; r < R; ++r) {

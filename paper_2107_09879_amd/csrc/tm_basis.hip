@@ -659,17 +659,19 @@ static inline unsigned nblk(long long n, int t = 256) { return (unsigned)((n + t
 // Work split of `rows` threads over `terms` terms each: threads per workgroup
 // (no wider than the rows need) and chunks of at least `least` terms so that
 // about `want` waves run (eight per SIMD for the near field; two for its
-// transpose, whose registers allow no more and whose partial sums are long).
+// transpose, whose registers allow no more and whose partial sums are long).  One chunk
+// while the stream is being captured: a graph then holds no workspace of the context,
+// which a later call may replace.
 struct RowSplit {
   int threads, chunks, per;
   unsigned blocks;
 };
-static RowSplit row_split(long long rows, int terms, int least, long long want) {
+static RowSplit row_split(tm_ctx* c, long long rows, int terms, int least, long long want) {
   RowSplit w;
   w.threads = rows <= 64 ? 64 : rows <= 128 ? 128 : 256;
   w.blocks = nblk(rows, w.threads);
   const long long waves = (long long)w.blocks * (w.threads / 64);
-  const int most = std::max(1, (terms + least - 1) / least);
+  const int most = capturing(c) ? 1 : std::max(1, (terms + least - 1) / least);
   w.chunks = (int)std::max(1ll, std::min<long long>(most, want / waves));
   w.per = least * std::max(1, (terms + w.chunks * least - 1) / (w.chunks * least));
   w.chunks = std::max(1, (terms + w.per - 1) / w.per);
@@ -679,7 +681,7 @@ static RowSplit row_split(long long rows, int terms, int least, long long want) 
 template <typename T, int LMAX>
 static int nf_launch(tm_ctx* c, int R, const tm_c128* s, const double* pts, int P, tm_c128* E) {
   const Geometry& g = c->g;
-  const RowSplit w = row_split(P, g.n, NfChunk<LMAX>::N, 8192);
+  const RowSplit w = row_split(c, P, g.n, NfChunk<LMAX>::N, 8192);
   const long long total = (long long)R * P * 3;
   int rc;
   if (w.chunks > 1 && (rc = ensure(c, c->partial, (size_t)w.chunks * total * sizeof(cx<T>))) != TM_OK) return rc;
@@ -718,14 +720,66 @@ static int nf_dispatch(tm_ctx* c, int R, const tm_c128* s, const double* pts, in
 // (blockIdx.y; four directions over 22500 scatterers were four workgroups, 760 us,
 // now 30 us), sums
 // c_n = sum_i e^{-ik d.x_i} s_{i,n} per thread, then a fixed-order wave + LDS
-// reduction into part [chunk][rhs, direction][L].
+// reduction, into F when there is one chunk, else into part [chunk][rhs, direction][L].
 constexpr int FF_THREADS = 256;
+
+// F of direction u from the sums c = (a, b) of coefficient n in thread n; ft, fp: [L]
+__device__ inline void far_sum_up(int n, double a, double b, int L, int lmax, double k, const double* __restrict__ u,
+                                  cplx<double>* ft, cplx<double>* fp, tm_c128* __restrict__ F) {
+  const double ux = u[0], uy = u[1];
+  const double rho = sqrt(ux * ux + uy * uy);
+  const double ct = u[2], st = rho;
+  double cf = 1.0, sf = 0.0;
+  if (rho > 0.0) {
+    cf = ux / rho;
+    sf = uy / rho;
+  }
+  if (n < L) {
+    int p, l, m;
+    plm_of_n(n, lmax, p, l, m);
+    double Pb, U, tau;
+    legendre_one<double>(l, m < 0 ? -m : m, ct, st, Pb, U, tau);
+    const double pi = (double)m * U;
+    double sm, cm;
+    sincos((double)m * atan2(sf, cf), &sm, &cm);
+    const cx<double> em(cm, sm);
+    const double nrm = 1.0 / sqrt(2.0 * l * (l + 1));
+    const cx<double> c = nrm * (cx<double>(a, b) * em);
+    if (p == 0) {
+      const cx<double> f = ipow<double>(-(l + 1)) * c;  // (-i)^{l+1} = i^{-(l+1)}
+      const cx<double> t = mul_i(pi * f), q = (-tau) * f;
+      ft[n] = cplx<double>{t.re, t.im};
+      fp[n] = cplx<double>{q.re, q.im};
+    } else {
+      const cx<double> f = ipow<double>(-l) * c;
+      const cx<double> t = tau * f, q = mul_i(pi * f);
+      ft[n] = cplx<double>{t.re, t.im};
+      fp[n] = cplx<double>{q.re, q.im};
+    }
+  }
+  __syncthreads();
+  if (n) return;
+  cx<double> Ft, Fp;
+  for (int q = 0; q < L; ++q) {
+    Ft = Ft + cx<double>(ft[q].re, ft[q].im);
+    Fp = Fp + cx<double>(fp[q].re, fp[q].im);
+  }
+  const double ik = 1.0 / k;
+  const cx<double> Fx = ik * ((ct * cf) * Ft - sf * Fp);
+  const cx<double> Fy = ik * ((ct * sf) * Ft + cf * Fp);
+  const cx<double> Fz = ik * ((-st) * Ft);
+  F[0] = tm_c128{Fx.re, Fx.im};
+  F[1] = tm_c128{Fy.re, Fy.im};
+  F[2] = tm_c128{Fz.re, Fz.im};
+}
+
 template <int LMAXT>
 __global__ __launch_bounds__(FF_THREADS) void far_sums_kernel(
     const tm_c128* __restrict__ s, int N, int per, SitePos sp, double k,
-    const double* __restrict__ dirs, int D, c128* __restrict__ part) {
+    const double* __restrict__ dirs, int D, c128* __restrict__ part, tm_c128* __restrict__ F) {
   constexpr int L = 2 * LMAXT * (LMAXT + 2);
   __shared__ double red[FF_THREADS / 64][2 * L];
+  __shared__ cplx<double> ft[L], fp[L];
   const int e = blockIdx.x;
   const int r = e / D, id = e % D;
   const double ux = dirs[3 * id], uy = dirs[3 * id + 1];
@@ -760,6 +814,17 @@ __global__ __launch_bounds__(FF_THREADS) void far_sums_kernel(
     }
   }
   __syncthreads();
+  if (gridDim.y == 1) {
+    const int n = threadIdx.x;
+    double a = 0.0, b = 0.0;
+    if (n < L)
+      for (int x = 0; x < FF_THREADS / 64; ++x) {
+        a += red[x][2 * n];
+        b += red[x][2 * n + 1];
+      }
+    far_sum_up(n, a, b, L, LMAXT, k, dirs + 3 * id, ft, fp, F + (size_t)e * 3);
+    return;
+  }
   double* out = (double*)(part + ((size_t)blockIdx.y * gridDim.x + e) * L);
   for (int q = threadIdx.x; q < 2 * L; q += FF_THREADS) {
     double v = red[0][q];
@@ -767,64 +832,20 @@ __global__ __launch_bounds__(FF_THREADS) void far_sums_kernel(
     out[q] = v;
   }
 }
-// The far field of every (rhs, direction): one workgroup of 128, a coefficient
-// per thread.
+// The far field from several chunks' sums: one workgroup of 128 per (rhs, direction).
 __global__ __launch_bounds__(128) void far_field_kernel(const c128* __restrict__ part, int chunks, int L, int lmax,
                                                         double k, const double* __restrict__ dirs, int D,
                                                         tm_c128* __restrict__ F) {
   __shared__ cplx<double> ft[LM_MAX], fp[LM_MAX];
-  const int e = blockIdx.x, id = e % D, n = threadIdx.x;
-  const double ux = dirs[3 * id], uy = dirs[3 * id + 1], uz = dirs[3 * id + 2];
-  const double rho = sqrt(ux * ux + uy * uy);
-  const double ct = uz, st = rho;
-  double cf = 1.0, sf = 0.0;
-  if (rho > 0.0) {
-    cf = ux / rho;
-    sf = uy / rho;
-  }
-  if (n < L) {
-    double a = 0.0, b = 0.0;
+  const int e = blockIdx.x, n = threadIdx.x;
+  double a = 0.0, b = 0.0;
+  if (n < L)
     for (int q = 0; q < chunks; ++q) {
       const c128 v = part[((size_t)q * gridDim.x + e) * L + n];
       a += v.re;
       b += v.im;
     }
-    int p, l, m;
-    plm_of_n(n, lmax, p, l, m);
-    double Pb, U, tau;
-    legendre_one<double>(l, m < 0 ? -m : m, ct, st, Pb, U, tau);
-    const double pi = (double)m * U;
-    double sm, cm;
-    sincos((double)m * atan2(sf, cf), &sm, &cm);
-    const cx<double> em(cm, sm);
-    const double nrm = 1.0 / sqrt(2.0 * l * (l + 1));
-    const cx<double> c = nrm * (cx<double>(a, b) * em);
-    if (p == 0) {
-      const cx<double> f = ipow<double>(-(l + 1)) * c;  // (-i)^{l+1} = i^{-(l+1)}
-      const cx<double> u = mul_i(pi * f), q = (-tau) * f;
-      ft[n] = cplx<double>{u.re, u.im};
-      fp[n] = cplx<double>{q.re, q.im};
-    } else {
-      const cx<double> f = ipow<double>(-l) * c;
-      const cx<double> u = tau * f, q = mul_i(pi * f);
-      ft[n] = cplx<double>{u.re, u.im};
-      fp[n] = cplx<double>{q.re, q.im};
-    }
-  }
-  __syncthreads();
-  if (n) return;
-  cx<double> Ft, Fp;
-  for (int q = 0; q < L; ++q) {
-    Ft = Ft + cx<double>(ft[q].re, ft[q].im);
-    Fp = Fp + cx<double>(fp[q].re, fp[q].im);
-  }
-  const double ik = 1.0 / k;
-  const cx<double> Fx = ik * ((ct * cf) * Ft - sf * Fp);
-  const cx<double> Fy = ik * ((ct * sf) * Ft + cf * Fp);
-  const cx<double> Fz = ik * ((-st) * Ft);
-  F[(size_t)e * 3 + 0] = tm_c128{Fx.re, Fx.im};
-  F[(size_t)e * 3 + 1] = tm_c128{Fy.re, Fy.im};
-  F[(size_t)e * 3 + 2] = tm_c128{Fz.re, Fz.im};
+  far_sum_up(n, a, b, L, lmax, k, dirs + 3 * (e % D), ft, fp, F + (size_t)e * 3);
 }
 
 // v[i][n] = sum_c w_c Phi_n(k(xd - x_i))_c
@@ -1852,17 +1873,19 @@ int launch_near_field(tm_ctx* c, int R, const tm_c128* s, int P, const double* p
 
 int launch_far_field(tm_ctx* c, int R, const tm_c128* s, int D, const double* dirs, tm_c128* F) {
   const Geometry& g = c->g;
-  // about 1024 workgroups, at least one scatterer per thread
+  // about 1024 workgroups, at least one scatterer per thread; the chunks' sums take
+  // 1.6 MB at most
   const long long E = (long long)R * D;
   int chunks = (int)std::max(1ll, std::min<long long>((g.n + FF_THREADS - 1) / FF_THREADS, 1024 / E));
+  if (capturing(c)) chunks = 1;
   const int per = (g.n + chunks - 1) / chunks;
   chunks = (g.n + per - 1) / per;
   int rc;
-  if ((rc = ensure(c, c->partial, (size_t)chunks * E * g.L * sizeof(c128))) != TM_OK) return rc;
+  if (chunks > 1 && (rc = ensure(c, c->partial, (size_t)chunks * E * g.L * sizeof(c128))) != TM_OK) return rc;
   c128* part = (c128*)c->partial.p;
 #define FF_LAUNCH(LM)                                                                                            \
   hipLaunchKernelGGL(far_sums_kernel<LM>, dim3((unsigned)E, chunks), dim3(FF_THREADS), 0, c->stream, s, g.n, per, \
-                     site_pos(c), g.k, dirs, D, part)
+                     site_pos(c), g.k, dirs, D, part, F)
   // per-thread coefficient sums sized for the geometry's lmax
   switch (g.lmax) {
     case 1: FF_LAUNCH(1); break;
@@ -1873,8 +1896,9 @@ int launch_far_field(tm_ctx* c, int R, const tm_c128* s, int D, const double* di
     default: FF_LAUNCH(6); break;
   }
 #undef FF_LAUNCH
-  hipLaunchKernelGGL(far_field_kernel, dim3((unsigned)E), dim3(128), 0, c->stream, (const c128*)part, chunks, g.L,
-                     g.lmax, g.k, dirs, D, F);
+  if (chunks > 1)
+    hipLaunchKernelGGL(far_field_kernel, dim3((unsigned)E), dim3(128), 0, c->stream, (const c128*)part, chunks, g.L,
+                       g.lmax, g.k, dirs, D, F);
   TM_HIP(c, hipGetLastError());
   return TM_OK;
 }
@@ -1891,7 +1915,7 @@ int launch_detector(tm_ctx* c, const double* xd, const tm_c128* w, tm_c128* v) {
 template <int LMAX>
 static int nft_launch(tm_ctx* c, int R, int P, const double* pts, const tm_c128* w, tm_c128* v) {
   const Geometry& g = c->g;
-  const RowSplit q = row_split((long long)g.n * R, P, 8, 2048);
+  const RowSplit q = row_split(c, (long long)g.n * R, P, 8, 2048);
   // rows are scatterers of one right-hand side; partial sums of at most 2 GB
   const unsigned blocks = nblk(g.n, q.threads);
   const size_t one = (size_t)g.n * g.L * sizeof(c128);

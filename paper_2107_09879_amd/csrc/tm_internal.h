@@ -213,6 +213,7 @@ int set_err(tm_ctx* c, int code, const std::string& msg);
 int ensure(tm_ctx* c, DevBuf& b, size_t bytes);
 int validate_incidence(tm_ctx* c, int R, const double* khat, const tm_c128* pol);
 void release(DevBuf& b);
+bool capturing(tm_ctx* c);  // whether the context's stream is being captured
 
 // ---- launchers implemented in the .hip files ------------------------------
 // tables (tm_table.hip)
