@@ -241,8 +241,10 @@ int tm_set_geometry(tm_ctx* c, int n, const double* pos, double k, int lmax) {
     if ((rc = tmh::build_tables(c)) != TM_OK) return rc;
     c->host_xy.clear();
   } else {
-    // no displacement tables: release a previous lattice's
-    for (tmh::DevBuf* b : {&c->tab64, &c->tab32, &c->tabT64, &c->tabT32, &c->tab_work})
+    // no displacement tables or transforms: release a previous lattice's
+    c->spec_const_lmax = 0;
+    for (tmh::DevBuf* b : {&c->tab64, &c->tab32, &c->tabT64, &c->tabT32, &c->tab_work, &c->spec_sym, &c->spec_w,
+                           &c->spec_const, &c->spec_d})
       if (b->p) {
         TM_HIP(c, hipStreamSynchronize(c->stream));
         tmh::release(*b);
@@ -551,6 +553,7 @@ static int solve_common(tm_ctx* c, Op op, int R, const tm_c128* rhs, tm_c128* ou
   // callback, which reports each by itself
   int group = 1;
   if (R > 1 && !c->progress && (rc = solve_group(c, R, o->restart, group)) != TM_OK) return rc;
+  const tmh::KryTrim trim{group > 1 ? c : nullptr};
   bool all_ok = true;
   for (int r = 0, n; r < R; r += n) {
     n = std::min(group, R - r);
@@ -589,7 +592,6 @@ static int solve_common(tm_ctx* c, Op op, int R, const tm_c128* rhs, tm_c128* ou
   }
   tmh::unpack_slots(c->stream, g, c->maps, R, xsl, out);
   TM_HIP(c, hipStreamSynchronize(c->stream));
-  if (group > 1) tmh::kry_trim(c);
   return all_ok ? TM_OK : TM_NOT_CONVERGED;
 }
 

@@ -61,7 +61,13 @@ struct KryProblem {
 };
 
 int kry_solve(tm_ctx* c, KryProblem& p, tm_solve_info* info);
-// gives a basis of several systems back once it is large (the stream is idle)
+// gives the workspaces of a solve of several systems back where they are large
 void kry_trim(tm_ctx* c);
+struct KryTrim {  // at every end of a solve
+  tm_ctx* c;
+  ~KryTrim() {
+    if (c) kry_trim(c);
+  }
+};
 
 }  // namespace tmh

@@ -630,9 +630,13 @@ static int kry_pinned(tm_ctx* c, size_t bytes) {
   return TM_OK;
 }
 
-// Allocating a basis costs far less than the solve that fills one of this size.
+// Allocating a workspace costs far less than the solve that fills one of this size.
 void kry_trim(tm_ctx* c) {
-  if (c->basis.bytes > ((size_t)2 << 30)) release(c->basis);
+  for (DevBuf* b : {&c->basis, &c->kry_dev, &c->spec_w})
+    if (b->bytes > ((size_t)2 << 30)) {
+      hipStreamSynchronize(c->stream);
+      release(*b);
+    }
 }
 
 int kry_solve(tm_ctx* c, KryProblem& p, tm_solve_info* info) {

@@ -440,6 +440,7 @@ static int batched_impl(tm_ctx* c, int S, const tm_subregion* subs, int R, const
                         const tm_c128* pol, const tm_c128* a0_packed, tm_c128* s_out,
                         const tm_solve_opts& o, tm_solve_info* info, int use_graph) {
   const Geometry& g = c->g;
+  const KryTrim trim{c};
   Batch B;
   B.ctx_stream = c->stream;
   B.S = S;
@@ -555,7 +556,6 @@ static int batched_impl(tm_ctx* c, int S, const tm_subregion* subs, int R, const
   hipLaunchKernelGGL(b_unpack, dim3(nbk(ooff)), dim3(BT), 0, c->stream, (const c128*)vx, sp,
                      (const long long*)B.d_out_off.p, S, R, c->maps, ooff, s_out);
   TM_HIP(c, hipStreamSynchronize(c->stream));
-  kry_trim(c);
   bool all_ok = true;
   for (int s = 0; s < p.nsys; ++s) all_ok = all_ok && info[s].status == TM_OK;
   c->last_batch_graphed = p.graphed ? 1 : 0;

@@ -876,6 +876,7 @@ static int spec_upload_constants(tm_ctx* c) {
   std::copy(k.info.begin(), k.info.end(), reinterpret_cast<int*>(h.data() + L.info));
   std::copy(k.fields.begin(), k.fields.end(), reinterpret_cast<short2*>(h.data() + L.fields));
   int rc;
+  c->spec_const_lmax = 0;  // until the new ones are there
   if ((rc = ensure(c, c->spec_const, L.bytes)) != TM_OK) return rc;
   TM_HIP(c, hipStreamSynchronize(c->stream));  // earlier products may still read the old ones
   TM_HIP(c, hipMemcpy(c->spec_const.p, h.data(), L.bytes, hipMemcpyHostToDevice));

@@ -432,8 +432,8 @@ static const TableConst& packed_constants(const Geometry& g) {
 
 // The kernel writes at the card's copy rate (100x100 at lmax 3: 487 MB, 104 us); around
 // it five allocations, their frees, three copies and the constants' Wigner symbols
-// took longer than it, so the constants are kept per lmax and the workspace per
-// context: a new 100x100 layout with T and two right-hand
+// took longer than it, so the constants are kept per lmax and the workspace, up
+// to 64 MB, per context: a new 100x100 layout with T and two right-hand
 // sides 510 -> 245 us.
 static int build_impl(tm_ctx* c, DevBuf& t64, DevBuf& t32, int transpose) {
   const Geometry& g = c->g;
@@ -473,6 +473,7 @@ static int build_impl(tm_ctx* c, DevBuf& t64, DevBuf& t32, int transpose) {
   TM_HIP(c, hipGetLastError());
   // complete when the call returns: the next product may be on another stream
   TM_HIP(c, hipStreamSynchronize(c->stream));
+  if (c->tab_work.bytes > ((size_t)64 << 20)) release(c->tab_work);
   return TM_OK;
 }
 
