@@ -192,8 +192,9 @@ typedef struct {
   int status;          /* TM_OK or TM_NOT_CONVERGED                          */
   int iters;           /* Arnoldi steps                                      */
   int cycles;          /* restart / refinement cycles                        */
-  int matvecs_fp64;
-  int matvecs_lowp;
+  int matvecs_fp64;    /* products with A done for it: one per step, one   */
+  int matvecs_lowp;    /* more in a cycle that it leaves early, one FP64   */
+                       /* residual per cycle (and one for a start vector)  */
   double rel_residual; /* final FP64 true relative residual                  */
 } tm_solve_info;
 

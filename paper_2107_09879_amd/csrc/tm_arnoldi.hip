@@ -11,7 +11,8 @@
 //                one block per system meanwhile completes Hessenberg column j - 1
 //                (its first pass + s, alpha below), rotates it (Givens), tests
 //                convergence and reports the step
-// A system so needs one product and one kry_dots more than it has steps.
+// A system so needs one product and one kry_dots more than it has steps (no product
+// where the step that makes its last column final is the cycle's last).
 // The kernels report steps and convergence in pinned host memory; the host stays
 // at most KRY_AHEAD steps ahead and ends the cycle when it sees the flag, so a
 // stopped cycle costs a few empty launches.  Several right-hand sides share the
@@ -924,14 +925,15 @@ int kry_solve(tm_ctx* c, KryProblem& p, tm_solve_info* info) {
         bad[s] = 1;
       }
       beta[s] = k.h_beta[s];
-      const int n = k.h_jend[s];
-      taken = std::max(taken, n);
+      // a system that stopped before the cycle's end had one product more than steps
+      const int n = k.h_jend[s], products = n < jmax ? n + 1 : n;
+      taken = std::max(taken, products);
       info[s].iters += n;
       info[s].matvecs_fp64++;
-      (prec == TM_PREC_MIXED ? info[s].matvecs_lowp : info[s].matvecs_fp64) += n;
+      (prec == TM_PREC_MIXED ? info[s].matvecs_lowp : info[s].matvecs_fp64) += products;
     }
-    // products queued after the convergence test fired did no work: their
-    // profile records (the last ones of the Arnoldi loop) are dropped
+    // products queued after the last system stopped did no work: their profile
+    // records (the last ones of the Arnoldi loop) are dropped
     if (c->prof && taken < launched) {
       auto& pend = c->prof_pending[which_prof];
       const size_t drop = (size_t)(launched - taken);

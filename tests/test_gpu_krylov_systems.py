@@ -112,3 +112,34 @@ def test_solved_right_hand_sides_cost_no_product(product, precision):
     assert float(s4[[0, 1, 3]].abs().max()) == 0.0
     assert t4 < 2.0 * t1
     ctx.close()
+
+
+@pytest.mark.parametrize("precision", ["fp64", "mixed"])
+def test_products_are_counted(precision):
+    """One product per step, one more in a cycle that ends early (its last step's second
+    Gram-Schmidt pass), one FP64 residual per cycle and one for a start vector; the
+    profiler records as many."""
+    print(f"[case] {precision}", flush=True)
+    ctx = setup(14, 9, 2)
+    a0 = rhs(ctx, 1, 6)
+    which = {"fp64": 0, "mixed": 1}[precision]
+
+    def check(early, x0=None, **opts):
+        ctx.profile_reset()
+        ctx.profile_enable(True)
+        s, info = ctx.solve(a0, x0=x0, precision=precision, **opts)
+        ctx.profile_enable(False)
+        i = info[0]
+        arnoldi, residuals = i["iters"] + early(i), i["cycles"] + (x0 is not None)
+        want = (arnoldi + residuals, 0) if precision == "fp64" else (residuals, arnoldi)
+        assert (i["matvecs_fp64"], i["matvecs_lowp"]) == want, i
+        assert ctx.profile_query(which)[1] == want[which]
+        assert ctx.profile_query(1 - which)[1] == want[1 - which]
+        return s
+
+    # cycles that converge (in mixed precision, to the inner tolerance)
+    s = check(lambda i: i["cycles"], tol=1e-12, restart=200)
+    check(lambda i: i["cycles"], x0=s + 1e-3 * rhs(ctx, 1, 7), tol=1e-12, restart=200)
+    # cycles that run to their end: 5, 5 and 2 steps
+    check(lambda i: 0, tol=1e-30, restart=5, max_iter=12)
+    ctx.close()
