@@ -322,20 +322,23 @@ int tm_jinc_rhs_batched(tm_ctx* ctx, int n_sub, const tm_subregion* subs, int n_
  * captured hipGraph, 0 if it ran them eagerly. */
 int tm_batch_graph_used(const tm_ctx* ctx);
 
-/* Batched autotuner (the work items of the batched path, App. I.D's
- * subregion jobs sharing one launch).  on = 1: every later tm_solve_batched
- * first times one batched matvec, all systems active, for each table
- * prefetch depth (1..3 complex64, 1..2 FP64) and work split (16k, 32k, 64k
- * workgroups), in the precision of its Arnoldi steps, and keeps the fastest
- * (18 or 12 extra matvecs, synchronous).  on = 0 (default): about 32k
+/* Batched autotuner of the block kernels (the work items of the batched path,
+ * App. I.D's subregion jobs sharing one launch), which run where
+ * tm_set_matvec_config chose them or a subregion does not fit the transformed
+ * product; elsewhere it has no effect.  on = 1: every later tm_solve_batched
+ * by block kernels first times one batched matvec, all systems active, for
+ * each table prefetch depth (1..3 complex64, 1..2 FP64) and work split (16k,
+ * 32k, 64k workgroups), in the precision of its Arnoldi steps, and keeps the
+ * fastest (18 or 12 extra matvecs, synchronous).  on = 0 (default): about 32k
  * workgroups and the prefetch depth of the context's matvec variant
  * (tm_set_matvec_config; depth 1 for variants 0..7).  Every configuration
  * computes the same product up to rounding. */
 int tm_set_batch_autotune(tm_ctx* ctx, int on);
 
-/* Launch configuration the last tm_solve_batched used for `precision`
- * (TM_PREC_FP64 or TM_PREC_MIXED): table prefetch depth and work items per
- * (rhs, class) pair; both 0 before the first batched solve. */
+/* Launch configuration of the block kernels in the last tm_solve_batched for
+ * `precision` (TM_PREC_FP64 or TM_PREC_MIXED), whether or not they ran: table
+ * prefetch depth and work items per (rhs, class) pair; both 0 before the first
+ * batched solve. */
 int tm_get_batch_config(const tm_ctx* ctx, int precision, int* prefetch, int* items);
 
 /* ---- readout ------------------------------------------------------------- */
@@ -466,10 +469,12 @@ int tm_set_progress(tm_ctx* ctx, tm_progress_fn fn, void* user);
 
 /* ---- profiling ------------------------------------------------------------ */
 
-/* When enabled, the block-matvec launches are bracketed by HIP events on the
- * context stream and their durations accumulated per precision. */
+/* When enabled, the products with A (block kernels or transformed) are bracketed
+ * by HIP events on the context stream and their durations accumulated per
+ * precision. */
 int tm_profile_enable(tm_ctx* ctx, int enable);
-/* which: 0 = FP64 block matvec, 1 = complex64 block matvec.  Synchronises. */
+/* which: 0 = FP64 products, 1 = complex64 products.  flops_per_launch: of the
+ * dense block product that one stands for, however it was done.  Synchronises. */
 int tm_profile_query(tm_ctx* ctx, int which, double* total_ms, long long* launches,
                      double* flops_per_launch);
 int tm_profile_reset(tm_ctx* ctx);

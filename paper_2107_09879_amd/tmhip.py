@@ -449,7 +449,8 @@ class Context:
         self._check(self.lib.tm_set_batch_autotune(self.h, int(bool(on))))
 
     def batch_config(self, precision):
-        """(table prefetch depth, items per (rhs, class)) of the last batched solve."""
+        """(table prefetch depth, items per (rhs, class)) of the block kernels in the last batched
+        solve, whether or not they ran."""
         pf, it = ctypes.c_int(), ctypes.c_int()
         self._check(self.lib.tm_get_batch_config(self.h, PRECISIONS[precision], ctypes.byref(pf),
                                                  ctypes.byref(it)))

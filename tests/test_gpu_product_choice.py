@@ -93,3 +93,30 @@ def test_a_choice_holds_for_its_lattice_size(precision):
             assert not same(outputs(ctx, precision), outputs(fresh, precision))[0]
     ctx.close()
     fresh.close()
+
+
+@pytest.mark.parametrize("precision", PRECISIONS)
+@pytest.mark.parametrize("graph", [False, True])
+def test_batch_autotuner_of_the_block_kernels(precision, graph):
+    """With the block kernels chosen the batched autotuner really times and re-plans: a
+    candidate's configuration, and the solution of the default one and of the transform."""
+    print(f"[case] {precision} graph {graph}", flush=True)
+    kh, po = wl.incidences(["x", "p10", "y"])
+    subs = [(0, 0, 9, 20), (3, 2, 1, 1), (5, 4, 16, 7), (0, 0, 24, 20)]
+    out = []
+    for blocks, autotune in ((True, True), (True, False), (False, True)):
+        ctx = tmhip.Context(0)
+        set_lattice(ctx, 24, 20, 3)
+        if blocks:
+            ctx.set_matvec_config("fp64", 9, 0)
+            ctx.set_matvec_config("mixed", 8, 0)
+        ctx.set_batch_autotune(autotune)
+        s, info = ctx.solve_batched(subs, kh, po, use_graph=graph, tol=1e-12, restart=40, precision=precision)
+        assert all(i["status"] == 0 for q in info for i in q) and ctx.batch_graph_used() == graph
+        prefetch, items = ctx.batch_config(precision)
+        assert 1 <= prefetch <= (3 if precision == "mixed" else 2)
+        assert items in ([wg // 6 for wg in (16384, 32768, 65536)] if blocks and autotune else [32768 // 6])
+        out.append(torch.cat([q.reshape(-1) for q in s]))
+        ctx.close()
+    for o in out[1:]:
+        assert float(torch.linalg.vector_norm(o - out[0])) < 1e-9 * float(torch.linalg.vector_norm(out[0]))
