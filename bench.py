@@ -53,10 +53,6 @@ def kernel_names(variant, ctype):
     return [f"block_matvec_kernel<{ctype}, {str(bool(gauss)).lower()}, {str(bool(pref)).lower()}, {occ}>"]
 
 
-def kernel_name(variant, ctype):
-    return " + ".join(kernel_names(variant, ctype))
-
-
 MATVEC_SOURCES = ("paper_2107_09879_amd/csrc/tm_matvec_lds.hip", "paper_2107_09879_amd/csrc/tm_matvec.hip")
 
 
@@ -93,10 +89,23 @@ def measured_traffic(kernels, workload):
     return sum(rows[k] for k in kernels)
 
 
-def fraction(tflops, peak):
+def transformed(ctx, prec, boxes=None):
+    """Whether products of the context's lattice (or of subregions of these (nx, ny), which
+    then all take the same product) run by Fourier transform: unless the block kernels
+    were chosen, where rows and columns fit."""
+    side = {"fp64": (300, 300, 300, 150, 100, 100), "mixed": (320, 320, 320, 300, 200, 200)}[prec][ctx.lmax - 1]
+    return ctx.get_matvec_config(prec)[1] < 0 and all(nx <= 320 and ny <= side
+                                                      for nx, ny in boxes or [ctx.get_lattice()[:2]])
+
+
+def product_name(by_transform):
+    return "Fourier transform" if by_transform else "block kernels"
+
+
+def fraction(tflops, peak, by_transform):
     """Of the matrix peak; None where the product is done by Fourier transform, whose
-    time stands for more dense block products than the matrix cores could do."""
-    return tflops / peak if tflops <= peak else None
+    time stands for the dense block products and not for operations done."""
+    return None if by_transform else tflops / peak
 
 
 def transform_bytes(nx, ny, lmax, R):
@@ -109,10 +118,10 @@ def transform_bytes(nx, ny, lmax, R):
     return R * (4 * grid + 3 * nx * ny * 2 * S * 16) + symbol + nx * ny * 2 * S * 16
 
 
-def matvec_roofline(dom, lmax, nx, ny, R, workload, kernels):
+def matvec_roofline(dom, lmax, nx, ny, R, workload, kernels, by_transform):
     """Of the complex64 product in the timed region: matrix cores for the block
     kernels, memory for the transformed product."""
-    if fraction(dom["tflops"], PEAK_FP32_MFMA) is None:
+    if by_transform:
         nbytes = transform_bytes(nx, ny, lmax, R)
         achieved = nbytes / (dom["avg_launch_ms"] * 1e-3) / 1e9
         return {"bound": "hbm", "achieved": achieved, "peak": PEAK_HBM, "unit": "GB/s", "frac": achieved / PEAK_HBM,
@@ -167,28 +176,31 @@ def copy_calibration(torch, mib=512):
     del x, y
 
 
+def fixed_configs(args):
+    return {prec: (int(v), int(items)) for prec, v, items in (c.split(":") for c in args.matvec_config)}
+
+
 def tune_matvec(ctx, args, n_rhs):
-    """Block-matvec kernel of each precision: fixed by --matvec-config, else
+    """Product of each precision: block kernels fixed by --matvec-config, else
     autotuned on the context's geometry (set-up, outside any timed region)."""
     tuned = {}
-    fixed = {}
-    for spec in args.matvec_config:
-        prec, v, items = spec.split(":")
-        fixed[prec] = (int(v), int(items))
+    fixed = fixed_configs(args)
     for prec in ("mixed", "fp64"):
         if prec in fixed:
             ctx.set_matvec_config(prec, *fixed[prec])
-            tuned[prec] = {"variant": fixed[prec][0], "items": fixed[prec][1], "fixed": True}
+            tuned[prec] = {"variant": fixed[prec][0], "items": fixed[prec][1], "fixed": True,
+                           "product": product_name(transformed(ctx, prec))}
             log(f"[bench] {prec} matvec fixed: variant {fixed[prec][0]}, items {fixed[prec][1]}")
         elif not args.no_autotune:
             ms, conf = ctx.autotune(n_rhs, prec)
-            tuned[prec] = {"block_matvec_ms": ms, "variant": conf[0], "items": conf[1]}
-            log(f"[bench] autotune {prec}: {ms:.3f} ms, variant {conf[0]}, items {conf[1]}")
+            tuned[prec] = {"matvec_ms": ms, "variant": conf[0], "items": conf[1],
+                           "product": product_name(transformed(ctx, prec))}
+            log(f"[bench] autotune {prec}: {ms:.3f} ms, {tuned[prec]['product']} (variant {conf[0]}, items {conf[1]})")
     return tuned
 
 
 def isolated_matvec(ctx, n_rhs, reps):
-    """Average block-matvec launch of each precision over `reps` back-to-back
+    """Average product of each precision over `reps` back-to-back
     forward operators on a seeded random vector (HIP events on the library's
     stream), with the algorithmic FP32 / FP64 rate against the matrix peak."""
     import torch
@@ -208,9 +220,10 @@ def isolated_matvec(ctx, n_rhs, reps):
         ms, launches, flops = ctx.profile_query(which)
         avg = ms / max(launches, 1) / 1e3
         tf = flops / avg / 1e12
-        mv[prec] = {"avg_launch_ms": avg * 1e3, "tflops": tf, "peak_tflops": peak, "frac": fraction(tf, peak),
+        mv[prec] = {"avg_launch_ms": avg * 1e3, "tflops": tf, "peak_tflops": peak,
+                    "frac": fraction(tf, peak, transformed(ctx, prec)), "product": product_name(transformed(ctx, prec)),
                     "flops_per_launch": flops, "launches": launches}
-        log(f"[bench] {prec} block matvec: {avg*1e3:.3f} ms, {tf:.2f} TFLOP/s of dense block products")
+        log(f"[bench] {prec} matvec by {mv[prec]['product']}: {avg*1e3:.3f} ms, {tf:.2f} TFLOP/s of dense block products")
     ctx.profile_reset()
     return mv
 
@@ -232,8 +245,8 @@ def main():
     ap.add_argument("--no-sequential", action="store_true",
                     help="c3: skip the one-subregion-at-a-time comparison")
     ap.add_argument("--no-batch-autotune", action="store_true",
-                    help="c3: keep the batched path's default launch configuration instead of "
-                         "timing the candidates on the batch first")
+                    help="c3: keep the batched block kernels' default launch configuration instead of "
+                         "timing the candidates on the batch first (where those run and not the transform)")
     ap.add_argument("--restart", type=int, default=0,
                     help="c3, c5: GMRES restart length (default: the workload's, 50)")
     ap.add_argument("--tile-iters", type=int, default=300,
@@ -252,8 +265,8 @@ def main():
     ap.add_argument("--offl-max-iter", type=int, default=5000,
                     help="offl: Arnoldi steps allowed to the solve of each step")
     ap.add_argument("--matvec-config", action="append", default=[], metavar="PREC:VARIANT:ITEMS",
-                    help="fix the block-matvec kernel of a precision (mixed or fp64) instead of "
-                         "autotuning it, e.g. mixed:9:16384")
+                    help="block kernels for a precision (mixed or fp64) instead of what the autotuner "
+                         "(c5: the default) takes, e.g. mixed:9:16384; items < 0: the transformed product")
     args = ap.parse_args()
     if args.gpus != 1:
         print("bench.py measures one GPU only; there is no multi-GPU path. Use --gpus 1.", file=sys.stderr)
@@ -306,7 +319,7 @@ def main():
         log(f"[bench] warmup {w}: {info}")
     copy_calibration(torch)
     # timed region; the library records HIP events on its own stream around
-    # every block-matvec launch, which gives the kernel's average duration
+    # every product, which gives its average duration
     ctx.profile_reset()
     ctx.profile_enable(True)
     torch.cuda.synchronize()
@@ -325,7 +338,8 @@ def main():
         if launches:
             avg = ms / launches / 1e3
             live[prec] = {"avg_launch_ms": avg * 1e3, "launches": launches, "flops_per_launch": flops,
-                          "tflops": flops / avg / 1e12, "frac": fraction(flops / avg / 1e12, peak)}
+                          "tflops": flops / avg / 1e12, "frac": fraction(flops / avg / 1e12, peak, transformed(ctx, prec)),
+                          "product": product_name(transformed(ctx, prec))}
     ctx.profile_reset()
     log(f"[bench] mixed time-to-solution {dt:.4f} s/step, info {infos[-1]}, matvec {live}")
 
@@ -340,7 +354,7 @@ def main():
         d = (s - s64).abs().pow(2).sum().sqrt() / s64.abs().pow(2).sum().sqrt()
         fp64["mixed_vs_fp64_rel_diff"] = float(d)
 
-    # block-matvec throughput in isolation (same kernels, back to back)
+    # the products' throughput in isolation (same kernels, back to back)
     mv = isolated_matvec(ctx, len(kh), args.matvec_reps)
 
     # algorithmic bytes of one complex64 matvec: table + input + output
@@ -381,7 +395,7 @@ def main():
         "matvec_timed_region": live,
         "matvec_isolated": mv,
         "matvec_algorithmic_GBps": gbs,
-        "roofline": matvec_roofline(dom, lmax, n, n, len(kh), cfg["name"], knames),
+        "roofline": matvec_roofline(dom, lmax, n, n, len(kh), cfg["name"], knames, transformed(ctx, "mixed")),
         "cpu_baseline": cpu,
         **extra,
     }
@@ -391,7 +405,7 @@ def main():
 
 def bench_tile(args):
     """300 x 300 lens tile (9e4 spheres, lmax 3, 2 RHS): translation-table
-    build, block-matvec throughput in both precisions, a bounded
+    build, product throughput in both precisions, a bounded
     mixed-precision solve (its residual history gives an extrapolated
     time-to-solution, labelled as such), and the scattered field on a
     1000 x 1000 plane 5 wavelengths above the lattice."""
@@ -411,16 +425,14 @@ def bench_tile(args):
     t_table = time.perf_counter() - t0
     ctx.set_spheres(torch.tensor(radii, dtype=torch.float64, device="cuda"), wl.N_REL)
     log(f"[bench] tile: N={N}, table build {t_table:.2f} s")
-    fixed = {"mixed": (9, 32768 // (2 * R)), "fp64": (8, 16384 // (2 * R))}
-    for spec in args.matvec_config:
-        prec, v, items = spec.split(":")
-        fixed[prec] = (int(v), int(items))
+    fixed = fixed_configs(args)
     rng = np.random.default_rng(0)
     x = torch.tensor(rng.normal(size=(R, N, ctx.L)) + 1j * rng.normal(size=(R, N, ctx.L)),
                      dtype=torch.complex128, device="cuda")
     mv = {}
     for which, prec, peak in ((1, "mixed", PEAK_FP32_MFMA), (0, "fp64", PEAK_FP64_MFMA)):
-        ctx.set_matvec_config(prec, *fixed[prec])
+        if prec in fixed:
+            ctx.set_matvec_config(prec, *fixed[prec])
         ctx.apply_operator(x, "forward", prec)
         ctx.profile_reset()
         ctx.profile_enable(True)
@@ -429,9 +441,12 @@ def bench_tile(args):
         ctx.profile_enable(False)
         ms, launches, flops = ctx.profile_query(which)
         avg = ms / launches / 1e3
-        mv[prec] = {"variant": fixed[prec][0], "items": fixed[prec][1], "avg_launch_ms": avg * 1e3,
-                    "tflops": flops / avg / 1e12, "frac": fraction(flops / avg / 1e12, peak), "rhs": R}
-        log(f"[bench] tile {prec} block matvec ({R} RHS): {avg*1e3:.1f} ms, {flops/avg/1e12:.2f} TFLOP/s")
+        conf, by_transform = ctx.get_matvec_config(prec), transformed(ctx, prec)
+        mv[prec] = {"variant": conf[0], "items": conf[1], "product": product_name(by_transform),
+                    "avg_launch_ms": avg * 1e3, "tflops": flops / avg / 1e12, "flops_per_launch": flops,
+                    "frac": fraction(flops / avg / 1e12, peak, by_transform), "rhs": R}
+        log(f"[bench] tile {prec} matvec by {mv[prec]['product']} ({R} RHS): {avg*1e3:.3f} ms, "
+            f"{flops/avg/1e12:.2f} TFLOP/s of dense block products")
     ctx.profile_reset()
     del x
     hist = []
@@ -476,7 +491,7 @@ def bench_tile(args):
         f"extrapolation {extrap}")
     nf = None if full else near_field_plane(ctx, s, cfg)
     out = {"metric": "time-to-solution at 1e-8 residual + translation-matvec GB/s, 1e4-1e5 scatterers",
-           "value": mv["mixed"]["avg_launch_ms"], "unit": "ms per c64 block matvec (2 RHS)",
+           "value": mv["mixed"]["avg_launch_ms"], "unit": "ms per c64 matvec (2 RHS)",
            "n_gpus": 1, "steps": 3, "warmup": 1, "ms_per_step": mv["mixed"]["avg_launch_ms"],
            "higher_is_better": False, "scaling": "weak", "vs_baseline": None, "dtype": "c64+f64",
            "data": "synthetic", "config": {"workload": cfg["name"], "scatterers": N, "lmax": lmax, "rhs": R,
@@ -487,9 +502,8 @@ def bench_tile(args):
                              "max_iter": args.tile_max_iter, "time_s": t_solve, "info": info}
            if full else None,
            "time_to_solution_extrapolated": None if full else extrap, "near_field": nf,
-           "roofline": {"bound": "mfma", "achieved": mv["mixed"]["tflops"], "peak": PEAK_FP32_MFMA,
-                        "unit": "TFLOP/s", "frac": mv["mixed"]["frac"], "traffic": None,
-                        "kernel": kernel_name(fixed["mixed"][0], "float")}}
+           "roofline": matvec_roofline(mv["mixed"], lmax, n, n, R, cfg["name"],
+                                       kernel_names(mv["mixed"]["variant"], "float"), transformed(ctx, "mixed"))}
     print(json.dumps(out), flush=True)
     ctx.close()
 
@@ -531,7 +545,7 @@ def bench_cylinders(args):
     null-field T per cylinder).  One step is the sphere workloads' step with
     the T-matrices built by the null-field kernel: translation table, T,
     plane-wave right-hand side, mixed-precision GMRES to 1e-8 and the far
-    field.  Then the lmax-6 block matvec in isolation in both precisions."""
+    field.  Then the lmax-6 product in isolation in both precisions."""
     import torch
 
     import workloads as wl
@@ -593,7 +607,8 @@ def bench_cylinders(args):
         if launches:
             avg = ms / launches / 1e3
             live[prec] = {"avg_launch_ms": avg * 1e3, "launches": launches, "flops_per_launch": flops,
-                          "tflops": flops / avg / 1e12, "frac": fraction(flops / avg / 1e12, peak)}
+                          "tflops": flops / avg / 1e12, "frac": fraction(flops / avg / 1e12, peak, transformed(ctx, prec)),
+                          "product": product_name(transformed(ctx, prec))}
     ctx.profile_reset()
     ctx.set_progress(None)
     log(f"[bench] cylinders time-to-solution {dt:.3f} s/step, matvec {live}")
@@ -615,7 +630,7 @@ def bench_cylinders(args):
            "solve_info": info[0], "phases_s": ph, "autotuned": tuned,
            "matvec_timed_region": live, "matvec_isolated": mv,
            "matvec_algorithmic_GBps": alg_bytes / (dom["avg_launch_ms"] / 1e3) / 1e9,
-           "roofline": matvec_roofline(dom, lmax, n, n, R, cfg["name"], knames)}
+           "roofline": matvec_roofline(dom, lmax, n, n, R, cfg["name"], knames, transformed(ctx, "mixed"))}
     print(json.dumps(out), flush=True)
     ctx.close()
 
@@ -774,9 +789,11 @@ def bench_batched(args):
         dt = time.perf_counter() - t0
         flat = [i for row in info for i in row]
         pf, items = ctx.batch_config(prec)
+        by_transform = transformed(ctx, prec, [q[2:] for q in subs])
         res[prec] = {"time_s": dt, "graph": ctx.batch_graph_used(),
-                     "launch": {"autotuned": not args.no_batch_autotune, "prefetch": pf,
-                                "items_per_rhs_class": items},
+                     "product": product_name(by_transform),
+                     "launch": None if by_transform else {"autotuned": not args.no_batch_autotune, "prefetch": pf,
+                                                          "items_per_rhs_class": items},
                      "iters_max": max(i["iters"] for i in flat),
                      "iters_mean": float(np.mean([i["iters"] for i in flat])),
                      "converged": sum(i["status"] == 0 for i in flat), "systems": len(flat),
@@ -949,7 +966,7 @@ def bench_adjoint(args):
     t_grad = time.perf_counter() - t0
     log(f"[bench] forward+adjoint+gradient {t_grad:.2f} s, O={O:.6e}, fwd {info_f[0]}, adj {info_a[0]}")
     # in-plane position gradient from the same two solutions (coupling, incident and detector
-    # terms); the first call also builds the four FP64 derivative tables
+    # terms); the first call also builds the symbols of the derivatives (block kernels: tables)
     gpos = {}
     for key in ("first_call_s", "s"):
         if key == "s":
@@ -966,7 +983,7 @@ def bench_adjoint(args):
         avg = ms / launches / 1e3
         gpos["derivative_matvecs"] = {"launches": launches, "avg_launch_ms": avg * 1e3,
                                       "tflops": flops / avg / 1e12,
-                                      "frac": fraction(flops / avg / 1e12, PEAK_FP64_MFMA)}
+                                      "frac": fraction(flops / avg / 1e12, PEAK_FP64_MFMA, transformed(ctx, "fp64"))}
     ctx.profile_reset()
     log(f"[bench] position gradient {gpos}")
     idx = np.random.default_rng(5).choice(len(radii), 20, replace=False)[: max(1, args.steps)]
