@@ -856,9 +856,11 @@ bool spec_use(tm_ctx* c, int which) {
   return c->spec_fit[which];
 }
 
+// The limit belongs to the kernel and not to the launch: always the same one, as another
+// thread may be about to launch the kernel on a larger lattice.
 static int allow_lds(tm_ctx* c, const void* f, size_t bytes) {
   if (bytes <= 64 * 1024) return TM_OK;
-  TM_HIP(c, hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes));
+  TM_HIP(c, hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)SPEC_LDS_MAX));
   return TM_OK;
 }
 
