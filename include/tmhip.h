@@ -263,9 +263,11 @@ typedef struct {
 /* Solve every subregion alone (scatterers outside it are ignored: the
  * subregion-plus-padding decomposition of the paper's distribution strategy)
  * for n_rhs plane waves (khat/pol: host [R][3], as tm_plane_wave_rhs), all
- * (subregion, rhs) systems advancing together: one block-matvec launch per
+ * (subregion, rhs) systems advancing together: one product per
  * Arnoldi step covers every system, each restart cycle is replayed from a
- * captured hipGraph when use_graph != 0, converged systems leave the batch.
+ * captured hipGraph when use_graph != 0 (while a call records them the HIP
+ * runtime can refuse synchronous copies of other threads, and theirs can end the
+ * recording: with several threads pass 0), converged systems leave the batch.
  * Geometry (the full lattice) and T must be set.  subs: host [S];
  * s_out: device, the subregions' [R][N_k][L] coefficient blocks concatenated
  * in subregion order (site index within a subregion ly*side_x + lx);

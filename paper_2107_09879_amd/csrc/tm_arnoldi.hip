@@ -175,7 +175,10 @@ __device__ inline double system_norm(const Kry& k, int s, double* sh) {
 }
 
 // The step's scalars from its sums, alike in every wave: alpha = |u - Q s|, and the
-// component of w along the new q_j.
+// component of w along the new q_j.  |u|^2 - |s|^2 loses alpha where u is left with no
+// more than rounding (s as large as u): from 0 on down it counts as 0, an exact
+// breakdown, which ends the cycle; the cycle's true residual decides whether another
+// one follows.
 struct KryStep {
   double alpha, f;
   c128 zeta;
@@ -776,7 +779,8 @@ int kry_solve(tm_ctx* c, KryProblem& p, tm_solve_info* info) {
     TM_HIP(c, hipGetLastError());
     return TM_OK;
   };
-  // until the GPU has finished `steps` steps of the cycle, or all of it
+  // until the GPU has finished `steps` steps of the cycle, or all of it: spins (a step
+  // takes 20 to 100 us, which a sleeping thread would miss)
   auto wait_steps = [&](int steps, hipStream_t s) -> int {
     for (unsigned spin = 1; hctl[KRY_HOST_STEPS] < steps && !hctl[KRY_HOST_DONE]; ++spin) {
       if (spin & 1023) continue;

@@ -6,8 +6,8 @@
 // with M the translation of App. I.C, eq. "tran_coeff".
 //
 // A translation along the z axis couples no two azimuthal orders, so the block
-// is applied as rotation, axial translation, rotation back: for d = (r, phi) in
-// the plane
+// is applied as rotation, axial translation, rotation back (White and Head-Gordon
+// 1996, there for the Laplace equation): for d = (r, phi) in the plane
 //   M = e^{-i m phi} B^T Z(r) B e^{i m phi},
 // B the rotation that turns x into z (Wigner's d^l_{m'm}(pi/2), constant, one
 // block per (l, p)) and Z the coefficients of eq. "tran_coeff" at theta = 0:
@@ -22,8 +22,8 @@
 // At lmax 3 this is about 1 400 FMAs per pair for both classes; forming the
 // 450 entries of the block, as before, took 16 400.  Operator on a jittered
 // lattice, complex64 (bound by FP32 VALU issue) and FP64: 100x100 at lmax 3
-// 46.4 -> 2.7 ms and 117 -> 6.9 ms, 28x30 1.58 -> 0.06 ms and 3.97 -> 0.09 ms,
-// 10x10 at lmax 6 27.6 -> 0.08 ms and 49.3 -> 0.19 ms.
+// 46.4 -> 2.5 ms and 117 -> 6.7 ms, 28x30 1.58 -> 0.044 ms and 3.97 -> 0.066 ms,
+// 10x10 at lmax 6 27.6 -> 0.075 ms and 49.3 -> 0.14 ms.
 //
 // A workgroup is two or four waves on the same 64 targets, each with its share
 // of the sources; their sums meet in LDS.  The workgroups of a launch split the sources into
@@ -576,8 +576,9 @@ static int ol_launch(tm_ctx* c, bool tr, int R, int& nchunk, const void* xin, un
   const int N = g.n;
   // about 1500 waves (the chip's 1024 SIMDs with some to spare), at least 8
   // sources each so that the sums' way through LDS and memory stays small.  For each
-  // right-hand side, as the others may have left the solve (512 MB of partial sums at
-  // most), else for all together.
+  // right-hand side, as the others may have left the solve (48x48 at lmax 3 FP64, one
+  // of four left: 1.45 s a solve with the chunks cut for all, 0.75 so), with 512 MB of
+  // partial sums at most; past that for all together.
   const int tb = (N + OL_TARGETS - 1) / OL_TARGETS, gy = 3 - NC, W = Cfg::WAVES;
   auto chunks = [&](int rows) { return std::max(1, std::min((N + 8 * W - 1) / (8 * W), 1536 / (W * tb * rows) + 1)); };
   const size_t one = (size_t)g.vec_len() * R * sizeof(cplx<T>);

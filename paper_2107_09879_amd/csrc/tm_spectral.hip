@@ -27,8 +27,8 @@
 // Bound: at 100x100, lmax 3 each launch moves 10-20 MB in a few microseconds and
 // the barriers and LDS round trips between stages set the time.  Operator with its
 // layout conversions, one right-hand side: 100x100 FP64 5.6 ms (block kernels) ->
-// 78 us, complex64 2.67 ms -> 58 us; 150x150 26.3 ms -> 150 us and 13.0 ms ->
-// 94 us; 33x31 at lmax 6 FP64 1.15 ms -> 70 us; 8x8 at lmax 2 100 -> 27 us, so no
+// 71 us, complex64 2.67 ms -> 53 us; 150x150 26.3 ms -> 142 us and 13.0 ms ->
+// 87 us; 33x31 at lmax 6 FP64 1.15 ms -> 63 us; 8x8 at lmax 2 100 -> 19 us, so no
 // lattice that fits is left to the block kernels.  Error against 64-bit sums of
 // the forward operator at 100x100: FP64 5.4e-16 (block kernels 1.3e-15), complex64
 // 9.7e-8 (6.1e-7).
