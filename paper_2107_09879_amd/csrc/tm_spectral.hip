@@ -425,7 +425,9 @@ __device__ __forceinline__ void block_rows(const T* cf, const cplx<T>* const* fr
 
 // blockIdx.x: column (position of kx), blockIdx.y: (rhs, class).
 // Block products: 64 / GROUPS lanes per (ky, -ky) pair, lane i < MEM the target.
-// Bound by LDS: forming an entry takes NQ constants and NQ fields.  So a lane works
+// Bound by LDS and by latency (100x100 FP64: LDS active in 51 % of the busy CU cycles,
+// half of that bank conflicts, FP64 issue 30 %; 150x150 FP32 45 %, a quarter, 25 %):
+// forming an entry takes NQ constants and NQ fields.  So a lane works
 // on PB pairs with one load of the constants, fields are loaded once for all
 // sources of an order m, and at lmax <= 3 (a pair's lanes are one row of 16) the
 // vectors' entries come by DPP instead of LDS broadcasts.  The next pairs' symbol
