@@ -570,8 +570,10 @@ static int solve_common(tm_ctx* c, Op op, int R, const tm_c128* rhs, tm_c128* ou
     p.x0 = o->use_x0 != 0;
     p.apply = [&](int prec, const c128* x, c128* y, const int* active) {
       c->mv_active = active;
+      c->mv_live = p.live;
       const int e = tmh::apply_op(c, op, prec, n, x, y);
       c->mv_active = nullptr;
+      c->mv_live = 0;
       return e;
     };
     if (c->progress) {

@@ -58,6 +58,7 @@ struct KryProblem {
   std::function<void(int, int, int, double)> progress;
   std::function<void(int, int, double)> progress_inside;  // every 50 steps: cycles, steps, residual
   bool graphed = false;         // out: cycles were replayed from graphs
+  int live = 0;                 // for `apply`: systems left at the cycle's start (0: all)
 };
 
 int kry_solve(tm_ctx* c, KryProblem& p, tm_solve_info* info);

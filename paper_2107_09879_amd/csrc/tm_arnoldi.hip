@@ -849,6 +849,7 @@ int kry_solve(tm_ctx* c, KryProblem& p, tm_solve_info* info) {
       if (live[s]) worst = std::max(worst, relres[s]);
     }
     if (!nlive) break;
+    p.live = nlive;
     if (p.progress) p.progress(cyc, it_most, nlive, worst);
     for (int s = 0; s < ns; ++s) {
       k.h_live[s] = live[s];

@@ -162,6 +162,7 @@ struct tm_ctx {
   // pointed-to flag is nonzero (the GMRES cycle has stopped), and leave out
   // right-hand sides whose flag is zero
   const int *mv_stop = nullptr, *mv_active = nullptr;
+  int mv_live = 0;  // how many are left at the cycle's start (0: all)
   // profiling
   bool prof = false;
   hipEvent_t ev0 = nullptr, ev1 = nullptr;

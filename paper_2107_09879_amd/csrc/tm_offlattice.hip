@@ -575,14 +575,16 @@ static int ol_launch(tm_ctx* c, bool tr, int R, int& nchunk, const void* xin, un
   const Geometry& g = c->g;
   const int N = g.n;
   // about 1500 waves (the chip's 1024 SIMDs with some to spare), at least 8
-  // sources each so that the sums' way through LDS and memory stays small.  For each
-  // right-hand side, as the others may have left the solve (48x48 at lmax 3 FP64, one
-  // of four left: 1.45 s a solve with the chunks cut for all, 0.75 so), with 512 MB of
-  // partial sums at most; past that for all together.
+  // sources each so that the sums' way through LDS and memory stays small.  For the
+  // right-hand sides that a solve still has (48x48 at lmax 3 FP64, one of four left: 1.45 s
+  // a solve with the chunks cut for all, 0.75 so), with 512 MB of partial sums at most.
+  // Cut for one where all run, as if the others could leave at any step, products took
+  // up to 17 % longer (30x30 at lmax 5 mixed, four right-hand sides 339 -> 398 us).
   const int tb = (N + OL_TARGETS - 1) / OL_TARGETS, gy = 3 - NC, W = Cfg::WAVES;
   auto chunks = [&](int rows) { return std::max(1, std::min((N + 8 * W - 1) / (8 * W), 1536 / (W * tb * rows) + 1)); };
   const size_t one = (size_t)g.vec_len() * R * sizeof(cplx<T>);
-  nchunk = std::max<int>(chunks(gy * R), (int)std::min<size_t>(chunks(gy), ((size_t)512 << 20) / one));
+  const int live = c->mv_live > 0 ? c->mv_live : R;
+  nchunk = std::max<int>(chunks(gy * R), (int)std::min<size_t>(chunks(gy * live), ((size_t)512 << 20) / one));
   const int chunk = (N + nchunk - 1) / nchunk;
   nchunk = (N + chunk - 1) / chunk;
   int rc;
